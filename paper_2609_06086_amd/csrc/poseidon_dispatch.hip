@@ -46,27 +46,21 @@ void *noalloc_scratch(int device) {
 
 size_t noalloc_scratch_bytes() { return sizeof(scratch); }
 
-#define PK_EXTERN(S)                                                                                     \
-    extern template hipError_t launch_eval_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);    \
-    extern template hipError_t launch_eval_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);    \
-    extern template hipError_t launch_decode_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);  \
-    extern template hipError_t launch_decode_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);  \
-    extern template hipError_t launch_resume_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t,   \
-                                                             uint32_t);                                       \
-    extern template hipError_t launch_resume_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t,   \
-                                                             uint32_t);                                       \
-    extern template hipError_t launch_bounded_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t,  \
-                                                              uint32_t);                                      \
-    extern template hipError_t launch_bounded_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t,  \
-                                                              uint32_t);                                      \
-    extern template hipError_t occupancy_s<S, uint32_t>(int *, size_t, bool, bool);                                 \
-    extern template hipError_t occupancy_s<S, uint64_t>(int *, size_t, bool, bool);                                 \
-    extern template hipError_t filter_occupancy_s<S, uint32_t>(const KParams &, size_t, int *);                     \
-    extern template hipError_t filter_occupancy_s<S, uint64_t>(const KParams &, size_t, int *);                     \
-    extern template hipError_t launch_search_s<S, uint32_t>(int, const KParams &, const SearchParams &, uint32_t,   \
-                                                             size_t, hipStream_t);                                  \
-    extern template hipError_t launch_search_s<S, uint64_t>(int, const KParams &, const SearchParams &, uint32_t,   \
-                                                             size_t, hipStream_t);
+#define PK_EXTERN(S)                                                                                                  \
+    extern template hipError_t launch_eval_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
+    extern template hipError_t launch_closed_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                       \
+    extern template hipError_t launch_full_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
+    extern template hipError_t launch_decode_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
+    extern template hipError_t launch_decode_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
+    extern template hipError_t launch_bounded_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t, uint32_t);  \
+    extern template hipError_t launch_bounded_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t, uint32_t);  \
+    extern template hipError_t occupancy_s<S>(const KParams &, size_t, int *, int *);                                     \
+    extern template hipError_t filter_occupancy_s<S, uint32_t>(const KParams &, size_t, int *);                           \
+    extern template hipError_t filter_occupancy_s<S, uint64_t>(const KParams &, size_t, int *);                           \
+    extern template hipError_t launch_search_s<S, uint32_t>(int, const KParams &, const SearchParams &, uint32_t, size_t, \
+                                                            hipStream_t);                                                 \
+    extern template hipError_t launch_search_s<S, uint64_t>(int, const KParams &, const SearchParams &, uint32_t, size_t, \
+                                                            hipStream_t);
 
 PK_EXTERN(1) PK_EXTERN(2) PK_EXTERN(3) PK_EXTERN(4) PK_EXTERN(5) PK_EXTERN(6) PK_EXTERN(7) PK_EXTERN(8)
 PK_EXTERN(9) PK_EXTERN(10) PK_EXTERN(11) PK_EXTERN(12) PK_EXTERN(13) PK_EXTERN(14) PK_EXTERN(15) PK_EXTERN(16)
@@ -166,18 +160,43 @@ __global__ void fill_u64(unsigned long long *p, uint32_t n, unsigned long long v
     default: return hipErrorInvalidValue;                                                      \
     }
 
+// The same over the stage count alone.
+#define PK_DISPATCH_S(FN, S_, ...)                          \
+    switch (S_) {                                           \
+    case 1: return FN<1>(__VA_ARGS__);                      \
+    case 2: return FN<2>(__VA_ARGS__);                      \
+    case 3: return FN<3>(__VA_ARGS__);                      \
+    case 4: return FN<4>(__VA_ARGS__);                      \
+    case 5: return FN<5>(__VA_ARGS__);                      \
+    case 6: return FN<6>(__VA_ARGS__);                      \
+    case 7: return FN<7>(__VA_ARGS__);                      \
+    case 8: return FN<8>(__VA_ARGS__);                      \
+    case 9: return FN<9>(__VA_ARGS__);                      \
+    case 10: return FN<10>(__VA_ARGS__);                    \
+    case 11: return FN<11>(__VA_ARGS__);                    \
+    case 12: return FN<12>(__VA_ARGS__);                    \
+    case 13: return FN<13>(__VA_ARGS__);                    \
+    case 14: return FN<14>(__VA_ARGS__);                    \
+    case 15: return FN<15>(__VA_ARGS__);                    \
+    case 16: return FN<16>(__VA_ARGS__);                    \
+    default: return hipErrorInvalidValue;                   \
+    }
+
 hipError_t launch_eval(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
     if (p.sched == 2) return launch_ilv(p, lc, st);   // Interleaved 1F1B
-    PK_DISPATCH(launch_eval_s, p.S, p.wide, p, lc, st)
+    PK_DISPATCH_S(launch_eval_s, p.S, p, lc, st)
 }
 
 hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
     PK_DISPATCH(launch_decode_s, p.S, p.wide, p, lc, st)
 }
 
-hipError_t launch_resume(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t lvl) {
-    if (p.sched == 2) return launch_ilv_resume(p, lc, st, lvl);   // Interleaved 1F1B
-    PK_DISPATCH(launch_resume_s, p.S, p.wide, p, lc, st, lvl)
+hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    PK_DISPATCH_S(launch_closed_s, p.S, p, lc, st)
+}
+
+hipError_t launch_full(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    PK_DISPATCH_S(launch_full_s, p.S, p, lc, st)
 }
 
 hipError_t launch_bounded(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t publish) {
@@ -188,9 +207,10 @@ hipError_t filter_occupancy(const KParams &p, size_t ent_lds, int *blocks) {
     PK_DISPATCH(filter_occupancy_s, p.S, p.wide, p, ent_lds, blocks)
 }
 
-hipError_t eval_occupancy(const KParams &p, size_t lds, int *blocks) {
+hipError_t eval_occupancy(const KParams &p, size_t lds, int *blocks, int *full) {
+    *full = 0;
     if (p.sched == 2) return ilv_occupancy(p, lds, blocks);
-    PK_DISPATCH(occupancy_s, p.S, p.wide, blocks, lds, p.has_ar != 0, p.sched != 0)
+    PK_DISPATCH_S(occupancy_s, p.S, p, lds, blocks, full)
 }
 
 hipError_t launch_argmin(const uint32_t *T, const uint32_t *bits, uint64_t count, uint32_t grid,

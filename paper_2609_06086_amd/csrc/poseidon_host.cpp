@@ -338,8 +338,10 @@ struct poseidon_ctx {
     size_t ent_lds_bytes;  // stage entries (and pdx): evaluation and early-stop kernels
     uint32_t filter_grid;  // blocks of the early-stop filter that are resident at once
     uint32_t grid_max;
+    uint32_t full_grid;    // blocks of the recurrence pass behind the closed form
     void *ws;              // cut codes + straggler queues of the steady-state cascade
-    uint64_t ws_cap;       // candidates per chunk the workspace holds
+    uint64_t ws_n;         // candidates per chunk the workspace is for
+    uint64_t ws_cap;       // entries of its arrays (ws_n and slack for per-block segments)
     void *sws;             // search frontiers (allocated on the first poseidon_search)
     unsigned long long *shost;   // pinned host words for the search's read-backs (level totals
                                  // and block offsets), allocated with sws
@@ -565,10 +567,26 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
         }
     }
     for (uint32_t s = 1; s < S; ++s) kp.psi[s] = kp.psi[s - 1] + kp.cf[s - 1];
+    // closed form (poseidon_closed.h); with fewer micro-batches the steady
+    // part is at most S + 1 (Eager 1F1B: 2S + 2) iterations of the recurrence
+    kp.closed = !ilv && !table_path && M >= (eager ? 4 * S + 2 : 2 * S + 2);
+    std::vector<uint32_t> ctab(pk::kCRows * pk::kSMax, 0);
+    for (uint32_t s = 0; s < S; ++s) {
+        auto row = [&](int r) { return &ctab[(size_t)r * pk::kSMax]; };
+        const uint32_t lo = s > 0 ? row(pk::kCE)[s - 1] : 0u, hi = s + 1 < S ? kp.cf[s] + kp.cb[s] : 0u;
+        row(pk::kCE)[s] = hi;
+        row(pk::kCSum)[s] = s > 0 ? row(pk::kCSum)[s - 1] + lo : 0u;
+        row(pk::kCE2)[s] = lo + hi;
+        // (1F1B, M > S; at most M times the boundaries' sum, below 2^31)
+        if (kp.closed) row(pk::kCE2n)[s] = (M - S - 1 + s) * (lo + hi);
+        row(pk::kCCb)[s] = s + 1 < S ? kp.cb[s] : 0u;
+        row(pk::kCPsi)[s] = s > 0 ? row(pk::kCPsi)[s - 1] + kp.cb[s - 1] : 0u;
+        kp.edge_max = std::max(kp.edge_max, hi);
+    }
     // cascade checkpoints of the steady loop: K0, 2 K0, 4 K0, ... below M - S
     // (steady iterations: 1F1B slot pairs after its prologue, Eager 1F1B
     // slot pairs between its prologue and epilogue)
-    if (!table_path) {   // (no cascade for the slot-table paths)
+    if (kp.closed) {   // (the recurrence of the candidates without a closed form)
         const uint32_t nit = eager ? M + 1 - 2 * S : M - S;
         uint32_t k = std::max<uint32_t>(2, eager ? PK_EAGER_K0 : PK_CASCADE_K0);
         while (k < nit && kp.nlevels < (uint32_t)pk::kMaxLevels) {
@@ -624,7 +642,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
             kp.g24 = 0;
     static_assert(7 * 4 * pk::kEntField < 65536, "entry-block offsets fit 16 bits");
 
-    // one device block: state words | cost | pm | cap | binom | assign | slots
+    // one device block: state words, the tables, and last the assignment table
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t off = 0;
     const size_t o_state = off; off = al(off + W_COUNT * 8);
@@ -633,10 +651,11 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     const size_t o_cap = off; off = al(off + (size_t)T * 4);
     const size_t o_binom = off; off = al(off + binom.size());
     const size_t o_btab = off; off = al(off + btab.size());
-    const size_t o_assign = off; off = al(off + (has_table ? (size_t)A * ndev : 0));
     const size_t o_slots = off; off = al(off + (table_path ? masks.size() * 4 : 0));
     const size_t o_pd = off; off = al(off + pd.size() * 4);
     const size_t o_ent = off; off = al(off + ent.size() * 4);
+    const size_t o_ctab = off; off = al(off + ctab.size() * 4);
+    const size_t o_assign = off; off = al(off + (has_table ? (size_t)A * ndev : 0));   // (last: not part of the image)
     const size_t total = off;
 
     poseidon_ctx *ctx = new (std::nothrow) poseidon_ctx;
@@ -649,24 +668,31 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     }
     int status = POSEIDON_OK;
     void *d = nullptr;
+    std::vector<unsigned char> img;
     do {
         if (hipMalloc(&d, total) != hipSuccess) { status = POSEIDON_E_NOMEM; break; }
         unsigned char *b = (unsigned char *)d;
         std::vector<unsigned long long> st(W_COUNT, 0);
         st[W_ACC] = ~0ull; st[W_RESULT] = ~0ull; st[W_RUN] = ~0ull; st[W_SNAP] = ~0ull;
-        bool ok = hipMemcpy(b + o_state, st.data(), W_COUNT * 8, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemcpy(b + o_cost, cost.data(), cost.size() * 8, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemcpy(b + o_pm, pm.data(), pm.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemcpy(b + o_cap, p->cap_mb, (size_t)T * 4, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemcpy(b + o_binom, binom.data(), binom.size(), hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemcpy(b + o_btab, btab.data(), btab.size(), hipMemcpyHostToDevice) == hipSuccess;
-        if (ok && has_table)
-            ok = hipMemcpy(b + o_assign, p->assign, (size_t)A * ndev, hipMemcpyHostToDevice) == hipSuccess;
-        if (ok && table_path)
-            ok = hipMemcpy(b + o_slots, masks.data(), masks.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
-        if (ok && has_ar) ok = hipMemcpy(b + o_pd, pd.data(), pd.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
-        if (ok) ok = hipMemcpy(b + o_ent, ent.data(), ent.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
-        if (!ok) { status = POSEIDON_E_DEVICE; break; }
+        // one image and one copy (the assignment table goes straight from the caller's memory)
+        img.resize(o_assign, 0);
+        auto put = [&img](size_t o, const void *src, size_t bytes) { if (bytes) memcpy(&img[o], src, bytes); };
+        put(o_state, st.data(), W_COUNT * 8);
+        put(o_cost, cost.data(), cost.size() * 8);
+        put(o_pm, pm.data(), pm.size() * 4);
+        put(o_cap, p->cap_mb, (size_t)T * 4);
+        put(o_binom, binom.data(), binom.size());
+        put(o_btab, btab.data(), btab.size());
+        if (table_path) put(o_slots, masks.data(), masks.size() * 4);
+        if (has_ar) put(o_pd, pd.data(), pd.size() * 4);
+        put(o_ent, ent.data(), ent.size() * 4);
+        put(o_ctab, ctab.data(), ctab.size() * 4);
+        if (hipMemcpy(d, img.data(), o_assign, hipMemcpyHostToDevice) != hipSuccess ||
+            (has_table && hipMemcpy(b + o_assign, p->assign, (size_t)A * ndev, hipMemcpyHostToDevice) != hipSuccess)) {
+            status = POSEIDON_E_DEVICE;
+            break;
+        }
+        kp.ctab = (const uint32_t *)(b + o_ctab);
         kp.cost = (const uint64_t *)(b + o_cost);
         kp.pm = (const uint32_t *)(b + o_pm);
         kp.cap = (const uint32_t *)(b + o_cap);
@@ -691,9 +717,9 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
         const size_t lds = ((cost.size() * 8 + pm.size() * 4 + (size_t)T * 4 + pd.size() * 4) + 15) & ~(size_t)15;
         const size_t elds = kp.ent_lds;
         if (lds > 64 * 1024 || elds > 64 * 1024) { status = POSEIDON_E_RANGE; break; }
-        int occ = 0;
+        int occ = 0, full = 0;
         hipDeviceProp_t prop;
-        if (pk::eval_occupancy(kp, ilv ? lds : elds, &occ) != hipSuccess ||
+        if (pk::eval_occupancy(kp, ilv ? lds : elds, &occ, &full) != hipSuccess ||
             hipGetDeviceProperties(&prop, hip_device) != hipSuccess) {
             status = POSEIDON_E_DEVICE;
             break;
@@ -709,6 +735,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
             break;
         }
         ctx->grid_max = (uint32_t)std::max(1, occ) * (uint32_t)std::max(1, prop.multiProcessorCount);
+        ctx->full_grid = (uint32_t)std::max(1, full) * (uint32_t)std::max(1, prop.multiProcessorCount);
         // (at most grid_max: the survivor segments are sized for that many blocks)
         ctx->filter_grid = std::min(ctx->grid_max,
                                     (uint32_t)std::max(1, focc) * (uint32_t)std::max(1, prop.multiProcessorCount));
@@ -801,71 +828,9 @@ int read_best(poseidon_ctx *ctx, hipStream_t st, unsigned long long word_index, 
 // are processed in chunks of this size.
 constexpr uint64_t kChunk = 1ull << 26;
 
-// Workspace for chunks of up to `n` candidates: the cut codes [words][cap],
-// the early-stop survivor indices [cap] and per-block survivor counts
-// [grid_max] (cap = n plus one decode batch per block of slack, so the
-// per-block survivor segments fit) and, with a cascade, two straggler
-// queues of qcap entries of queue_entry_words uint32
-// (qcap = n plus one block of slack per segment) and the per-block queue
-// counts [levels][grid_max].  Grown on demand; the old buffer is released
-// only after the stream has drained.
-uint64_t queue_cap(const poseidon_ctx *ctx, uint64_t n) { return n + (uint64_t)ctx->grid_max * 256; }
-
-// DP state words per queue entry: S registers for 1F1B, 2S for Eager 1F1B,
-// the live registers at a period boundary for Interleaved 1F1B
-uint64_t queue_state_words(const poseidon_ctx *ctx) {
-    if (ctx->base.sched == POSEIDON_SCHEDULE_INTERLEAVED_1F1B)
-        return (uint64_t)pk::ilv_state_words(ctx->S, ctx->base.ndev);
-    return ctx->base.sched ? 2ull * ctx->S : ctx->S;
-}
-
-// Words of one queue entry: candidate index, cut codes, the assignment
-// index (room for it whenever the problem has more than one assignment;
-// used by calls with a list of assignment indices) and the DP state.
-uint64_t queue_entry_words(const poseidon_ctx *ctx) {
-    return 1 + (uint64_t)pk::code_words((int)ctx->S) + (ctx->A > 1 ? 1 : 0) + queue_state_words(ctx);
-}
-
-int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
-    if (ctx->ws_cap >= n) return POSEIDON_OK;
-    if (ctx->ws) {
-        if (hipStreamSynchronize(st) != hipSuccess) return POSEIDON_E_DEVICE;
-        (void)hipFree(ctx->ws);
-        ctx->ws = nullptr;
-        ctx->ws_cap = 0;
-    }
-    // (a multiple of 4 words: the range-mode decode stores four code words at once)
-    const uint64_t cap = (std::max<uint64_t>(n, 1024) + (uint64_t)ctx->grid_max * pk::kDecodeIlp * 256 + 3) & ~3ull;
-    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
-    // cut codes, the early stop's survivor and first-stage lists and their counts
-    uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * ctx->grid_max;
-    if (ctx->base.nlevels)
-        elems += 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) +
-                 (uint64_t)pk::kMaxLevels * ctx->grid_max;
-    // the kernels address the code words, each list and each queue with
-    // 32-bit word offsets (n is at most kChunk, so this always holds)
-    if ((words + pk::kAListWords) * cap >= (1ull << 32) || queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32))
-        return POSEIDON_E_RANGE;
-    void *q = nullptr;
-    if (hipMalloc(&q, elems * 4) != hipSuccess) {
-        (void)hipGetLastError();
-        return POSEIDON_E_NOMEM;
-    }
-    ctx->ws = q;
-    ctx->ws_cap = cap;
-    return POSEIDON_OK;
-}
-
-// After a failed launch: re-arm the reduction words and queue counters.
-int rearm(poseidon_ctx *ctx, hipStream_t st) {
-    (void)pk::launch_fill(ctx->state + W_ACC, 1, ~0ull, st);
-    (void)pk::launch_fill(ctx->state + W_DONE, 1, 0ull, st);
-    return POSEIDON_E_DEVICE;
-}
-
-// Grid of the evaluation kernels for a chunk of n candidates, and the queue
-// slots its blocks own: block b of every level holds seg_cap entries, so a
-// chunk's queues need grid * seg_cap slots (non-decreasing in n).
+// Grid of the evaluation kernels for a chunk of n candidates, and the list
+// (Interleaved 1F1B: queue) slots its blocks own: seg_cap entries each, so a
+// chunk's lists need grid * seg_cap slots (non-decreasing in n).
 struct ChunkGrid {
     uint32_t grid;
     uint64_t seg_cap;
@@ -878,27 +843,148 @@ ChunkGrid chunk_grid(const poseidon_ctx *ctx, uint64_t n) {
     return g;
 }
 
-// Largest power-of-two chunk (at least one wave) whose cut codes, straggler
-// queues and queue counts fit the allocation-free scratch; 0 if none does.
-uint64_t noalloc_chunk_for(const poseidon_ctx *ctx) {
-    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S), ent = queue_entry_words(ctx);
-    const uint64_t cap_words = pk::noalloc_scratch_bytes() / 4;
-    for (uint64_t n = kChunk; n >= 64; n >>= 1) {
-        const ChunkGrid g = chunk_grid(ctx, n);
-        uint64_t need = words * n;
-        if (ctx->base.nlevels) need += 2 * ent * g.grid * g.seg_cap + (uint64_t)pk::kMaxLevels * g.grid;
-        if (need <= cap_words) return n;
+// Interleaved 1F1B: slots of a straggler queue for chunks of n candidates
+// (one block of slack per segment) and the words of an entry: candidate
+// index, cut codes, the assignment index (room for it whenever the problem
+// has more than one assignment; used by calls with a list of assignment
+// indices) and the live registers at a period boundary.
+uint64_t queue_cap(const poseidon_ctx *ctx, uint64_t n) { return n + (uint64_t)ctx->grid_max * 256; }
+uint64_t queue_entry_words(const poseidon_ctx *ctx) {
+    return 1 + (uint64_t)pk::code_words((int)ctx->S) + (ctx->A > 1 ? 1 : 0) +
+           (uint64_t)pk::ilv_state_words(ctx->S, ctx->base.ndev);
+}
+
+// Closed form: words per entry of the list of candidates without a proof
+// (position, cut codes, assignment), and of the recurrence pass's two queues
+// per block for tiles of `tile` entries (the same and the DP state: S
+// registers for 1F1B, 2S for Eager 1F1B).
+uint64_t full_list_words(const poseidon_ctx *ctx) { return 2 + (uint64_t)pk::code_words((int)ctx->S); }
+uint64_t tile_queue_words(const poseidon_ctx *ctx, uint64_t tile) {
+    return 2 * tile * (full_list_words(ctx) + (ctx->base.sched ? 2ull : 1ull) * ctx->S);
+}
+// tile of the recurrence pass: enough entries that the few lanes left at its
+// last checkpoints still fill waves
+constexpr uint32_t kTile = 1024;
+// its blocks for chunks of n candidates (a block takes at least one wave of
+// them), and the tile, no longer than a block's share of them
+uint32_t full_grid_for(const poseidon_ctx *ctx, uint64_t n) {
+    return (uint32_t)std::min<uint64_t>((n + 63) / 64, ctx->full_grid);
+}
+uint32_t tile_for(const poseidon_ctx *ctx, uint64_t n) {
+    const uint64_t grid = full_grid_for(ctx, n), waves = (n + 63) / 64;
+    return (uint32_t)std::min<uint64_t>(kTile, (waves + grid - 1) / grid * 64);
+}
+
+// Workspace for chunks of up to `n` candidates (cap = n and one decode batch
+// per block of slack, so that per-block segments fit): the cut codes
+// [words][cap], the early-stop survivor indices [cap] and the first-stage
+// list [kAListWords][cap] (the closed form's list of candidates without a
+// proof takes the same words) with their per-block counts [grid_max] each;
+// then the recurrence pass's queues (closed form), or two straggler queues
+// and their counts [levels][grid_max] (Interleaved 1F1B).  Grown on demand;
+// the old buffer is released only after the stream has drained.
+int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
+    if (ctx->ws_n >= n) return POSEIDON_OK;
+    if (ctx->ws) {
+        if (hipStreamSynchronize(st) != hipSuccess) return POSEIDON_E_DEVICE;
+        (void)hipFree(ctx->ws);
+        ctx->ws = nullptr;
+        ctx->ws_cap = 0;
+        ctx->ws_n = 0;
     }
+    // a power of two up to 2^20, then a multiple of it, so that calls of
+    // slowly growing size do not reallocate each time
+    uint64_t r = 1024;
+    while (r < n && r < (1ull << 20)) r *= 2;
+    n = (n + r - 1) / r * r;
+    // (a multiple of 4 words: the range-mode decode stores four code words at once)
+    const uint64_t cap = (n + (uint64_t)chunk_grid(ctx, n).grid * pk::kDecodeIlp * 256 + 3) & ~3ull;
+    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
+    // cut codes, the early stop's survivor and first-stage lists and their counts
+    uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * ctx->grid_max;
+    if (ctx->base.closed) elems += tile_queue_words(ctx, tile_for(ctx, n)) * full_grid_for(ctx, n);
+    else if (ctx->base.nlevels)
+        elems += 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) + (uint64_t)pk::kMaxLevels * ctx->grid_max;
+    // the kernels address the code words, each list and each queue with
+    // 32-bit word offsets (n is at most kChunk, so this always holds)
+    if ((words + pk::kAListWords) * cap >= (1ull << 32) ||
+        (!ctx->base.closed && ctx->base.nlevels && queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32)))
+        return POSEIDON_E_RANGE;
+    void *q = nullptr;
+    if (hipMalloc(&q, elems * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        return POSEIDON_E_NOMEM;
+    }
+    ctx->ws = q;
+    ctx->ws_cap = cap;
+    ctx->ws_n = n;
+    return POSEIDON_OK;
+}
+
+// After a failed launch: re-arm the reduction words and queue counters.
+int rearm(poseidon_ctx *ctx, hipStream_t st) {
+    (void)pk::launch_fill(ctx->state + W_ACC, 1, ~0ull, st);
+    (void)pk::launch_fill(ctx->state + W_DONE, 1, 0ull, st);
+    return POSEIDON_E_DEVICE;
+}
+
+// Memory of one evaluation call: cut codes [words][cap] at `codes`; closed
+// form: the list of candidates without a proof [full_list_words][cap] at
+// `list` with counts [grid] at `counts`, and the recurrence pass's queues
+// for `tile` entries on `full_grid` blocks at `queues`; Interleaved 1F1B:
+// two straggler queues of qcap entries at `queues`, then their counts
+// [levels][grid].
+struct EvalMem {
+    uint64_t cap, qcap;
+    uint32_t *codes, *list, *queues;
+    unsigned int *counts;
+    uint32_t tile, full_grid;
+};
+
+// The allocation-free scratch cut for chunks of n candidates: the layout
+// (from address `base`, which may be null to size it) and the words it takes.
+// The recurrence pass gets one block per CU's worth of small queues there,
+// which leaves the most room for the chunk.
+constexpr uint32_t kNoallocTile = 256, kNoallocFullGrid = 256;
+uint64_t noalloc_layout(const poseidon_ctx *ctx, uint64_t n, uint32_t *base, EvalMem *m) {
+    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
+    const ChunkGrid g = chunk_grid(ctx, n);
+    memset(m, 0, sizeof(*m));
+    uint64_t o = 0;
+    const uint64_t cap = std::max<uint64_t>(n, (uint64_t)g.grid * g.seg_cap);
+    m->codes = base;
+    o += words * cap;
+    if (ctx->base.closed) {
+        m->tile = kNoallocTile;
+        m->full_grid = std::min(ctx->full_grid, kNoallocFullGrid);
+        m->list = base + o;
+        o += full_list_words(ctx) * cap;
+        m->counts = base + o;
+        o += g.grid;
+        m->queues = base + o;
+        o += tile_queue_words(ctx, m->tile) * m->full_grid;
+    } else if (ctx->base.nlevels) {
+        m->queues = base + o;
+        m->qcap = (uint64_t)g.grid * g.seg_cap;
+        o += 2 * queue_entry_words(ctx) * m->qcap + (uint64_t)pk::kMaxLevels * g.grid;
+    }
+    m->cap = cap;
+    return o;
+}
+
+// Largest power-of-two chunk (at least one wave) whose memory fits the
+// allocation-free scratch; 0 if none does.
+uint64_t noalloc_chunk_for(const poseidon_ctx *ctx) {
+    EvalMem m;
+    for (uint64_t n = kChunk; n >= 64; n >>= 1)
+        if (noalloc_layout(ctx, n, nullptr, &m) <= pk::noalloc_scratch_bytes() / 4) return n;
     return 0;
 }
 
-// One evaluation call in chunks of at most `chunk` candidates on a
-// workspace: cut codes [words][ccap] at `codes`; with a cascade, two
-// straggler queues of qcap entries of queue_entry_words at `queues`,
-// followed by the per-block queue counts [levels][grid].
+// One evaluation call in chunks of at most `chunk` candidates.
 int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makespan_out,
                 uint32_t *feasible_bits_out, poseidon_best *best_out, hipStream_t st, uint64_t chunk,
-                uint32_t *codes, uint64_t ccap, uint32_t *queues, uint64_t qcap) {
+                const EvalMem &m) {
     pk::KParams kp = ctx->base;
     kp.first = cands->first;
     kp.count = cands->count;
@@ -909,11 +995,16 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
     kp.makespan_out = makespan_out;
     kp.feas_bits_out = feasible_bits_out;
     kp.nwords = (cands->count + 31) / 32;
-    kp.codes = codes;
-    kp.ccap = ccap;
-    if (kp.nlevels) {
-        kp.qcap = qcap;
-        kp.queue[0] = queues;
+    kp.codes = m.codes;
+    kp.ccap = m.cap;
+    if (kp.closed) {
+        kp.flist = m.list;
+        kp.fcount = m.counts;
+        kp.tile = m.tile;
+        kp.tileq = m.queues;
+    } else if (kp.nlevels) {
+        kp.qcap = m.qcap;
+        kp.queue[0] = m.queues;
         kp.queue[1] = kp.queue[0] + queue_entry_words(ctx) * kp.qcap;
         kp.qcount = kp.queue[1] + queue_entry_words(ctx) * kp.qcap;
     }
@@ -925,15 +1016,21 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         pk::LaunchCfg lc;
         lc.lds_bytes = ctx->base.sched == POSEIDON_SCHEDULE_INTERLEAVED_1F1B ? ctx->lds_bytes : ctx->ent_lds_bytes;
         lc.grid = g.grid;
-        // queue segments: block b of every level owns seg_cap slots
+        lc.grid2 = m.full_grid;
+        // segments of the lists: block b owns seg_cap slots
         kp.nseg = lc.grid;
         kp.seg_cap = g.seg_cap;
         pk::LaunchCfg ld = lc;
         ld.grid = (uint32_t)std::min<uint64_t>((kp.n_i + 4 * 256 - 1) / (4 * 256), ctx->grid_max);
         if (pk::launch_decode(kp, ld, st) != hipSuccess) return rearm(ctx, st);
+        if (kp.closed) {
+            if (pk::launch_closed(kp, lc, st) != hipSuccess || pk::launch_full(kp, lc, st) != hipSuccess)
+                return rearm(ctx, st);
+            continue;
+        }
         if (pk::launch_eval(kp, lc, st) != hipSuccess) return rearm(ctx, st);
         for (uint32_t l = 1; l <= kp.nlevels; ++l)
-            if (pk::launch_resume(kp, lc, st, l) != hipSuccess) return rearm(ctx, st);
+            if (pk::launch_ilv_resume(kp, lc, st, l) != hipSuccess) return rearm(ctx, st);
     }
     if (best_out) return read_best(ctx, st, W_RESULT, ctx->result_base, best_out);
     return POSEIDON_OK;
@@ -960,14 +1057,18 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands, uin
     const uint64_t chunk = std::min<uint64_t>(cands->count, kChunk);
     rc = ensure_workspace(ctx, chunk, st);
     if (rc != POSEIDON_OK) return rc;
-    // workspace: cut codes [words][cap]; the early stop's survivor indices
-    // [cap], their counts [grid_max], its first-stage list [kAListWords][cap]
-    // and counts [grid_max]; then the straggler queues
-    uint32_t *ws = (uint32_t *)ctx->ws;
-    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
-    return eval_chunks(ctx, cands, makespan_out, feasible_bits_out, best_out, st, chunk, ws, ctx->ws_cap,
-                       ws + (words + 1 + pk::kAListWords) * ctx->ws_cap + 2ull * ctx->grid_max,
-                       queue_cap(ctx, ctx->ws_cap));
+    EvalMem m;
+    m.cap = ctx->ws_cap;
+    m.codes = (uint32_t *)ctx->ws;
+    // (laid out as ensure_workspace describes it)
+    uint32_t *o = m.codes + ((uint64_t)pk::code_words((int)ctx->S) + 1) * m.cap;
+    m.counts = o;
+    m.list = o + ctx->grid_max;
+    m.queues = m.list + pk::kAListWords * m.cap + ctx->grid_max;
+    m.qcap = queue_cap(ctx, m.cap);
+    m.tile = tile_for(ctx, ctx->ws_n);
+    m.full_grid = full_grid_for(ctx, ctx->ws_n);
+    return eval_chunks(ctx, cands, makespan_out, feasible_bits_out, best_out, st, chunk, m);
 }
 
 int poseidon_eval_candidates_noalloc(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makespan_out,
@@ -985,13 +1086,9 @@ int poseidon_eval_candidates_noalloc(poseidon_ctx *ctx, const poseidon_cands *ca
         if (best_out) return read_best(ctx, st, W_RESULT, ctx->result_base, best_out);
         return POSEIDON_OK;
     }
-    // scratch: cut codes [words][chunk], then the straggler queues
-    const uint64_t chunk = ctx->noalloc_chunk;
-    const ChunkGrid cg = chunk_grid(ctx, chunk);
-    uint32_t *scr = (uint32_t *)ctx->scratch;
-    const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
-    return eval_chunks(ctx, cands, makespan_out, feasible_bits_out, best_out, st, chunk, scr, chunk,
-                       scr + words * chunk, (uint64_t)cg.grid * cg.seg_cap);
+    EvalMem m;
+    noalloc_layout(ctx, ctx->noalloc_chunk, (uint32_t *)ctx->scratch, &m);
+    return eval_chunks(ctx, cands, makespan_out, feasible_bits_out, best_out, st, ctx->noalloc_chunk, m);
 }
 
 int poseidon_last_best(poseidon_ctx *ctx, poseidon_best *best_out, void *hip_stream) {
@@ -1043,7 +1140,7 @@ int poseidon_eval_candidates_bounded(poseidon_ctx *ctx, const poseidon_cands *ca
     lc.lds_bytes = ctx->ent_lds_bytes;
     // survivor kernel: as many blocks as the evaluation kernel keeps resident
     // (those the survivors need run, the others leave at once)
-    lc.grid2 = ctx->grid_max;
+    lc.grid2 = ctx->base.closed ? ctx->full_grid : ctx->grid_max;
     uint64_t size = chunk;
     for (uint64_t lo = 0, hi; lo < n; lo = hi) {
         hi = n - lo > size ? lo + size : n;

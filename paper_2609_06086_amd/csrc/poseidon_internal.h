@@ -36,6 +36,11 @@ constexpr uint32_t kSearchScanMax = 16384;   // blocks of one search level piece
 
 enum AssignMode : uint32_t { kAssignFixed = 0, kAssignTable = 1, kAssignDigits = 2 };
 
+// Rows of the closed form's constant table, per 0-based stage x with
+// e_x = cf_x + cb_x: e_x; e_0 + .. + e_{x-1}; g_x = e_{x-1} + e_x;
+// (n_x - 1) g_x with n_x the stage's pairs (1F1B); cb_x; cb_0 + .. + cb_{x-1}.
+enum ClosedRow : int { kCE = 0, kCSum = 1, kCE2 = 2, kCE2n = 3, kCCb = 4, kCPsi = 5, kCRows = 6 };
+
 // Kernel arguments, passed by value (uniform values land in SGPRs).
 struct KParams {
     // device tables owned by the context
@@ -74,6 +79,9 @@ struct KParams {
                                   // that on u (the search's last-stage Eq. 2 then falls with the cut)
     uint32_t ilv_compiled, ilv_trips; // Interleaved 1F1B: the schedule runs as compiled code with
                                       // this many steady periods
+    uint32_t closed;              // 1F1B / Eager 1F1B with M large enough for the closed form
+    uint32_t edge_max;            // largest cf_s + cb_s
+    const uint32_t *ctab;         // [kCRows][kSMax] constants of the closed form (ClosedRow)
     uint32_t psi[kSMax];          // cf_0 + ... + cf_{s-1}: undoes the per-stage shift at the end
     uint8_t fixed_types[kSMax];
     // candidates of the call
@@ -103,16 +111,23 @@ struct KParams {
     unsigned int *scount;
     uint32_t *alist;
     unsigned int *acount;
+    // closed form: the candidates of a chunk without a proof, in per-block
+    // segments of seg_cap entries (position, cut codes, assignment: arrays
+    // of ccap words), their counts in fcount; full_kernel's tiles and the
+    // blocks' queues (two of `tile` entries each)
+    uint32_t *flist;
+    unsigned int *fcount;
+    uint32_t tile;
+    uint32_t *tileq;
     // steady-state cascade: lanes not settled at iteration (Interleaved
-    // 1F1B: period) lvl_k[l-1] are
-    // queued (candidate index + registers) and resumed by level l
+    // 1F1B: period) lvl_k[l-1] are queued and resumed by level l
     uint32_t nlevels;                 // 0 = no cascade
     uint32_t lvl_k[kMaxLevels];
+    // Interleaved 1F1B: the queues between its levels
     unsigned int *qcount;             // [level][nseg]: entries block b queued for level + 1
     uint32_t *queue[2];               // ping-pong queues: level l reads queue (l-1) & 1;
                                       // each idx[qcap] | codes[words][qcap] | asg[qcap] (if qasg)
-                                      // | Y[NX][qcap] (NX = S for 1F1B, 2S for Eager 1F1B, the
-                                      // live registers under Interleaved 1F1B),
+                                      // | Y[NX][qcap] (the live registers),
                                       // block b owning slots [b * seg_cap, (b+1) * seg_cap)
     uint32_t qasg;                    // queue entries carry the assignment index (calls with a
                                       // list of assignment indices)
@@ -171,18 +186,21 @@ __host__ __device__ constexpr size_t entry_bytes(uint32_t T, bool ar) {
 
 struct LaunchCfg {
     uint32_t grid = 0;
-    uint32_t grid2 = 0;   // early stop: blocks of the survivor kernel
+    uint32_t grid2 = 0;   // blocks of the survivor kernel (early stop) or of full_kernel
     size_t lds_bytes = 0;     // stage tables: the entries (evaluation, early-stop kernels) or cost, pm,
                           // cap (search and Interleaved 1F1B kernels)
 };
 
 hipError_t launch_eval(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st);
-hipError_t launch_resume(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t lvl);
+// Problems with a closed form (KParams::closed): the closed-form pass over a
+// chunk, then the recurrence for the candidates it could not prove.
+hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st);
+hipError_t launch_full(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 hipError_t launch_bounded(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t publish);
 constexpr int kAListWords = 6;  // words per entry of the early stop's first-stage list
 constexpr int kDecodeIlp = 4;   // candidates per lane of the decode and early-stop filter kernels
-hipError_t eval_occupancy(const KParams &p, size_t lds, int *blocks);
+hipError_t eval_occupancy(const KParams &p, size_t lds, int *blocks, int *full);
 hipError_t filter_occupancy(const KParams &p, size_t ent_lds, int *blocks);
 hipError_t launch_ilv(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 hipError_t ilv_occupancy(const KParams &p, size_t lds, int *blocks);

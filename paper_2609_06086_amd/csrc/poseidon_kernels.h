@@ -18,6 +18,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "poseidon_closed.h"
 #include "poseidon_internal.h"
 
 namespace pk {
@@ -135,12 +136,7 @@ __device__ __forceinline__ bool unpack_cuts(const uint32_t (&w)[Codes<S>::kWords
     cut[S] = L;
 #pragma unroll
     for (int j = 1; j <= S - 1; ++j) cut[j] = (w[(j - 1) / 4] >> (8 * ((j - 1) % 4))) & 0xFFu;
-    const bool ok = (w[0] & 0xFFu) != 0u;
-    if (!ok) {
-#pragma unroll
-        for (int j = 1; j <= S - 1; ++j) cut[j] = 0;
-    }
-    return ok;
+    return (w[0] & 0xFFu) != 0u;   // (an invalid candidate's words are all zero)
 }
 
 template <int S>
@@ -359,15 +355,6 @@ __device__ __forceinline__ void steady_slot(int parity, uint32_t (&Y)[S], const 
     }
 #pragma unroll
     for (int s = 0; s < S; ++s) Y[s] = N[s];
-}
-
-// k * x for a small k; U24: the full-rate 24-bit multiply (the problem's
-// stage weights fit 24 bits).  The callers take U24 as a template argument
-// and branch once on it, so that no select merges the two products into one
-// slow 32-bit multiply.
-template <bool U24>
-__device__ __forceinline__ uint32_t mul_small(uint32_t x, uint32_t k) {
-    return U24 ? __umul24(x, k) : x * k;
 }
 
 // Prologue (slots 0 .. 2S-2) with its warm-up forwards in closed form.
@@ -767,14 +754,6 @@ __device__ __forceinline__ void eager_unpack(const uint32_t (&X)[2 * S], uint32_
     }
 }
 
-// schedules other than 1F1B: the slot table (TAB) or the closed form
-template <int S, bool TAB>
-__device__ __forceinline__ void dp_other(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
-                                         const Comm<S> &c, uint32_t (&Y)[S]) {
-    if (TAB) dp_sched<S>(p, F, B, c, Y);
-    else dp_eager<S>(p.M, F, B, c, Y);
-}
-
 // registers after the whole DP (any M); SCH = the problem is not 1F1B
 template <int S, bool SCH>
 __device__ __forceinline__ void dp_full(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
@@ -1029,6 +1008,22 @@ __device__ __forceinline__ unsigned long long block_exclusive_scan_u64(unsigned 
     __syncthreads();
     total = all;
     return before + inc - v;
+}
+
+// Exclusive scan of n per-block counts into LDS (pre[0 .. n-1]) with their
+// total; the caller's next barrier publishes pre.
+__device__ __forceinline__ void scan_counts(const unsigned int *counts, uint32_t n, uint32_t *pre, uint32_t &total) {
+    const uint32_t per = (n + kBlock - 1) / kBlock, j0 = threadIdx.x * per;
+    uint32_t mine = 0;
+    for (uint32_t j = j0; j < j0 + per && j < n; ++j)
+        mine += __hip_atomic_load(&counts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long all;
+    uint32_t run = (uint32_t)block_exclusive_scan_u64(mine, all);
+    for (uint32_t j = j0; j < j0 + per && j < n; ++j) {
+        pre[j] = run;
+        run += __hip_atomic_load(&counts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    total = (uint32_t)all;
 }
 
 __device__ __forceinline__ unsigned long long make_key(bool feasible, uint32_t T, uint32_t i) {
@@ -1484,11 +1479,25 @@ __global__ __launch_bounds__(kBlock) void decode_kernel(KParams p) {
     if (bad) atomicOr(p.err, 1u);
 }
 
-// (a2)-(a4), (a6) for the chunk: stage weights from the cut codes, memory
-// check, the DP and the reduction.  With a cascade (p.nlevels > 0) a lane
-// whose steady state has not settled by iteration p.lvl_k[0] is queued for
-// resume_kernel instead of finishing here.
-template <int S, bool AR>
+// Outputs of a wave's candidates gi (one per lane, 64 aligned consecutive
+// positions: chunks start at multiples of 64): makespans of the lanes with
+// `write` set and the packed feasibility bits.  They are read back only by
+// the host or the argmin pass: stream them past the caches.
+__device__ __forceinline__ void write_outputs(const KParams &p, uint32_t gi, bool write, uint32_t T, bool feas) {
+    if (write && p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + gi);
+    if (p.feas_bits_out) {
+        const unsigned long long bits = __ballot(feas);
+        const uint32_t w0 = (gi - (threadIdx.x & 63)) >> 5, nwords = (uint32_t)p.nwords;
+        if ((threadIdx.x & 63) == 0 && w0 < nwords) __builtin_nontemporal_store((uint32_t)bits, p.feas_bits_out + w0);
+        if ((threadIdx.x & 63) == 32 && w0 + 1 < nwords) __builtin_nontemporal_store((uint32_t)(bits >> 32), p.feas_bits_out + w0 + 1);
+    }
+}
+
+// (a2)-(a4), (a6) for the chunk by the recurrence alone (problems with too
+// few micro-batches for the closed form, and the slot tables): stage weights
+// from the cut codes, memory check, the DP and the reduction.  SCH: Eager
+// 1F1B; TAB: the slot table instead of the compiled schedule.
+template <int S, bool AR, bool SCH, bool TAB>
 __global__ __launch_bounds__(kBlock) void eval_kernel(KParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Ent tab = entry_tables(p, smem);
@@ -1502,10 +1511,6 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(KParams p) {
     const uint32_t first_i = (uint32_t)p.first_i;
     // every wave runs the same trip count so that ballots see whole waves
     const uint32_t span = (n_i + stride - 1) / stride;
-    const uint32_t nit = p.M >= (uint32_t)S ? p.M - S : 0u;
-    __shared__ unsigned int nq;
-    if (threadIdx.x == 0) nq = 0;
-    __syncthreads();
     uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     for (uint32_t it = 0; it < span; ++it, i += stride) {
         const bool active = i < n_i;
@@ -1518,61 +1523,57 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(KParams p) {
         const uint32_t a = ok ? assign_of(p, gi) : 0u;
         decode_toff<S>(p, tab, a, to);
         const bool feas = stage_weights<S>(p, tab, cut, to, F, B) && ok && active;
-        bool done_here = true;
         uint32_t T;
-        if (p.M < (uint32_t)S) {
-            dp_table<S>(p, F, B, comm, Y);
+        if constexpr (TAB) {
+            if constexpr (SCH) dp_sched<S>(p, F, B, comm, Y);
+            else dp_table<S>(p, F, B, comm, Y);
+            T = end_time<S, AR>(p, tab, Y, comm, w, a);
+        } else if constexpr (SCH) {
+            dp_eager<S>(p.M, F, B, comm, Y);
             T = end_time<S, AR>(p, tab, Y, comm, w, a);
         } else {
             dp_prologue<S>(Y, F, B, comm, p.g24 != 0);
-            const uint32_t k1 = p.nlevels ? p.lvl_k[0] : nit;
-            done_here = dp_advance<S>(Y, F, B, comm, 0, k1, nit);
-            if (p.nlevels) enqueue<S, S>(p, 0, &nq, !done_here && active && ok, gi, w, -1, Y);
+            for (uint32_t k = S; k < p.M; ++k) dp_iter<S>(Y, F, B, comm);
             T = dp_end<S, AR>(p, tab, Y, F, B, comm, w, a);
         }
         if (!ok) T = 0xFFFFFFFFu;
-        const bool write = active && (done_here || !ok);
-        // outputs are read back only by the host or the argmin pass: stream them past the caches
-        if (write && p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + gi);
-        if (p.feas_bits_out) {
-            // chunks start at multiples of 64, so a wave covers 64 aligned candidates
-            const unsigned long long bits = __ballot(feas);
-            const uint32_t w0 = (gi - (threadIdx.x & 63)) >> 5, nwords = (uint32_t)p.nwords;
-            if ((threadIdx.x & 63) == 0 && w0 < nwords) __builtin_nontemporal_store((uint32_t)bits, p.feas_bits_out + w0);
-            if ((threadIdx.x & 63) == 32 && w0 + 1 < nwords) __builtin_nontemporal_store((uint32_t)(bits >> 32), p.feas_bits_out + w0 + 1);
-        }
-        if (write) {
+        write_outputs(p, gi, active, T, feas);
+        if (active) {
             const unsigned long long key = make_key(feas, T, gi);
             best = key < best ? key : best;
         }
     }
-    if (p.nlevels) {
-        __syncthreads();
-        if (threadIdx.x == 0) p.qcount[blockIdx.x] = nq;   // entries for level 1
-    }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, p.nlevels == 0, p.accumulate);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate);
 }
 
-// Schedules other than 1F1B: the same pass as eval_kernel with the
-// schedule-table DP (TAB) or the Eager 1F1B closed form, whose steady part
-// takes the same cascade (queue entries carry 2S state words).  Held to 128
-// VGPRs (4 waves per SIMD instead of 3 at S = 16, with a few words spilled
-// to scratch outside the steady loop): 2 % faster on the 16-stage workload.
-template <int S, bool AR, bool TAB>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void sched_kernel(KParams p) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Ent tab = entry_tables(p, smem);
-    const Comm<S> comm = load_comm<S>(p);
+// The list of candidates without a closed-form proof, arrays of lcap
+// entries: call position, cut codes, assignment index.  Block b of
+// closed_kernel fills slots [b * seg_cap, (b + 1) * seg_cap) and writes its
+// count to fcount[b].
+template <int S>
+struct FullList {
+    uint32_t *pos, *w, *asg;
+    __device__ __forceinline__ explicit FullList(const KParams &p)
+        : pos(p.flist), w(p.flist + p.ccap), asg(p.flist + (1 + Codes<S>::kWords) * p.ccap) {}
+};
+
+// (a2)-(a4), (a6) for the chunk: stage weights from the cut codes, memory
+// check, and the closed-form makespan (poseidon_closed.h).  Lanes whose value
+// is not proven go to the list that full_kernel evaluates by the recurrence.
+// VALU-bound: about 31 operations a stage, against 37 a stage for every one
+// of the recurrence's steady iterations (at least S of them before its first
+// settle check).  2^24 candidates of 16 stages: 0.35 ms (and 0.05 ms for the
+// list) against 1.09 ms and 0.51 ms for the recurrence and its later
+// checkpoints; Eager 1F1B 0.35 against 3.42 ms; 2^26 of 8 stages 0.76 ms
+// (0.07) against 1.42 ms (0.65).
+template <int S, bool AR, bool SCH, bool U24>
+__device__ __forceinline__ unsigned long long closed_all(const KParams &p, const Ent &tab, unsigned int &nq) {
     constexpr int NW = Codes<S>::kWords;
     unsigned long long best = ~0ull;
-    // 32-bit positions, as in eval_kernel
+    // 32-bit positions and word offsets, as in eval_kernel
     const uint32_t stride = gridDim.x * kBlock, n_i = (uint32_t)p.n_i, ccap = (uint32_t)p.ccap;
-    const uint32_t first_i = (uint32_t)p.first_i;
+    const uint32_t first_i = (uint32_t)p.first_i, seg = blockIdx.x * (uint32_t)p.seg_cap;
     const uint32_t span = (n_i + stride - 1) / stride;
-    const uint32_t npairs = TAB ? 0u : p.M - 2 * S + 1;
-    __shared__ unsigned int nq;
-    if (threadIdx.x == 0) nq = 0;
-    __syncthreads();
     uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     for (uint32_t it = 0; it < span; ++it, i += stride) {
         const bool active = i < n_i;
@@ -1580,117 +1581,171 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         uint32_t w[NW];
 #pragma unroll
         for (int k = 0; k < NW; ++k) w[k] = active ? p.codes[k * ccap + i] : 0u;
-        uint32_t cut[S + 1], to[S], F[S], B[S], Y[S];
+        uint32_t cut[S + 1], to[S], F[S], B[S], D[S], T;
         const bool ok = unpack_cuts<S>(w, p.L, cut);
         const uint32_t a = ok ? assign_of(p, gi) : 0u;
         decode_toff<S>(p, tab, a, to);
         const bool feas = stage_weights<S>(p, tab, cut, to, F, B) && ok && active;
-        bool done_here = true;
-        if (TAB) {
-            dp_sched<S>(p, F, B, comm, Y);
-        } else {
-            uint32_t Fn[S], Fp[S];
-            eager_prologue<S>(Y, Fn, Fp, F, B, comm);
-            const uint32_t k1 = p.nlevels ? p.lvl_k[0] : npairs;
-            done_here = eager_advance<S>(Y, Fn, Fp, F, B, comm, 0, k1, npairs);
-            if (p.nlevels) {
-                uint32_t X[2 * S];
-                eager_pack<S>(Y, Fn, Fp, X);
-                enqueue<S, 2 * S>(p, 0, &nq, !done_here && active && ok, gi, w, -1, X);
-            }
-            eager_epilogue<S>(Y, Fn, Fp, F, B, comm);
-        }
-        uint32_t T = end_time<S, AR>(p, tab, Y, comm, w, a);
+        if (AR) stage_allreduce<S>(p, tab, cut, to, D);
+        const bool proven = closed_form<S, SCH, AR, U24>(p, F, B, D, T) || !ok;
         if (!ok) T = 0xFFFFFFFFu;
-        const bool write = active && (done_here || !ok);
-        // outputs are read back only by the host or the argmin pass: stream them past the caches
-        if (write && p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + gi);
-        if (p.feas_bits_out) {
-            const unsigned long long bits = __ballot(feas);
-            const uint32_t w0 = (gi - (threadIdx.x & 63)) >> 5, nwords = (uint32_t)p.nwords;
-            if ((threadIdx.x & 63) == 0 && w0 < nwords) __builtin_nontemporal_store((uint32_t)bits, p.feas_bits_out + w0);
-            if ((threadIdx.x & 63) == 32 && w0 + 1 < nwords) __builtin_nontemporal_store((uint32_t)(bits >> 32), p.feas_bits_out + w0 + 1);
+        const bool write = active && proven;
+        const unsigned long long m = __ballot(active && !proven);
+        if (m) {
+            const unsigned int lane = threadIdx.x & 63;
+            unsigned int base = 0;
+            if (lane == 0) base = atomicAdd(&nq, (unsigned int)__popcll(m));
+            base = __shfl(base, 0, 64);
+            if (active && !proven) {
+                const uint32_t slot = seg + base + __popcll(lane ? (m & ((1ull << lane) - 1ull)) : 0ull);
+                const FullList<S> l(p);
+                l.pos[slot] = gi;
+#pragma unroll
+                for (int k = 0; k < NW; ++k) l.w[k * ccap + slot] = w[k];
+                l.asg[slot] = a;
+            }
         }
+        write_outputs(p, gi, write, T, feas);
         if (write) {
             const unsigned long long key = make_key(feas, T, gi);
             best = key < best ? key : best;
         }
     }
-    if (!TAB && p.nlevels) {
-        __syncthreads();
-        if (threadIdx.x == 0) p.qcount[blockIdx.x] = nq;
-    }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, TAB || p.nlevels == 0, p.accumulate);
+    return best;
 }
 
-// Level `lvl` of the cascade: resume the queued lanes from steady
-// iteration p.lvl_k[lvl-1] to p.lvl_k[lvl] (the end at the last level).
-// SCH: Eager 1F1B (2S state words per entry, steady pairs), else 1F1B.
 template <int S, bool AR, bool SCH>
-__global__ __launch_bounds__(kBlock) void resume_kernel(KParams p, uint32_t lvl) {
+__global__ __launch_bounds__(kBlock) void closed_kernel(KParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Ent tab = entry_tables(p, smem);
-    const Comm<S> comm = load_comm<S>(p);
-    constexpr int NW = Codes<S>::kWords;
-    constexpr int NX = SCH ? 2 * S : S;
-    const uint32_t nit = SCH ? p.M - 2 * S + 1 : p.M - S;
-    const uint32_t k0 = p.lvl_k[lvl - 1];
-    const uint32_t k1 = lvl < p.nlevels ? p.lvl_k[lvl] : nit;
-    // this block's segment of the queue written by level lvl - 1
-    const uint32_t n = __hip_atomic_load(&p.qcount[(uint64_t)(lvl - 1) * p.nseg + blockIdx.x], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-    const QueueView<S> qin(p, (lvl - 1) & 1);
     __shared__ unsigned int nq;
     if (threadIdx.x == 0) nq = 0;
     __syncthreads();
+    const unsigned long long best = p.g24 ? closed_all<S, AR, SCH, true>(p, tab, nq) : closed_all<S, AR, SCH, false>(p, tab, nq);
+    __syncthreads();
+    if (threadIdx.x == 0) p.fcount[blockIdx.x] = nq;
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, false);
+}
+
+// The candidates of the list by the recurrence.  Every block scans the
+// segment counts and takes an equal run of the list's entries (in segment
+// order, whole waves), in tiles of p.tile: a tile's lanes run to the first
+// checkpoint of the steady part, the ones that have not settled are packed
+// into the block's queue and run to the next, and so on, so that the few
+// long transients share waves.  Queue entries carry position, cut codes,
+// assignment and the DP state; blocks share nothing.
+template <int S, bool AR, bool SCH>
+__global__ __launch_bounds__(kBlock) void full_kernel(KParams p, uint32_t nseg) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint32_t *pre = reinterpret_cast<uint32_t *>(smem + p.ent_lds);   // nseg entries
+    uint32_t n;
+    scan_counts(p.fcount, nseg, pre, n);
+    const uint32_t waves = (n + 63) / 64;
+    const uint32_t share = (waves + gridDim.x - 1) / gridDim.x * 64;   // entries a block takes
+    const uint32_t need = n == 0 ? 1u : (n + share - 1) / share;       // blocks that have any
+    if (blockIdx.x >= need) return;   // (block-uniform)
+    const Ent tab = entry_tables(p, smem);   // (its barrier also publishes pre)
+    const Comm<S> comm = load_comm<S>(p);
+    constexpr int NW = Codes<S>::kWords;
+    constexpr int NX = SCH ? 2 * S : S;
+    constexpr uint32_t kEntry = 2 + NW + NX;
+    const uint32_t nit = SCH ? p.M - 2 * S + 1 : p.M - S, ccap = (uint32_t)p.ccap, tile = p.tile;
+    const FullList<S> list(p);
+    // the block's two queues: kEntry arrays of `tile` words each
+    uint32_t *const q0 = p.tileq + (uint64_t)blockIdx.x * 2 * kEntry * tile;
+    __shared__ unsigned int nq[2];
     unsigned long long best = ~0ull;
-    const uint32_t span = (n + kBlock - 1) / kBlock;
-    // 32-bit word offsets: a queue holds fewer than 2^32 words
-    const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap, qcap = (uint32_t)p.qcap;
-    for (uint32_t it = 0; it < span; ++it) {
-        const uint32_t q = seg + it * kBlock + threadIdx.x;
-        const bool active = it * kBlock + threadIdx.x < n;
-        const uint32_t i = active ? qin.idx[q] : 0u;
-        uint32_t w[NW], cut[S + 1], to[S], F[S], B[S], X[NX], Y[S];
+    const uint32_t e0 = blockIdx.x * share, e1 = min(n, e0 + share);
+    for (uint32_t t0 = e0; t0 < e1; t0 += tile) {
+        uint32_t cnt = min(tile, e1 - t0), k0 = 0;
+        for (uint32_t lvl = 0; cnt; ++lvl) {
+            const uint32_t k1 = lvl < p.nlevels ? p.lvl_k[lvl] : nit;
+            const uint32_t *qin = q0 + ((lvl + 1) & 1) * (uint64_t)kEntry * tile;
+            uint32_t *qout = q0 + (lvl & 1) * (uint64_t)kEntry * tile;
+            if (threadIdx.x == 0) nq[lvl & 1] = 0;
+            __syncthreads();
+            for (uint32_t j0 = (threadIdx.x >> 6) * 64; j0 < cnt; j0 += kBlock) {   // (wave-uniform)
+                const uint32_t j = j0 + (threadIdx.x & 63);
+                const bool active = j < cnt;
+                uint32_t i = 0, a = 0, w[NW], X[NX], cut[S + 1], to[S], F[S], B[S], Y[S];
+                if (lvl == 0) {
+                    // the last segment g with pre[g] <= entry holds it
+                    const uint32_t e = t0 + (active ? j : 0u);
+                    uint32_t lo = 0, hi = nseg;
+                    while (hi - lo > 1) {
+                        const uint32_t mid = (lo + hi) >> 1;
+                        if (pre[mid] <= e) lo = mid;
+                        else hi = mid;
+                    }
+                    const uint32_t at = lo * (uint32_t)p.seg_cap + (e - pre[lo]);
+                    i = list.pos[at];
+                    a = list.asg[at];
 #pragma unroll
-        for (int k = 0; k < NW; ++k) w[k] = active ? qin.codes[k * qcap + q] : 0u;
+                    for (int k = 0; k < NW; ++k) w[k] = list.w[k * ccap + at];
+                } else {
+                    const uint32_t at = active ? j : 0u;
+                    i = qin[at];
+                    a = qin[tile + at];
 #pragma unroll
-        for (int s = 0; s < NX; ++s) X[s] = active ? qin.Y[s * qcap + q] : 0u;
-        unpack_cuts<S>(w, p.L, cut);   // (a queued entry's codes were valid when it was queued)
-        const uint32_t a = !active ? 0u : p.qasg ? qin.asg[q] : assign_of(p, i);
-        decode_toff<S>(p, tab, a, to);
-        const bool feas = stage_weights<S>(p, tab, cut, to, F, B);
-        bool settled;
-        uint32_t T;
-        if constexpr (SCH) {
-            uint32_t Fn[S], Fp[S];
-            eager_unpack<S>(X, Y, Fn, Fp);
-            settled = eager_advance<S>(Y, Fn, Fp, F, B, comm, k0, k1, nit);
-            if (lvl < p.nlevels) {
-                eager_pack<S>(Y, Fn, Fp, X);
-                enqueue<S, NX>(p, lvl & 1, &nq, active && !settled, i, w, a, X);
+                    for (int k = 0; k < NW; ++k) w[k] = qin[(2 + k) * tile + at];
+#pragma unroll
+                    for (int s = 0; s < NX; ++s) X[s] = qin[(2 + NW + s) * tile + at];
+                }
+                unpack_cuts<S>(w, p.L, cut);
+                decode_toff<S>(p, tab, a, to);
+                const bool feas = stage_weights<S>(p, tab, cut, to, F, B);
+                bool settled;
+                uint32_t T = 0;
+                if constexpr (SCH) {
+                    uint32_t Fn[S], Fp[S];
+                    if (lvl == 0) eager_prologue<S>(Y, Fn, Fp, F, B, comm);
+                    else eager_unpack<S>(X, Y, Fn, Fp);
+                    settled = eager_advance<S>(Y, Fn, Fp, F, B, comm, k0, k1, nit);
+                    eager_pack<S>(Y, Fn, Fp, X);
+                    if (__ballot(active && settled)) {
+                        eager_epilogue<S>(Y, Fn, Fp, F, B, comm);
+                        T = end_time<S, AR>(p, tab, Y, comm, w, a);
+                    }
+                } else {
+                    if (lvl == 0) {
+                        dp_prologue<S>(Y, F, B, comm, p.g24 != 0);
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < S; ++s) Y[s] = X[s];
+                    }
+                    settled = dp_advance<S>(Y, F, B, comm, k0, k1, nit);
+#pragma unroll
+                    for (int s = 0; s < S; ++s) X[s] = Y[s];
+                    if (__ballot(active && settled)) T = dp_end<S, AR>(p, tab, Y, F, B, comm, w, a);
+                }
+                const unsigned long long m = __ballot(active && !settled);
+                if (m) {
+                    const unsigned int lane = threadIdx.x & 63;
+                    unsigned int base = 0;
+                    if (lane == 0) base = atomicAdd(&nq[lvl & 1], (unsigned int)__popcll(m));
+                    base = __shfl(base, 0, 64);
+                    if (active && !settled) {
+                        const uint32_t at = base + __popcll(lane ? (m & ((1ull << lane) - 1ull)) : 0ull);
+                        qout[at] = i;
+                        qout[tile + at] = a;
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) qout[(2 + k) * tile + at] = w[k];
+#pragma unroll
+                        for (int s = 0; s < NX; ++s) qout[(2 + NW + s) * tile + at] = X[s];
+                    }
+                }
+                if (active && settled) {
+                    if (p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + i);
+                    const unsigned long long key = make_key(feas, T, i);
+                    best = key < best ? key : best;
+                }
             }
-            eager_epilogue<S>(Y, Fn, Fp, F, B, comm);
-            T = end_time<S, AR>(p, tab, Y, comm, w, a);
-        } else {
-#pragma unroll
-            for (int s = 0; s < S; ++s) Y[s] = X[s];
-            settled = dp_advance<S>(Y, F, B, comm, k0, k1, nit);
-            if (lvl < p.nlevels) enqueue<S, S>(p, lvl & 1, &nq, active && !settled, i, w, a, Y);
-            T = dp_end<S, AR>(p, tab, Y, F, B, comm, w, a);
-        }
-        if (active && settled) {
-            // scattered one-word writes: the nontemporal hint keeps them out of L2 write-allocate
-            if (p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + i);
-            const unsigned long long key = make_key(feas, T, i);
-            best = key < best ? key : best;
+            __syncthreads();   // the level's entries are written and counted
+            cnt = nq[lvl & 1];
+            k0 = k1;
         }
     }
-    if (lvl < p.nlevels) {
-        __syncthreads();
-        if (threadIdx.x == 0) p.qcount[(uint64_t)lvl * p.nseg + blockIdx.x] = nq;
-    }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, lvl == p.nlevels, p.accumulate);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate, nullptr, need);
 }
 
 // Early stop (Eq. 2 / Theorem 1) over one piece of a chunk.  Against the
@@ -2087,18 +2142,8 @@ template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publish, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *pre = reinterpret_cast<uint32_t *>(smem + p.ent_lds);   // nseg + 1 entries
-    // exclusive scan of the segment counts, kPer consecutive segments a thread
-    const uint32_t per = (nseg + kBlock - 1) / kBlock, j0 = threadIdx.x * per;
-    uint32_t mine = 0;
-    for (uint32_t j = j0; j < j0 + per && j < nseg; ++j)
-        mine += __hip_atomic_load(&p.scount[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned long long total;
-    uint32_t run = (uint32_t)block_exclusive_scan_u64(mine, total);
-    for (uint32_t j = j0; j < j0 + per && j < nseg; ++j) {
-        pre[j] = run;
-        run += __hip_atomic_load(&p.scount[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const uint32_t n = (uint32_t)total;
+    uint32_t n;
+    scan_counts(p.scount, nseg, pre, n);
     const uint32_t need = n == 0 ? 1u : min(gridDim.x, (n + kBlock - 1) / kBlock);
     if (blockIdx.x >= need) return;   // (block-uniform: every thread has the same n)
     const Ent tab = entry_tables(p, smem);   // (its barrier also publishes pre)
@@ -2129,21 +2174,57 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
     block_min_and_finish(best, p.acc, p.done, nullptr, p.run_best, true, false, publish ? p.snap : nullptr, need);
 }
 
+constexpr size_t kLdsBlockMax = 64 * 1024;   // LDS bytes one block of these kernels may use
+
 // host-side launchers
 // ---------------------------------------------------------------------------
-template <int S, typename R>
+template <int S>
 hipError_t launch_eval_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
-    if (p.sched) {
-        const dim3 g(lc.grid), b(kBlock);
-        if (p.has_ar && p.nslots) hipLaunchKernelGGL((sched_kernel<S, true, true>), g, b, lc.lds_bytes, st, p);
-        else if (p.has_ar) hipLaunchKernelGGL((sched_kernel<S, true, false>), g, b, lc.lds_bytes, st, p);
-        else if (p.nslots) hipLaunchKernelGGL((sched_kernel<S, false, true>), g, b, lc.lds_bytes, st, p);
-        else hipLaunchKernelGGL((sched_kernel<S, false, false>), g, b, lc.lds_bytes, st, p);
-        return hipGetLastError();
+    const dim3 g(lc.grid), b(kBlock);
+    const bool sch = p.sched != 0, ar = p.has_ar != 0, tab = p.nslots != 0;
+    const int k = (ar ? 4 : 0) | (sch ? 2 : 0) | (tab ? 1 : 0);
+    switch (k) {
+    case 0: hipLaunchKernelGGL((eval_kernel<S, false, false, false>), g, b, lc.lds_bytes, st, p); break;
+    case 1: hipLaunchKernelGGL((eval_kernel<S, false, false, true>), g, b, lc.lds_bytes, st, p); break;
+    case 2: hipLaunchKernelGGL((eval_kernel<S, false, true, false>), g, b, lc.lds_bytes, st, p); break;
+    case 3: hipLaunchKernelGGL((eval_kernel<S, false, true, true>), g, b, lc.lds_bytes, st, p); break;
+    case 4: hipLaunchKernelGGL((eval_kernel<S, true, false, false>), g, b, lc.lds_bytes, st, p); break;
+    case 5: hipLaunchKernelGGL((eval_kernel<S, true, false, true>), g, b, lc.lds_bytes, st, p); break;
+    case 6: hipLaunchKernelGGL((eval_kernel<S, true, true, false>), g, b, lc.lds_bytes, st, p); break;
+    default: hipLaunchKernelGGL((eval_kernel<S, true, true, true>), g, b, lc.lds_bytes, st, p); break;
     }
-    if (p.has_ar) hipLaunchKernelGGL((eval_kernel<S, true>), dim3(lc.grid), dim3(kBlock), lc.lds_bytes, st, p);
-    else hipLaunchKernelGGL((eval_kernel<S, false>), dim3(lc.grid), dim3(kBlock), lc.lds_bytes, st, p);
     return hipGetLastError();
+}
+
+// The kernels of one schedule and end node: f(integral constants AR, SCH)
+template <typename F>
+auto with_variant(const KParams &p, F &&f) {
+    using std::false_type;
+    using std::true_type;
+    if (p.has_ar) return p.sched ? f(true_type{}, true_type{}) : f(true_type{}, false_type{});
+    return p.sched ? f(false_type{}, true_type{}) : f(false_type{}, false_type{});
+}
+
+template <int S>
+hipError_t launch_closed_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    return with_variant(p, [&](auto ar, auto sch) {
+        hipLaunchKernelGGL((closed_kernel<S, decltype(ar)::value, decltype(sch)::value>), dim3(lc.grid), dim3(kBlock),
+                           lc.lds_bytes, st, p);
+        return hipGetLastError();
+    });
+}
+
+// full_kernel on lc.grid2 blocks (LDS: the stage entries, then the scan of
+// the lc.grid segment counts)
+template <int S>
+hipError_t launch_full_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    const size_t lds = (size_t)p.ent_lds + (size_t)lc.grid * 4;
+    if (lds > kLdsBlockMax || lc.grid2 == 0) return hipErrorInvalidValue;
+    return with_variant(p, [&](auto ar, auto sch) {
+        hipLaunchKernelGGL((full_kernel<S, decltype(ar)::value, decltype(sch)::value>), dim3(lc.grid2), dim3(kBlock),
+                           lds, st, p, lc.grid);
+        return hipGetLastError();
+    });
 }
 
 template <int S, typename R>
@@ -2153,24 +2234,11 @@ hipError_t launch_decode_s(const KParams &p, const LaunchCfg &lc, hipStream_t st
     return hipGetLastError();
 }
 
-template <int S, typename R>
-hipError_t launch_resume_s(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t lvl) {
-    const dim3 g(lc.grid), b(kBlock);
-    const bool sch = p.sched != 0;
-    if (p.has_ar && sch) hipLaunchKernelGGL((resume_kernel<S, true, true>), g, b, lc.lds_bytes, st, p, lvl);
-    else if (p.has_ar) hipLaunchKernelGGL((resume_kernel<S, true, false>), g, b, lc.lds_bytes, st, p, lvl);
-    else if (sch) hipLaunchKernelGGL((resume_kernel<S, false, true>), g, b, lc.lds_bytes, st, p, lvl);
-    else hipLaunchKernelGGL((resume_kernel<S, false, false>), g, b, lc.lds_bytes, st, p, lvl);
-    return hipGetLastError();
-}
-
 // One piece of an early-stop chunk: filter_kernel on the grid in lc (LDS:
 // Pascal columns, then the stage tables of lc.lds_bytes), in prefix then
 // gather mode for S >= 4, else in full mode; then surv_kernel on lc.grid2
 // blocks (LDS: the stage entries, then the scan of the lc.grid segment
 // counts).
-constexpr size_t kLdsBlockMax = 64 * 1024;   // LDS bytes one block of these kernels may use
-
 template <int S, typename R, int MODE>
 hipError_t launch_filter_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
     const size_t pas = pascal_bytes<S, R, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p.L);
@@ -2239,15 +2307,21 @@ hipError_t filter_occupancy_s(const KParams &p, size_t ent_lds, int *blocks) {
     }
 }
 
-template <int S, typename R>
-hipError_t occupancy_s(int *blocks, size_t lds, bool ar, bool sched) {
-    // schedules other than 1F1B: the closed-form kernel (the table kernel
-    // runs few candidates per call in practice and takes the same grid)
-    if (sched && ar) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, sched_kernel<S, true, false>, kBlock, lds);
-    if (sched) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, sched_kernel<S, false, false>, kBlock, lds);
-    if (ar) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, eval_kernel<S, true>, kBlock, lds);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, eval_kernel<S, false>, kBlock, lds);
+// Resident blocks per CU of the kernel that evaluates a problem's candidates
+// (`blocks`) and, with the closed form, of full_kernel (`full`).
+template <int S>
+hipError_t occupancy_s(const KParams &p, size_t lds, int *blocks, int *full) {
+    return with_variant(p, [&](auto arc, auto schc) {
+        constexpr bool ar = decltype(arc)::value, sch = decltype(schc)::value;
+        if (!p.closed) {
+            *full = 0;
+            if (p.nslots) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, eval_kernel<S, ar, sch, true>, kBlock, lds);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, eval_kernel<S, ar, sch, false>, kBlock, lds);
+        }
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, closed_kernel<S, ar, sch>, kBlock, lds);
+        if (e != hipSuccess) return e;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(full, full_kernel<S, ar, sch>, kBlock, lds);
+    });
 }
-
 
 }  // namespace pk

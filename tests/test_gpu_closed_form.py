@@ -1,0 +1,92 @@
+"""The closed-form makespan and the recurrence behind it (GPU, through the C-ABI) against the C oracle.
+
+1F1B with M >= 2S + 2 and Eager 1F1B with M >= 4S + 2 take a closed form per candidate, with a
+proof per lane that it is exact; lanes without one go through the recurrence.  The cases sit on both
+sides of those limits, and where the proof goes either way: no, small and dominating transfer times,
+identical layers (stages that tie), layers of zero time, weights above 24 bits, and all-reduce nodes.
+Integer results: equality, no tolerance.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2609_06086_amd import poseidon as P  # noqa: E402
+from paper_2609_06086_amd import workloads as W  # noqa: E402
+from oracle import coracle  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(prob, cands, noalloc):
+    dev = torch.device("cuda:0")
+    ctx = P.poseidon_load_costs(prob, 0)
+    n = len(cands)
+    T = torch.full((n,), -1, dtype=torch.int32, device=dev)
+    bits = torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device=dev)
+    if cands.is_list:
+        kw = dict(comp_rank=torch.from_numpy(cands.comp_rank.view(np.int64)).to(dev))
+        if cands.assign_idx is not None:
+            kw["assign_idx"] = torch.from_numpy(cands.assign_idx.view(np.int32)).to(dev)
+    else:
+        kw = dict(first=cands.first, count=cands.count)
+    call = P.poseidon_eval_candidates_noalloc if noalloc else P.poseidon_eval_candidates
+    best = call(ctx, makespan_out=T, feasible_bits_out=bits, **kw)
+    To, fo = coracle.evaluate(prob, cands)
+    Tg = T.cpu().numpy().view(np.uint32)
+    assert np.array_equal(Tg, To), f"makespans differ at {np.nonzero(Tg != To)[0][:8]}"
+    i = np.arange(n)
+    fg = (bits.cpu().numpy().view(np.uint32)[i >> 5] >> (i & 31).astype(np.uint32)) & 1
+    assert np.array_equal(fg.astype(bool), fo.astype(bool))
+    ob = coracle.argmin(To, fo)
+    assert (best.index, best.makespan) == (ob if ob is not None else (None, None))
+    ctx.close()
+
+
+# transfer times (upper limit) against layer times of 0..hi
+KINDS = {"no_transfer": dict(cost_lo=1, cost_hi=1000, comm_hi=0),
+         "small_transfer": dict(cost_lo=700, cost_hi=1300, comm_hi=150),
+         "ties": dict(cost_lo=1, cost_hi=3, comm_hi=2),
+         "zero_layers": dict(cost_lo=0, cost_hi=5, comm_hi=4),
+         "large_transfer": dict(cost_lo=1, cost_hi=100, comm_hi=3000),
+         "wide_weights": dict(cost_lo=200000, cost_hi=700000, comm_hi=900)}
+
+
+@pytest.mark.parametrize("schedule", [P.SCHEDULE_1F1B, P.SCHEDULE_EAGER_1F1B])
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_closed_form_against_oracle(kind, schedule):
+    rng = np.random.default_rng(7000 + 10 * list(KINDS).index(kind) + schedule)
+    for S in range(1, 17):
+        limit = (4 if schedule else 2) * S + 2
+        M = int(rng.choice([limit - 1, limit, limit + 1, limit + 5, 2 * limit]))
+        L = S + int(rng.integers(0, 40))
+        prob = W.random_problem(rng, L, S, M, int(rng.integers(1, 5)), assign_rows=int(rng.integers(1, 4)),
+                                **KINDS[kind])
+        if kind == "wide_weights":    # a type's total above 2^24, paths below 2^31
+            prob.M = max(2, min(M, int((2 ** 31 - 1) // (2 * 700000 * L + 2 * 900 * S))))
+        prob.schedule = schedule
+        if rng.random() < 0.4 and kind != "wide_weights":
+            prob.allreduce = rng.integers(0, int(rng.choice([2, 50, 5000])), size=(prob.T, L)).astype(np.uint32)
+        cands = W.random_candidates(rng, prob, int(rng.choice([1, 63, 257, 3000])))
+        _check(prob, cands, noalloc=False)
+
+
+@pytest.mark.parametrize("schedule", [P.SCHEDULE_1F1B, P.SCHEDULE_EAGER_1F1B])
+def test_many_candidates_without_proof(schedule):
+    """Transfer times of the order of the stages': most candidates take the recurrence, in tiles of a block's
+    queue (more than one tile, several checkpoints), in the context's workspace and in the fixed scratch."""
+    rng = np.random.default_rng(7100 + schedule)
+    prob = W.random_problem(rng, 40, 6, 90, 2, cost_lo=5, cost_hi=60, comm_hi=900, assign_rows=3)
+    prob.schedule = schedule
+    cands = W.random_candidates(rng, prob, 1500001)
+    _check(prob, cands, noalloc=False)
+    _check(prob, cands, noalloc=True)
+
+
+def test_identical_layers():
+    rng = np.random.default_rng(7200)
+    for S, L, M in ((2, 30, 12), (8, 40, 64), (16, 80, 50)):
+        prob = W.random_problem(rng, L, S, M, 2, comm_hi=60, assign_rows=2)
+        prob.fwd = np.stack([np.full(L, 1000, np.uint32), np.full(L, 1400, np.uint32)])
+        prob.bwd = 2 * prob.fwd
+        _check(prob, W.random_candidates(rng, prob, 20000), noalloc=False)
