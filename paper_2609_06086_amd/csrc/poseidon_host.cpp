@@ -1295,7 +1295,10 @@ int search_expand(SearchRun &r, uint32_t x, uint64_t n, const unsigned long long
     // the count and write kernels add three per-type tables (fb, mfb, hm)
     const size_t lds_cw = lds + 3 * (size_t)r.ctx->T * (r.ctx->L + 1) * 4;
     if (x + 1 == S) {
-        if (pk::launch_search(pk::kSearchOpLeaf, r.kp, q, grid, lds, r.st) != hipSuccess ||
+        // (S > 1: a grid that strides over the piece and takes the stage
+        // entries; a lone stage is tested there too, one candidate a thread)
+        const uint32_t lgrid = S > 1 ? std::min(grid, r.ctx->grid_max) : grid;
+        if (pk::launch_search(pk::kSearchOpLeaf, r.kp, q, lgrid, S > 1 ? r.ctx->ent_lds_bytes : lds, r.st) != hipSuccess ||
             pk::launch_search(pk::kSearchOpMerge, r.kp, q, 1, 0, r.st) != hipSuccess)
             return POSEIDON_E_DEVICE;
         return POSEIDON_OK;

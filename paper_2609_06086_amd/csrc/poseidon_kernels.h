@@ -1010,18 +1010,24 @@ __device__ __forceinline__ unsigned long long block_exclusive_scan_u64(unsigned 
     return before + inc - v;
 }
 
-// Exclusive scan of n per-block counts into LDS (pre[0 .. n-1]) with their
-// total; the caller's next barrier publishes pre.
+// Exclusive scan of n per-block counts (of an earlier kernel) into LDS
+// (pre[0 .. n-1]) with their total; the caller's next barrier publishes pre.
+// The counts are staged in LDS by independent coalesced loads: a thread that
+// loaded its own run of counts waited for each of them, which was most of
+// the time of a kernel with a short list.
 __device__ __forceinline__ void scan_counts(const unsigned int *counts, uint32_t n, uint32_t *pre, uint32_t &total) {
+#pragma unroll 8
+    for (uint32_t j = threadIdx.x; j < n; j += kBlock) pre[j] = counts[j];
+    __syncthreads();
     const uint32_t per = (n + kBlock - 1) / kBlock, j0 = threadIdx.x * per;
     uint32_t mine = 0;
-    for (uint32_t j = j0; j < j0 + per && j < n; ++j)
-        mine += __hip_atomic_load(&counts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (uint32_t j = j0; j < j0 + per && j < n; ++j) mine += pre[j];
     unsigned long long all;
     uint32_t run = (uint32_t)block_exclusive_scan_u64(mine, all);
     for (uint32_t j = j0; j < j0 + per && j < n; ++j) {
+        const uint32_t c = pre[j];
         pre[j] = run;
-        run += __hip_atomic_load(&counts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        run += c;
     }
     total = (uint32_t)all;
 }
@@ -2130,17 +2136,108 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(KParams p) {
     if (bad) atomicOr(p.err, 1u);
 }
 
+// Where only the best candidate of a list is wanted (early stop, search), a
+// candidate whose closed form is not proven needs the recurrence only if its
+// value, a lower bound of its makespan, could still win: its key
+// (value << 32 | position) is below the best known one.  Each wave keeps such
+// candidates in a list in LDS and runs the recurrence on them when 64 have
+// gathered, and on the rest once the block's proven candidates are known.
+// (Problems without a closed form put every candidate there, with value 0.)
+// The best known key is the block's own, in LDS: read from a global word by
+// every wave it cost more than it saved (that word's line serialises them).
+struct Pend {
+    uint32_t *at, *low;            // the wave's [128]: where the candidate is, and its value
+    unsigned long long *known;     // the block's best key so far (starts at the largest that counts)
+    uint32_t n;                    // entries (wave-uniform)
+};
+struct PendLds {
+    uint32_t at[kWaves][128], low[kWaves][128];
+    unsigned long long known;
+};
+__device__ __forceinline__ Pend pend_init(PendLds &l, unsigned long long limit) {
+    if (threadIdx.x == 0) l.known = limit;   // (published by the caller's next barrier)
+    return Pend{l.at[threadIdx.x >> 6], l.low[threadIdx.x >> 6], &l.known, 0u};
+}
+
+// f(at) = exact key, for entries 0 .. n-1 that can still win (n <= 64).
+template <typename F>
+__device__ __forceinline__ void pend_run(const Pend &l, uint32_t first, uint32_t n, unsigned long long &best, F &&f) {
+    wave_lds_sync();
+    const uint32_t lane = threadIdx.x & 63;
+    if (lane < n && (unsigned long long)l.low[first + lane] << 32 <= *l.known) {
+        const unsigned long long key = f(l.at[first + lane]);
+        best = key < best ? key : best;
+    }
+    wave_lds_sync();
+}
+
+// One batch of a wave: `proven` lanes offer their key, the other lanes with
+// `want` set are kept; then the wave runs a full batch if it has one.
+template <typename F>
+__device__ __forceinline__ void pend_add(Pend &l, bool want, bool proven, uint32_t at, uint32_t T, uint32_t pos,
+                                         unsigned long long &best, F &&f) {
+    const uint32_t lane = threadIdx.x & 63;
+    if (want && proven) {
+        const unsigned long long key = make_key(true, T, pos);
+        if (key < best) {
+            best = key;
+            if (key < *l.known) atomicMin(l.known, key);
+        }
+    }
+    const bool keep = want && !proven && (unsigned long long)T << 32 <= *l.known;
+    const unsigned long long m = __ballot(keep);
+    if (m == 0) return;
+    if (keep) {
+        const uint32_t j = l.n + __popcll(lane ? (m & ((1ull << lane) - 1ull)) : 0ull);
+        l.at[j] = at;
+        l.low[j] = T;
+    }
+    l.n += __popcll(m);
+    if (l.n >= 64) {
+        l.n -= 64;
+        pend_run(l, l.n, 64u, best, f);   // (the last 64: the rest stays in place)
+    }
+}
+
+// After a block's last batch (all threads): the rest of the lists against
+// the block's best and *acc.  Returns the thread's best key.
+template <typename F>
+__device__ __forceinline__ unsigned long long pend_finish(Pend &l, unsigned long long best, unsigned long long *acc, F &&f) {
+    if (__syncthreads_or(l.n != 0)) {
+        if (threadIdx.x == 0)
+            atomicMin(l.known, __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        __syncthreads();
+        pend_run(l, 0u, l.n, best, f);
+    }
+    return best;
+}
+
+// One candidate's closed form on its stage weights: true if T is exact,
+// else T is a lower bound (0 without a closed form).
+template <int S, bool AR, bool SCH>
+__device__ __forceinline__ bool closed_or_bound(const KParams &p, const Ent &tab, const uint32_t (&cut)[S + 1],
+                                                const uint32_t (&to)[S], const uint32_t (&F)[S],
+                                                const uint32_t (&B)[S], uint32_t &T) {
+    T = 0;
+    if (!p.closed) return false;
+    uint32_t D[S];
+    if (AR) stage_allreduce<S>(p, tab, cut, to, D);
+    return p.g24 ? closed_form<S, SCH, AR, true>(p, F, B, D, T) : closed_form<S, SCH, AR, false>(p, F, B, D, T);
+}
+
 // surv_kernel takes the survivor list as one sequence in segment order
 // (segment j: scount[j] entries from j seg_cap).  Every block scans the nseg
 // segment counts into LDS, after the stage entries; survivor k then goes to
 // thread k mod (grid kBlock), found by a binary search of the scan, so the
-// DPs of however many survivors spread over the whole grid, 64 to a wave.
-// Only the blocks the list needs (one per kBlock survivors, at least one)
-// go on: the others leave before loading the entries and take no ticket on
-// the done counter.
+// survivors spread over the whole grid, 64 to a wave.  Only the blocks the
+// list needs (one per kBlock survivors, at least one) go on: the others
+// leave before loading the entries and take no ticket on the done counter.
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publish, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ PendLds pend;
+    // a makespan above the caller's bound never becomes the result
+    Pend l = pend_init(pend, (unsigned long long)p.es_bound << 32 | 0xFFFFFFFFu);
     uint32_t *pre = reinterpret_cast<uint32_t *>(smem + p.ent_lds);   // nseg + 1 entries
     uint32_t n;
     scan_counts(p.scount, nseg, pre, n);
@@ -2149,28 +2246,43 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
     const Ent tab = entry_tables(p, smem);   // (its barrier also publishes pre)
     const Comm<S> comm = load_comm<S>(p);
     constexpr int NW = Codes<S>::kWords;
-    unsigned long long best = ~0ull;
-    for (uint32_t k = blockIdx.x * kBlock + threadIdx.x; k < n; k += gridDim.x * kBlock) {
-        // the last segment j with pre[j] <= k holds survivor k
-        uint32_t lo = 0, hi = nseg;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (pre[mid] <= k) lo = mid;
-            else hi = mid;
-        }
-        const uint32_t at = lo * (uint32_t)p.seg_cap + (k - pre[lo]);
-        const uint32_t i = p.sidx[at];
-        uint32_t w[NW], cut[S + 1], to[S], F[S], B[S];
+    auto load = [&](uint32_t at, uint32_t &i, uint32_t &a, uint32_t (&w)[NW], uint32_t (&cut)[S + 1], uint32_t (&to)[S],
+                    uint32_t (&F)[S], uint32_t (&B)[S]) {
+        i = p.sidx[at];
 #pragma unroll
         for (int kk = 0; kk < NW; ++kk) w[kk] = p.codes[kk * (uint32_t)p.ccap + at];
         unpack_cuts<S>(w, p.L, cut);
-        const uint32_t a = assign_of(p, i);
+        a = assign_of(p, i);
         decode_toff<S>(p, tab, a, to);
         stage_weights<S>(p, tab, cut, to, F, B);
-        const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, a);
-        const unsigned long long key = make_key(true, T, i);
-        best = key < best ? key : best;
+    };
+    auto full = [&](uint32_t at) {
+        uint32_t i, a, w[NW], cut[S + 1], to[S], F[S], B[S];
+        load(at, i, a, w, cut, to, F, B);
+        return make_key(true, dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, a), i);
+    };
+    unsigned long long best = ~0ull;
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t k0 = blockIdx.x * kBlock + (threadIdx.x - lane); k0 < n; k0 += gridDim.x * kBlock) {   // (wave-uniform)
+        const uint32_t k = k0 + lane;
+        uint32_t at = 0, i = 0, T = 0;
+        bool proven = false;
+        if (k < n) {
+            // the last segment j with pre[j] <= k holds survivor k
+            uint32_t lo = 0, hi = nseg;
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (pre[mid] <= k) lo = mid;
+                else hi = mid;
+            }
+            at = lo * (uint32_t)p.seg_cap + (k - pre[lo]);
+            uint32_t a, w[NW], cut[S + 1], to[S], F[S], B[S];
+            load(at, i, a, w, cut, to, F, B);
+            proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
+        }
+        pend_add(l, k < n, proven, at, T, i, best, full);
     }
+    best = pend_finish(l, best, p.acc, full);
     block_min_and_finish(best, p.acc, p.done, nullptr, p.run_best, true, false, publish ? p.snap : nullptr, need);
 }
 

@@ -596,38 +596,76 @@ __global__ __launch_bounds__(kBlock) void search_write_kernel(KParams p, SearchP
     }
 }
 
-// Level S-1: the last stage is [c_{S-1}, L); test it like any stage, then
-// evaluate the complete configuration on the DAG.  Reduces
-// (T << 32 | position) over the candidates with T <= bound into *q.acc.
+// Complete configurations (level S-1; for S > 1 the level that fixed the
+// last cut already tested the last stage, for S = 1 it is tested here):
+// their makespans, closed form first.  Reduces (T << 32 | position) over the
+// candidates with T <= bound into *q.acc.  The grid strides over the piece;
+// almost every candidate ends with its closed form (2^22 of 8 stages: 225 us
+// with the recurrence for each).
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void search_leaf_kernel(KParams p, SearchParams q) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t n_in = search_n_in(q);
     if (blockIdx.x * kBlock >= n_in) return;   // past the level's nodes
-    const Lds tab = stage_tables(p, smem);
-    const Comm<S> comm = load_comm<S>(p);
     constexpr int NW = Codes<S>::kWords;
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    const bool active = i < n_in;
     const uint32_t bound = *q.bound;
-    uint32_t row, w[NW], ty[S], cut[S + 1];
-    search_load<S>(q, i, active, row, w);
-    int why = 4;
-    unsigned long long key = ~0ull;
-    if (active) {
-        const SearchNode n = search_node<S, AR>(p, tab, row, w, S - 1, ty, cut);
-        // for S > 1 the level that fixed the last cut already tested the last stage
-        why = S == 1 ? search_try<AR>(p, tab, n, S - 1, p.L, q.flags, bound) : 0;
+    if constexpr (S == 1) {
+        const Lds tab = stage_tables(p, smem);
+        const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+        uint32_t row, w[NW], ty[S], cut[S + 1];
+        search_load<S>(q, i, i < n_in, row, w);
+        int why = 4;
+        unsigned long long key = ~0ull;
+        if (i < n_in) {
+            const SearchNode n = search_node<S, AR>(p, tab, row, w, S - 1, ty, cut);
+            why = search_try<AR>(p, tab, n, S - 1, p.L, q.flags, bound);
+            if (why == 0) {
+                uint32_t F[S], B[S];
+                stage_weights<S>(p, tab, cut, ty, F, B);
+                const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, load_comm<S>(p), w, row);
+                if (T <= bound) key = ((unsigned long long)T << 32) | i;
+            }
+        }
+        search_flush(q, why == 0, why == 0, why == 1, why == 2, why == 3);
+        block_min_and_finish(key, q.acc, nullptr, nullptr, nullptr, false);
+    } else {
+        __shared__ PendLds pend;
+        // a makespan above the bound or not below the best of the earlier
+        // pieces never becomes the result
+        const unsigned long long had = q.best[0];
+        if (had == 0) return;
+        const uint32_t most = had <= bound ? (uint32_t)had - 1u : bound;
+        Pend l = pend_init(pend, (unsigned long long)most << 32 | 0xFFFFFFFFu);
+        const Ent tab = entry_tables(p, smem);   // (its barrier publishes pend)
+        const Comm<S> comm = load_comm<S>(p);
+        auto full = [&](uint32_t i) {
+            uint32_t row, w[NW], cut[S + 1], to[S], F[S], B[S];
+            search_load<S>(q, i, true, row, w);
+            unpack_cuts<S>(w, p.L, cut);
+            decode_toff<S>(p, tab, row, to);
+            stage_weights<S>(p, tab, cut, to, F, B);
+            const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, row);
+            return make_key(true, T, i);
+        };
+        unsigned long long best = ~0ull;
+        const uint32_t lane = threadIdx.x & 63;
+        for (uint32_t i0 = blockIdx.x * kBlock + (threadIdx.x - lane); i0 < n_in; i0 += gridDim.x * kBlock) {   // (wave-uniform)
+            const uint32_t i = i0 + lane;
+            uint32_t T = 0;
+            bool proven = false;
+            if (i < n_in) {
+                uint32_t row, w[NW], cut[S + 1], to[S], F[S], B[S];
+                search_load<S>(q, i, true, row, w);
+                unpack_cuts<S>(w, p.L, cut);
+                decode_toff<S>(p, tab, row, to);
+                stage_weights<S>(p, tab, cut, to, F, B);
+                proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
+            }
+            pend_add(l, i < n_in, proven, i, T, i, best, full);
+        }
+        best = pend_finish(l, best, q.acc, full);
+        block_min_and_finish((uint32_t)(best >> 32) <= bound ? best : ~0ull, q.acc, nullptr, nullptr, nullptr, false);
     }
-    const bool leaf = why == 0;
-    if (leaf) {
-        uint32_t F[S], B[S];
-        stage_weights<S>(p, tab, cut, ty, F, B);
-        const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, row);
-        if (T <= bound) key = ((unsigned long long)T << 32) | i;
-    }
-    if (S == 1) search_flush(q, leaf, leaf, why == 1, why == 2, why == 3);
-    block_min_and_finish(key, q.acc, nullptr, nullptr, nullptr, false);
 }
 
 // After a leaf piece: the piece's best candidate replaces the best so far
