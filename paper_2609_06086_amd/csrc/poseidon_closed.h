@@ -7,20 +7,17 @@
 // backwards (1F1B's order F^{S-x-1} (F B)* B* is the same sequence).  Write
 // r_x = F_x + B_x and e_x = cf_x + cb_x (boundary x, between stages x, x+1).
 //
-// Value.  For every stage x there is a path that enters the pairs of stage x
-// as late as any path can, stays there to the last pair and leaves along the
+// Value.  For every stage x there is a path that reaches its first pair as
+// late as any path, stays at the stage to the last pair and leaves along the
 // heaviest way out:
-//   T_x = phi_x + (n_x - 1) r_x + X_x,
-//   Fw_x  = (F_0 + .. + F_x) + (cf_0 + .. + cf_{x-1}) + (m_x - 1) max(F_0 .. F_x)
-//           the finish of the last warm-up forward (a monotone path through
-//           rows of constant weight spends its free steps on the heaviest),
-//   U_x   = max(Fw_x, U_{x+1} + B_{x+1} + cb_x)          the start of B_{x,1},
-//   phi_x = max(U_x + B_x, the warm-up forwards of stage x-1 that the first
-//           pairs read)                                   the start of F_{x,m_x+1},
-// and, from the finish of the stage's last pair backward, X_x: the same with
-// time reversed (F and B, cf and cb exchanged, the drain for the warm-up;
-// with all-reduce nodes a drain path may end at any stage's R).  Every T_x
-// is the weight of a path, so T >= max_x T_x.
+//   T_x = U_x + n_x r_x + V_x,
+//   U_x  = max(Fw_x, U_{x+1} + B_{x+1} + cb_x)          the start of B_{x,1},
+//   Fw_x = (F_0 + .. + F_x) + (cf_0 + .. + cf_{x-1}) + (m_x - 1) max(F_0 .. F_x)
+//          the finish of the last warm-up forward (a monotone path through
+//          rows of constant weight spends its free steps on the heaviest),
+// and V_x, from the finish of F_{x,M} to the end, the same with time reversed
+// (F and B, cf and cb exchanged, the drain for the warm-up; with all-reduce
+// nodes a drain path may end at any stage's R).  So T >= max_x T_x.
 //
 // Proof.  Let s be the stage with the largest rate among those a path visits
 // in its pairs.  Every edge between pair nodes of 1F1B joins consecutive
@@ -30,19 +27,24 @@
 // towards s, and as many of the other one.  So if every stage y that is not
 // in a set K of pairwise non-adjacent stages has
 //   r_y + e_{y-1} + e_y <= r_k for all k in K                             (1)
-// then no detour gains (each edge is charged to an end point outside K), and
-// neither does entering or leaving the pairs elsewhere and walking to s:
-// the longest path stays at one stage.  Raising the rate of the stages
-// outside K to r~_y = r_y + e_{y-1} + e_y makes that hold whichever of them
-// a path visits, so
-//   T <= max( max_{k in K} T_k, max_{y not in K} T_y + (n_y - 1)(e_{y-1} + e_y) ).
+// then no detour gains (each edge is charged to an end point outside K).
+// Nor does entering the pairs elsewhere and walking to s: from a stage below,
+// the walk's backwards are in U_s; from the warm-up of a stage above, it
+// brought (m - 1) max(F_0 .. F_x) along, and is matched by Fw_s while that
+// maximum is at most r_s; if it is larger, at stage j, the path that stays at
+// j until it walks to s is heavier and has the larger rate, and the argument
+// starts again from there.  Leaving is entering with time reversed.  Raising
+// the rate of the stages outside K to r_y + g_y, g_y = e_{y-1} + e_y, makes
+// (1) hold whichever of them a path visits (and its first and last pair may
+// each gain g_y), so
+//   T <= max( max_{k in K} T_k, max_{y not in K} T_y + (n_y + 1) g_y ).
 // With K = the stages whose raised value or rate reaches the largest
-// (T_x + (n_x - 1) g_x >= max T, or r_x + g_x >= max r; g_x = e_{x-1} + e_x)
-// the right side is max_x T_x, and the lane holds the exact makespan if K
-// satisfies (1) and has no adjacent stages.  Under Eager 1F1B a detour also
-// takes two idle slots per crossing, which its forward and backward cover,
-// and T = max_x T_x whenever no boundary weighs more than a stage's F or B.
-// The bounds on M leave room for the walks between stages.
+// (T_x + (n_x + 1) g_x >= max T, or r_x + g_x >= max r) the right side is
+// max_x T_x, and the lane holds the exact makespan if K satisfies (1) and has
+// no adjacent stages.  Under Eager 1F1B a detour also takes two idle slots
+// per crossing, which its forward and backward cover, and T = max_x T_x
+// whenever no boundary weighs more than a stage's F or B.  The bounds on M
+// leave room for the walks between stages.
 //
 // Lanes without proof are evaluated by the recurrence.  On the synthetic
 // workloads (16 and 8 stages, 2-4 device types) 99.5 - 99.8 % of the
@@ -86,16 +88,16 @@ struct ClosedConst {
 // whether it is proven to be the makespan.
 //
 // The quantities are kept relative to the transfer times of the boundaries
-// above their stage: entries less Phi_x = cf_0 + .. + cf_{x-1}, exits less
-// Psi_x = cb_0 + .. + cb_{x-1}.  An input from the stage above then needs no
-// transfer time, one from the stage below carries e_x = cf_x + cb_x, and
+// above their stage: U less Phi_x = cf_0 + .. + cf_{x-1}, V less Psi_x =
+// cb_0 + .. + cb_{x-1}.  An input from the stage below then carries e_x, and
 // T_x gains Phi_x + Psi_x = e_0 + .. + e_{x-1}.
 template <int S, bool EAGER, bool AR, bool U24>
 __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
-                                              const uint32_t (&D)[S], uint32_t &T) {
+                                            const uint32_t (&D)[S], uint32_t &T) {
     const ClosedConst cc(p);
-    // entries: P[x] = phi_x (Fw_x until then); C[x]: Eager's forward inputs
-    uint32_t P[S], C[EAGER ? S : 1];
+    // P[x] = Fw_x (later T_x), X[x] = the drain of stage x from the start of
+    // its first backward
+    uint32_t P[S], X[S];
     {
         uint32_t pre = 0, mx = 0;
 #pragma unroll
@@ -103,64 +105,42 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
             pre += F[x];
             mx = max(mx, F[x]);
             P[x] = pre + mul_small<U24>(mx, warm_steps<S, EAGER>(x));
-            // Eager: F_{x+1,m+1} reads stage x's last but one warm-up
-            // forward, F_{x+1,m+2} (one pair later) its last
-            if constexpr (EAGER) {
-                const int n = x + 1 < S ? x + 1 : 0;
-                C[n] = P[x] - min(mx, F[n] + B[n]);
-            }
         }
-        uint32_t u = P[S - 1];
-#pragma unroll
-        for (int x = S - 1; x > 0; --x) {
-            const uint32_t t = u + B[x];
-            u = max(P[x - 1], t + cc.at<kCE>(x - 1));
-            P[x] = max(t, EAGER ? C[EAGER ? x : 0] : P[x - 1]);
-        }
-        P[0] = u + B[0];
     }
-    // exits: X[x] = the drain of stage x from the start of its first
-    // backward (Dr_x); E[x]: the way out through the drain of stage x - 1
-    uint32_t X[S], E[EAGER ? S : 1];
     {
         uint32_t pre = 0, mx = 0, tail = 0, A[AR ? S : 1];
 #pragma unroll
         for (int x = 0; x < S; ++x) {
-            const int n = x + 1 < S ? x + 1 : 0;
+            const uint32_t h = warm_steps<S, EAGER>(x);
             pre += B[x];
             if constexpr (!AR) {
                 mx = max(mx, B[x]);
-                X[x] = pre + mul_small<U24>(mx, warm_steps<S, EAGER>(x));
-                if constexpr (EAGER) E[n] = X[x] - min(mx, F[n] + B[n]);
+                X[x] = pre + mul_small<U24>(mx, h);
             } else {
                 // A[j] + h B_j (+ the path down to stage j): the drain that
                 // takes its h free steps at stage j and then goes on to the
                 // heaviest R
                 tail = x == 0 ? D[0] : max(D[x], tail + B[x > 0 ? x - 1 : 0] + cc.at<kCCb>(x > 0 ? x - 1 : 0));
                 A[x] = tail + B[x] - pre - cc.at<kCPsi>(x);
-                const uint32_t h = warm_steps<S, EAGER>(x);
-                uint32_t m = 0, m1 = 0;
+                uint32_t m = 0;
 #pragma unroll
-                for (int j = 0; j <= x; ++j) {
-                    m = max(m, A[j] + mul_small<U24>(B[j], h));
-                    if (EAGER && n) m1 = max(m1, A[j] + mul_small<U24>(B[j], h - 1));
-                }
+                for (int j = 0; j <= x; ++j) m = max(m, A[j] + mul_small<U24>(B[j], h));
                 X[x] = pre + m;
-                // (one pair earlier; a drain shorter than that pair never decides)
-                if constexpr (EAGER) E[n] = max(pre + m1, max(X[x], F[n] + B[n]) - (F[n] + B[n]));
             }
         }
     }
-    // T_x, from the last stage down (n_x - 1 = M - 2 - (m_x - 1))
-    uint32_t v = X[S - 1], Tm = 0, rm = 0;
+    // T_x, from the last stage up (n_x = M - 1 - (m_x - 1))
+    uint32_t u = P[S - 1], v = X[S - 1], Tm = 0, rm = 0;
 #pragma unroll
     for (int x = S - 1; x >= 0; --x) {
-        const int d = x > 0 ? x - 1 : 0;
-        const uint32_t t = v + F[x], r = F[x] + B[x];
-        const uint32_t out = x > 0 ? max(t, EAGER ? E[EAGER ? x : 0] : X[d]) : t;
-        if (x > 0) v = max(X[d], t + cc.at<kCE>(d));
-        P[x] += mul_small<U24>(r, p.M - 2 - warm_steps<S, EAGER>(x));
-        P[x] += out + cc.at<kCSum>(x);
+        if (x < S - 1) {
+            const int b = x + 1 < S ? x + 1 : 0;   // the stage below
+            u = max(P[x], u + B[b] + cc.at<kCE>(x));
+            v = max(X[x], v + F[b] + cc.at<kCE>(x));
+        }
+        const uint32_t r = F[x] + B[x];
+        P[x] = u + mul_small<U24>(r, p.M - 1 - warm_steps<S, EAGER>(x));
+        P[x] += v + cc.at<kCSum>(x);
         Tm = max(Tm, P[x]);
         rm = max(rm, r);
     }

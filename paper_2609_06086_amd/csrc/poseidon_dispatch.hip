@@ -50,6 +50,10 @@ size_t noalloc_scratch_bytes() { return sizeof(scratch); }
     extern template hipError_t launch_eval_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     extern template hipError_t launch_closed_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                       \
     extern template hipError_t launch_full_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
+    extern template hipError_t launch_fused_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
+    extern template hipError_t launch_fused_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
+    extern template hipError_t fused_occupancy_s<S, uint32_t>(const KParams &, int *);                                    \
+    extern template hipError_t fused_occupancy_s<S, uint64_t>(const KParams &, int *);                                    \
     extern template hipError_t launch_decode_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
     extern template hipError_t launch_decode_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
     extern template hipError_t launch_bounded_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t, uint32_t);  \
@@ -193,6 +197,14 @@ hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st) 
 
 hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
     PK_DISPATCH_S(launch_closed_s, p.S, p, lc, st)
+}
+
+hipError_t launch_fused(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    PK_DISPATCH(launch_fused_s, p.S, p.wide, p, lc, st)
+}
+
+hipError_t fused_occupancy(const KParams &p, int *blocks) {
+    PK_DISPATCH(fused_occupancy_s, p.S, p.wide, p, blocks)
 }
 
 hipError_t launch_full(const KParams &p, const LaunchCfg &lc, hipStream_t st) {

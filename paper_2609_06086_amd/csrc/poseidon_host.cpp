@@ -339,6 +339,7 @@ struct poseidon_ctx {
     uint32_t filter_grid;  // blocks of the early-stop filter that are resident at once
     uint32_t grid_max;
     uint32_t full_grid;    // blocks of the recurrence pass behind the closed form
+    uint32_t fuse_grid;    // blocks of the fused decode and closed form (0: not used)
     void *ws;              // cut codes + straggler queues of the steady-state cascade
     uint64_t ws_n;         // candidates per chunk the workspace is for
     uint64_t ws_cap;       // entries of its arrays (ws_n and slack for per-block segments)
@@ -511,12 +512,10 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
         const unsigned __int128 vmax = w == 64 ? (unsigned __int128)UINT64_MAX : (unsigned __int128)0xFFFFFFFFu;
         std::vector<unsigned __int128> col(NHd);
         for (uint32_t n = 0; n < NHd; ++n) col[n] = std::min<unsigned __int128>(binom_sat(n, k), vmax);
-        for (int z = 0; z < w; ++z)
-            for (int m = 0; m < 16; ++m) {
-                const unsigned __int128 lo = pk::bucket_lo(w, z, m);
-                const uint32_t n = (uint32_t)(std::lower_bound(col.begin(), col.end(), lo) - col.begin());
-                btab[(size_t)k * pk::kBucketTab + 16 * z + m] = (uint8_t)std::min(n, NHd - 1);
-            }
+        for (uint32_t key = 0; key < pk::bucket_tab_bytes(w); ++key) {
+            const uint32_t n = (uint32_t)(std::lower_bound(col.begin(), col.end(), pk::bucket_lo(key)) - col.begin());
+            btab[(size_t)k * pk::kBucketTab + key] = (uint8_t)std::min(n, NHd - 1);
+        }
     }
 
     pk::KParams kp;
@@ -578,7 +577,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
         row(pk::kCSum)[s] = s > 0 ? row(pk::kCSum)[s - 1] + lo : 0u;
         row(pk::kCE2)[s] = lo + hi;
         // (1F1B, M > S; at most M times the boundaries' sum, below 2^31)
-        if (kp.closed) row(pk::kCE2n)[s] = (M - S - 1 + s) * (lo + hi);
+        if (kp.closed) row(pk::kCE2n)[s] = (M - S + 1 + s) * (lo + hi);
         row(pk::kCCb)[s] = s + 1 < S ? kp.cb[s] : 0u;
         row(pk::kCPsi)[s] = s > 0 ? row(pk::kCPsi)[s - 1] + kp.cb[s - 1] : 0u;
         kp.edge_max = std::max(kp.edge_max, hi);
@@ -603,7 +602,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     const bool has_table = p->assign && A > 1;
     if (A == 1) {
         kp.assign_mode = pk::kAssignFixed;
-        for (uint32_t s = 0; s < ndev; ++s) kp.fixed_types[s] = p->assign ? p->assign[s] : 0;
+        for (uint32_t s = 0; s < ndev; ++s) kp.fixed_word[s / 4] |= (uint32_t)(p->assign ? p->assign[s] : 0) << (8 * (s % 4));
     } else if (has_table) {
         kp.assign_mode = pk::kAssignTable;
     } else {
@@ -735,6 +734,13 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
             break;
         }
         ctx->grid_max = (uint32_t)std::max(1, occ) * (uint32_t)std::max(1, prop.multiProcessorCount);
+        // the fused pass needs its products in 24 bits and its tables in a CU's LDS
+        int fuse = 0;
+        if (kp.closed && kp.g24 && pk::fused_occupancy(kp, &fuse) != hipSuccess) {
+            status = POSEIDON_E_DEVICE;
+            break;
+        }
+        ctx->fuse_grid = (uint32_t)std::max(0, fuse) * (uint32_t)std::max(1, prop.multiProcessorCount);
         ctx->full_grid = (uint32_t)std::max(1, full) * (uint32_t)std::max(1, prop.multiProcessorCount);
         // (at most grid_max: the survivor segments are sized for that many blocks)
         ctx->filter_grid = std::min(ctx->grid_max,
@@ -842,6 +848,27 @@ ChunkGrid chunk_grid(const poseidon_ctx *ctx, uint64_t n) {
     g.seg_cap = (n + stride - 1) / stride * 256;
     return g;
 }
+// The same of the fused pass: a block of kFuseThreads lanes takes one
+// candidate a lane at a time (succ: consecutive ranks, kDecodeIlp a lane), so
+// a short call spreads over the chip before its lanes take several.
+ChunkGrid fuse_chunk_grid(const poseidon_ctx *ctx, uint64_t n, bool succ) {
+    ChunkGrid g;
+    const uint64_t per = (uint64_t)pk::kFuseThreads * (succ ? pk::kDecodeIlp : 1);
+    g.grid = (uint32_t)std::min<uint64_t>((n + per - 1) / per, ctx->fuse_grid);
+    const uint64_t stride = g.grid * per;
+    g.seg_cap = (n + stride - 1) / stride * per;
+    return g;
+}
+// Entries that hold any pass's segments for n candidates.
+uint64_t segment_cap(const poseidon_ctx *ctx, uint64_t n) {
+    const ChunkGrid g = chunk_grid(ctx, n);
+    uint64_t cap = std::max<uint64_t>(n, g.grid * g.seg_cap);
+    for (int succ = 0; ctx->fuse_grid && succ < 2; ++succ) {
+        const ChunkGrid f = fuse_chunk_grid(ctx, n, succ != 0);
+        cap = std::max<uint64_t>(cap, f.grid * f.seg_cap);
+    }
+    return cap;
+}
 
 // Interleaved 1F1B: slots of a straggler queue for chunks of n candidates
 // (one block of slack per segment) and the words of an entry: candidate
@@ -879,10 +906,13 @@ uint32_t tile_for(const poseidon_ctx *ctx, uint64_t n) {
 // per block of slack, so that per-block segments fit): the cut codes
 // [words][cap], the early-stop survivor indices [cap] and the first-stage
 // list [kAListWords][cap] (the closed form's list of candidates without a
-// proof takes the same words) with their per-block counts [grid_max] each;
+// proof takes the same words) with their per-block counts [count_words] each;
 // then the recurrence pass's queues (closed form), or two straggler queues
 // and their counts [levels][grid_max] (Interleaved 1F1B).  Grown on demand;
 // the old buffer is released only after the stream has drained.
+// per-block counts of any pass
+uint64_t count_words(const poseidon_ctx *ctx) { return std::max(ctx->grid_max, ctx->fuse_grid); }
+
 int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     if (ctx->ws_n >= n) return POSEIDON_OK;
     if (ctx->ws) {
@@ -898,10 +928,10 @@ int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     while (r < n && r < (1ull << 20)) r *= 2;
     n = (n + r - 1) / r * r;
     // (a multiple of 4 words: the range-mode decode stores four code words at once)
-    const uint64_t cap = (n + (uint64_t)chunk_grid(ctx, n).grid * pk::kDecodeIlp * 256 + 3) & ~3ull;
+    const uint64_t cap = (std::max<uint64_t>(segment_cap(ctx, n), n + (uint64_t)chunk_grid(ctx, n).grid * pk::kDecodeIlp * 256) + 3) & ~3ull;
     const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
     // cut codes, the early stop's survivor and first-stage lists and their counts
-    uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * ctx->grid_max;
+    uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * count_words(ctx);
     if (ctx->base.closed) elems += tile_queue_words(ctx, tile_for(ctx, n)) * full_grid_for(ctx, n);
     else if (ctx->base.nlevels)
         elems += 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) + (uint64_t)pk::kMaxLevels * ctx->grid_max;
@@ -951,16 +981,16 @@ uint64_t noalloc_layout(const poseidon_ctx *ctx, uint64_t n, uint32_t *base, Eva
     const ChunkGrid g = chunk_grid(ctx, n);
     memset(m, 0, sizeof(*m));
     uint64_t o = 0;
-    const uint64_t cap = std::max<uint64_t>(n, (uint64_t)g.grid * g.seg_cap);
+    const uint64_t cap = segment_cap(ctx, n);
     m->codes = base;
-    o += words * cap;
+    if (!ctx->fuse_grid) o += words * cap;   // (the fused pass keeps the cut codes in registers)
     if (ctx->base.closed) {
         m->tile = kNoallocTile;
         m->full_grid = std::min(ctx->full_grid, kNoallocFullGrid);
         m->list = base + o;
         o += full_list_words(ctx) * cap;
         m->counts = base + o;
-        o += g.grid;
+        o += count_words(ctx);
         m->queues = base + o;
         o += tile_queue_words(ctx, m->tile) * m->full_grid;
     } else if (ctx->base.nlevels) {
@@ -981,6 +1011,19 @@ uint64_t noalloc_chunk_for(const poseidon_ctx *ctx) {
     return 0;
 }
 
+// Range mode with several assignments: `first` as rank and assignment, and
+// the magic number of a 32-bit division by A where every assignment of the
+// call plus `first`'s fits 32 bits (else 0: the kernels divide in 64 bits).
+void split_first(const poseidon_ctx *ctx, const poseidon_cands *c, pk::KParams &kp) {
+    if (c->comp_rank || ctx->A < 2) return;
+    kp.first_rank = c->first / ctx->A;
+    const uint64_t asg = c->first % ctx->A;
+    if (ctx->A < (1ull << 32) && asg + c->count <= (1ull << 32)) {
+        kp.first_asg = (uint32_t)asg;
+        kp.div_magic = (uint32_t)((1ull << 32) / ctx->A);
+    }
+}
+
 // One evaluation call in chunks of at most `chunk` candidates.
 int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makespan_out,
                 uint32_t *feasible_bits_out, poseidon_best *best_out, hipStream_t st, uint64_t chunk,
@@ -995,6 +1038,7 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
     kp.makespan_out = makespan_out;
     kp.feas_bits_out = feasible_bits_out;
     kp.nwords = (cands->count + 31) / 32;
+    split_first(ctx, cands, kp);
     kp.codes = m.codes;
     kp.ccap = m.cap;
     if (kp.closed) {
@@ -1012,7 +1056,8 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         kp.first_i = c0;
         kp.n_i = std::min(chunk, cands->count - c0);
         kp.accumulate = c0 > 0;
-        const ChunkGrid g = chunk_grid(ctx, kp.n_i);
+        const bool fuse = ctx->fuse_grid != 0;
+        const ChunkGrid g = fuse ? fuse_chunk_grid(ctx, kp.n_i, !kp.comp_rank && ctx->A == 1) : chunk_grid(ctx, kp.n_i);
         pk::LaunchCfg lc;
         lc.lds_bytes = ctx->base.sched == POSEIDON_SCHEDULE_INTERLEAVED_1F1B ? ctx->lds_bytes : ctx->ent_lds_bytes;
         lc.grid = g.grid;
@@ -1020,6 +1065,11 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         // segments of the lists: block b owns seg_cap slots
         kp.nseg = lc.grid;
         kp.seg_cap = g.seg_cap;
+        if (fuse) {
+            if (pk::launch_fused(kp, lc, st) != hipSuccess || pk::launch_full(kp, lc, st) != hipSuccess)
+                return rearm(ctx, st);
+            continue;
+        }
         pk::LaunchCfg ld = lc;
         ld.grid = (uint32_t)std::min<uint64_t>((kp.n_i + 4 * 256 - 1) / (4 * 256), ctx->grid_max);
         if (pk::launch_decode(kp, ld, st) != hipSuccess) return rearm(ctx, st);
@@ -1063,8 +1113,8 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands, uin
     // (laid out as ensure_workspace describes it)
     uint32_t *o = m.codes + ((uint64_t)pk::code_words((int)ctx->S) + 1) * m.cap;
     m.counts = o;
-    m.list = o + ctx->grid_max;
-    m.queues = m.list + pk::kAListWords * m.cap + ctx->grid_max;
+    m.list = o + count_words(ctx);
+    m.queues = m.list + pk::kAListWords * m.cap + count_words(ctx);
     m.qcap = queue_cap(ctx, m.cap);
     m.tile = tile_for(ctx, ctx->ws_n);
     m.full_grid = full_grid_for(ctx, ctx->ws_n);
@@ -1122,6 +1172,7 @@ int poseidon_eval_candidates_bounded(poseidon_ctx *ctx, const poseidon_cands *ca
     kp.count = cands->count;
     kp.comp_rank = cands->comp_rank;
     kp.assign_idx = cands->assign_idx;
+    split_first(ctx, cands, kp);
     const uint64_t n = cands->count;
     if (chunk == 0 || chunk > n) chunk = n;
     // the survivor list has room for the survivors of kChunk candidates; a
@@ -1133,7 +1184,7 @@ int poseidon_eval_candidates_bounded(poseidon_ctx *ctx, const poseidon_cands *ca
     kp.ccap = ctx->ws_cap;
     kp.sidx = (uint32_t *)ctx->ws + (uint64_t)pk::code_words((int)ctx->S) * ctx->ws_cap;
     kp.scount = (unsigned int *)(kp.sidx + ctx->ws_cap);
-    kp.alist = (uint32_t *)(kp.scount + ctx->grid_max);
+    kp.alist = (uint32_t *)(kp.scount + count_words(ctx));
     kp.acount = (unsigned int *)(kp.alist + (uint64_t)pk::kAListWords * ctx->ws_cap);
     kp.es_bound = bound;
     pk::LaunchCfg lc;

@@ -9,6 +9,10 @@
     template hipError_t launch_eval_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     template hipError_t launch_closed_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                       \
     template hipError_t launch_full_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
+    template hipError_t launch_fused_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
+    template hipError_t launch_fused_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
+    template hipError_t fused_occupancy_s<S, uint32_t>(const KParams &, int *);                                    \
+    template hipError_t fused_occupancy_s<S, uint64_t>(const KParams &, int *);                                    \
     template hipError_t launch_decode_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
     template hipError_t launch_decode_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);             \
     template hipError_t launch_bounded_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t, uint32_t);  \

@@ -10,26 +10,37 @@ constexpr int kSMax = 16;
 constexpr uint32_t kNB = 256;   // Pascal-table column length (n = 0..255; L <= 256)
 constexpr uint32_t kTypesMax = 8;   // device types (the ABI's limit, checked where both are seen)
 
-// Buckets of the unranking searches.  A value Q >= 1 of a w-bit type falls in
-// bucket (z, m): z its number of leading zeros in w bits, m the 4 bits after
-// its leading one (zero-filled when fewer follow it); key = 16 z + m.  The
-// bucket holds [bucket_lo(z, m), bucket_lo of the next key), the next key
-// being (z, m + 1), or (z - 1, 0) after m = 15; keys that no value has get
-// an empty range.  For each Pascal column the host tabulates, per key, the
-// first row whose entry reaches bucket_lo (kBucketTab bytes a column), so a
-// search starts there and needs only a few halvings.
 // Halvings of one cut search over a whole Pascal column: the smallest H with
 // L <= 2^H (at least 5); the columns hold rows n < 2^H.
 __host__ __device__ constexpr uint32_t decode_levels(uint32_t L) {
     return L > 128 ? 8u : L > 64 ? 7u : L > 32 ? 6u : 5u;
 }
 
-constexpr uint32_t kBucketTab = 1024;   // 64 z values x 16 m values, one byte each
-__host__ __device__ constexpr unsigned __int128 bucket_lo(int w, int z, int m) {
-    // the smallest value whose leading one is bit e = w - 1 - z and whose next
-    // four bits are at least m
-    return (w - 1 - z) >= 4 ? (unsigned __int128)(16 + m) << ((w - 1 - z) - 4)
-                            : ((unsigned __int128)(16 + m) + ((1u << (4 - (w - 1 - z))) - 1)) >> (4 - (w - 1 - z));
+// Buckets of the unranking searches.  A value Q >= 1 falls in the bucket of
+// its float32 conversion's exponent e and top four mantissa bits m, key =
+// 16 e + m: a conversion and a shift (for 64 bits two conversions and an fma
+// of the halves) instead of a leading-zero count, shifts and masks.  The
+// conversions round, by less than 2^-22 of the value, so the values of a
+// bucket lie in [bucket_lo(key), bucket_hi(key)): the exact limits, moved out
+// by 2^-20 where a value can have more bits than a float32 mantissa.  For
+// each Pascal column the host tabulates, per key, the first row whose entry
+// reaches bucket_lo, one byte each, so a search starts there and needs only a
+// few halvings.
+constexpr uint32_t bucket_tab_bytes(int w) { return w == 64 ? 1056u : 544u; }   // keys of w-bit values (rounding
+                                                                                // up reaches e = w), 16-byte rows
+constexpr uint32_t kBucketTab = bucket_tab_bytes(64);   // a column's table in global memory
+constexpr uint32_t kBucketBias = 127u << 4;             // float32's exponent bias in key units
+__host__ __device__ constexpr unsigned __int128 bucket_exact(uint32_t key) {
+    // the smallest whole number of exponent e = key / 16 whose next four bits are at least m = key % 16
+    const uint32_t e = key / 16, m = key % 16;
+    return e >= 4 ? (unsigned __int128)(16 + m) << (e - 4)
+                  : ((unsigned __int128)(16 + m) + ((1u << (4 - e)) - 1)) >> (4 - e);
+}
+__host__ __device__ constexpr unsigned __int128 bucket_lo(uint32_t key) {
+    return bucket_exact(key) - (bucket_exact(key) >> 20);
+}
+__host__ __device__ constexpr unsigned __int128 bucket_hi(uint32_t key) {
+    return bucket_exact(key + 1) + (bucket_exact(key + 1) >> 20);
 }
 constexpr int kMaxLevels = 6;   // cascade checkpoints of the steady loop
 constexpr uint32_t kSearchScanMax = 16384;   // blocks of one search level piece (search_scan_kernel's LDS)
@@ -38,7 +49,7 @@ enum AssignMode : uint32_t { kAssignFixed = 0, kAssignTable = 1, kAssignDigits =
 
 // Rows of the closed form's constant table, per 0-based stage x with
 // e_x = cf_x + cb_x: e_x; e_0 + .. + e_{x-1}; g_x = e_{x-1} + e_x;
-// (n_x - 1) g_x with n_x the stage's pairs (1F1B); cb_x; cb_0 + .. + cb_{x-1}.
+// (n_x + 1) g_x with n_x the stage's pairs (1F1B); cb_x; cb_0 + .. + cb_{x-1}.
 enum ClosedRow : int { kCE = 0, kCSum = 1, kCE2 = 2, kCE2n = 3, kCCb = 4, kCPsi = 5, kCRows = 6 };
 
 // Kernel arguments, passed by value (uniform values land in SGPRs).
@@ -83,9 +94,12 @@ struct KParams {
     uint32_t edge_max;            // largest cf_s + cb_s
     const uint32_t *ctab;         // [kCRows][kSMax] constants of the closed form (ClosedRow)
     uint32_t psi[kSMax];          // cf_0 + ... + cf_{s-1}: undoes the per-stage shift at the end
-    uint8_t fixed_types[kSMax];
-    // candidates of the call
+    uint32_t fixed_word[kSMax / 4];   // kAssignFixed: the stages' (devices') types, one byte each
+    // candidates of the call; range mode: first = first_rank * A + first_asg,
+    // div_magic = floor(2^32 / A) when a call's assignments split in 32 bits (else 0)
     uint64_t first, count;
+    uint64_t first_rank;
+    uint32_t first_asg, div_magic;
     const uint64_t *comp_rank;
     const uint32_t *assign_idx;
     // outputs
@@ -196,6 +210,9 @@ hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 // Problems with a closed form (KParams::closed): the closed-form pass over a
 // chunk, then the recurrence for the candidates it could not prove.
 hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st);
+hipError_t launch_fused(const KParams &p, const LaunchCfg &lc, hipStream_t st);   // decode and closed form
+hipError_t fused_occupancy(const KParams &p, int *blocks);
+constexpr uint32_t kFuseThreads = 512;   // threads of its blocks
 hipError_t launch_full(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 hipError_t launch_bounded(const KParams &p, const LaunchCfg &lc, hipStream_t st, uint32_t publish);
 constexpr int kAListWords = 6;  // words per entry of the early stop's first-stage list

@@ -73,11 +73,12 @@ struct Ent {
     const uint64_t *dig;       // [T^4] packed offsets of four digits (dig_tg > 0)
 };
 
+template <int NT = kBlock>
 __device__ __forceinline__ Ent entry_tables(const KParams &p, unsigned char *smem) {
     uint4 *e = reinterpret_cast<uint4 *>(smem);
     const uint4 *g = reinterpret_cast<const uint4 *>(p.ent);
     const uint32_t n = (p.ent_bytes + 8 * p.dig_tg) / 16;
-    for (uint32_t i = threadIdx.x; i < n; i += kBlock) e[i] = g[i];
+    for (uint32_t i = threadIdx.x; i < n; i += NT) e[i] = g[i];
     if (threadIdx.x == 0 && (p.dig_tg & 1u))   // an odd number of 8-byte digit entries
         reinterpret_cast<uint64_t *>(smem + p.ent_bytes)[p.dig_tg - 1] =
             reinterpret_cast<const uint64_t *>(reinterpret_cast<const unsigned char *>(p.ent) + p.ent_bytes)[p.dig_tg - 1];
@@ -143,7 +144,7 @@ template <int S>
 __device__ __forceinline__ void decode_types(const KParams &p, uint32_t a, uint32_t (&ty)[S]) {
     if (p.assign_mode == kAssignFixed) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) ty[s] = p.fixed_types[s];
+        for (int s = 0; s < S; ++s) ty[s] = (p.fixed_word[s / 4] >> (8 * (s % 4))) & 0xFFu;
     } else if (p.assign_mode == kAssignTable) {
         const uint8_t *row = p.assign + (uint64_t)a * S;
 #pragma unroll
@@ -199,8 +200,7 @@ __device__ __forceinline__ void decode_toff(const KParams &p, const Ent &t, uint
         // invariant values holding scalar registers through the whole kernel
 #pragma unroll
         for (int g = 0; g < (S + 3) / 4; ++g) {
-            uint32_t wd = (uint32_t)p.fixed_types[4 * g] | (uint32_t)p.fixed_types[4 * g + 1] << 8 |
-                          (uint32_t)p.fixed_types[4 * g + 2] << 16 | (uint32_t)p.fixed_types[4 * g + 3] << 24;
+            uint32_t wd = p.fixed_word[g];
             asm volatile("" : "+s"(wd));
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -214,6 +214,25 @@ __device__ __forceinline__ void decode_toff(const KParams &p, const Ent &t, uint
     for (int s = 0; s < S; ++s) to[s] = __umul24(ty[s], p.erow);
 }
 
+// Joint index first + i = rank * A + assignment of candidate i of the call,
+// range mode.  The host gives first = first_rank * A + first_asg; when
+// first_asg plus a call's largest i fits 32 bits the rest is one 32-bit
+// division by A: q = umulhi(v, floor(2^32 / A)) is floor(v / A) or one less.
+// (The 64-bit division it replaces took most of the decode's operations.)
+__device__ __forceinline__ void split_index(const KParams &p, uint32_t i, uint64_t &rank, uint64_t &asg) {
+    if (p.div_magic) {
+        const uint32_t v = p.first_asg + i, A = (uint32_t)p.A;
+        uint32_t q = __umulhi(v, p.div_magic), r = v - q * A;
+        if (r >= A) { q += 1; r -= A; }
+        rank = p.first_rank + q;
+        asg = r;
+    } else {
+        const uint64_t idx = p.first + i;
+        rank = idx / p.A;
+        asg = idx - rank * p.A;
+    }
+}
+
 // Candidate i of the call -> (rank, assignment); false if out of range.
 template <typename R>
 __device__ __forceinline__ bool candidate(const KParams &p, uint64_t i, R &r, uint32_t &a) {
@@ -222,9 +241,8 @@ __device__ __forceinline__ bool candidate(const KParams &p, uint64_t i, R &r, ui
         rank = p.comp_rank[i];
         asg = p.assign_idx ? p.assign_idx[i] : 0u;
     } else {
-        const uint64_t idx = p.first + i;
-        if (p.A == 1) { rank = idx; asg = 0; }
-        else { rank = idx / p.A; asg = idx - rank * p.A; }
+        if (p.A == 1) { rank = p.first + i; asg = 0; }
+        else { split_index(p, (uint32_t)i, rank, asg); }
     }
     const bool ok = rank < p.n_comp && asg < p.A;
     r = ok ? (R)rank : (R)0;
@@ -236,7 +254,9 @@ __device__ __forceinline__ bool candidate(const KParams &p, uint64_t i, R &r, ui
 __device__ __forceinline__ uint32_t assign_of(const KParams &p, uint64_t i) {
     if (p.comp_rank) return p.assign_idx ? p.assign_idx[i] : 0u;
     if (p.A == 1) return 0u;
-    return (uint32_t)((p.first + i) % p.A);
+    uint64_t rank, asg;
+    split_index(p, (uint32_t)i, rank, asg);
+    return (uint32_t)asg;
 }
 
 // ---------------------------------------------------------------------------
@@ -937,6 +957,20 @@ __device__ __forceinline__ unsigned long long wave_min(unsigned long long v) {
     return v;
 }
 
+// Block min of `v` over NT threads, folded into *acc (part: NT / 64 words of LDS).
+template <int NT>
+__device__ __forceinline__ void block_min(unsigned long long v, unsigned long long *acc, unsigned long long *part) {
+    v = wave_min(v);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long m = part[0];
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) m = part[w] < m ? part[w] : m;
+        if (m != ~0ull) atomicMin(acc, m);
+    }
+}
+
 // Block min of `v`, folded into *acc.  When `finalize` is set (the last
 // kernel of an evaluation chunk), the last block of the grid also moves *acc
 // to *result (or folds it in, for the second and later chunks of a call,
@@ -1117,15 +1151,15 @@ __device__ __forceinline__ uint32_t tree_step(uint32_t t, uint32_t probe, uint32
     return t;
 }
 
-// Bucket key of Q >= 1 (its leading zeros, then the 4 bits after its leading one).
+// Bucket key of Q >= 1, plus kBucketBias (a constant of the table's address).
 __device__ __forceinline__ uint32_t bucket_key(uint64_t q) {
-    const uint32_t z = (uint32_t)__clzll(q);
-    return 16u * z + ((uint32_t)((q << z) >> 59) & 15u);
+    float hi, lo;   // (two 32-bit conversions, spelled out: the compiler makes one of 64 bits, three times as long)
+    asm("v_cvt_f32_u32_e32 %0, %1" : "=v"(hi) : "v"((uint32_t)(q >> 32)));
+    asm("v_cvt_f32_u32_e32 %0, %1" : "=v"(lo) : "v"((uint32_t)q));
+    const float f = __fmaf_rn(hi, 4294967296.0f, lo);
+    return __float_as_uint(f) >> 19;
 }
-__device__ __forceinline__ uint32_t bucket_key(uint32_t q) {
-    const uint32_t z = (uint32_t)__clz(q);
-    return 16u * z + (((q << z) >> 27) & 15u);
-}
+__device__ __forceinline__ uint32_t bucket_key(uint32_t q) { return __float_as_uint((float)q) >> 19; }
 
 constexpr uint32_t kBucketPad = 8;   // rows past 2^H: a search reads at most 2^3 - 2 past its start
 constexpr int kBucketStepsMax = 3;
@@ -1146,25 +1180,23 @@ __host__ __device__ constexpr int bucket_steps(int w, int H, int c) {
     }
     const unsigned __int128 top = col[NH - 1];
     int most = 1;
-    for (int z = 0; z < w; ++z)
-        for (int m = 0; m < 16; ++m) {
-            const unsigned __int128 lo = bucket_lo(w, z, m);
-            const unsigned __int128 nx = m < 15 ? bucket_lo(w, z, m + 1) : z > 0 ? bucket_lo(w, z - 1, 0) : vmax + 1;
-            const unsigned __int128 hi = nx < top + 1 ? nx : top + 1;   // the bucket's values a search sees: [lo, hi)
-            if (lo >= hi) continue;
-            int a = 0, b = 0;
-            for (int x = 0; x < 2; ++x) {   // first rows reaching lo and hi - 1
-                const unsigned __int128 t = x == 0 ? lo : hi - 1;
-                int l = 0, r = NH;
-                while (l < r) {
-                    const int mid = (l + r) / 2;
-                    if (col[mid] < t) l = mid + 1;
-                    else r = mid;
-                }
-                (x == 0 ? a : b) = l;
+    for (uint32_t key = 0; key < bucket_tab_bytes(w); ++key) {
+        const unsigned __int128 lo = bucket_lo(key);
+        const unsigned __int128 nx = bucket_hi(key), hi = nx < top + 1 ? nx : top + 1;   // values a search sees: [lo, hi)
+        if (lo >= hi) continue;
+        int a = 0, b = 0;
+        for (int x = 0; x < 2; ++x) {   // first rows reaching lo and hi - 1
+            const unsigned __int128 t = x == 0 ? lo : hi - 1;
+            int l = 0, r = NH;
+            while (l < r) {
+                const int mid = (l + r) / 2;
+                if (col[mid] < t) l = mid + 1;
+                else r = mid;
             }
-            most = b - a + 1 > most ? b - a + 1 : most;
+            (x == 0 ? a : b) = l;
         }
+        most = b - a + 1 > most ? b - a + 1 : most;
+    }
     int h = 0;
     while ((1 << h) < most) ++h;
     return h;
@@ -1198,7 +1230,7 @@ __device__ __forceinline__ void search_cut(const KParams &p, const V *col, const
     for (int u = 0; u < NI; ++u) Q[u] = (V)q[u];
 #pragma unroll
     for (int u = 0; u < NI; ++u) {
-        n0[u] = tab[bucket_key(Q[u])];
+        n0[u] = tab[bucket_key(Q[u]) - kBucketBias];
         t[u] = 0;
     }
     // halving d probes the last row of the left half of rows
@@ -1206,8 +1238,10 @@ __device__ __forceinline__ void search_cut(const KParams &p, const V *col, const
 #pragma unroll
     for (int d = 0; d < HS; ++d) {
 #pragma unroll
-        for (int u = 0; u < NI; ++u)
-            t[u] = tree_step(t[u], col[n0[u] + (t[u] << (HS - d)) + (1u << (HS - 1 - d)) - 1u], Q[u]);
+        for (int u = 0; u < NI; ++u) {
+            const V probe = col[n0[u] + (t[u] << (HS - d)) + (1u << (HS - 1 - d)) - 1u];
+            t[u] = d == 0 ? (uint32_t)(probe < Q[u]) : tree_step(t[u], probe, Q[u]);   // (no register to clear first)
+        }
     }
 #pragma unroll
     for (int u = 0; u < NI; ++u) {
@@ -1230,7 +1264,9 @@ struct Pascal {
     static constexpr int NHI = C1 < NN - 1 ? C1 : NN - 1;    // last narrow column held
     static constexpr int NNC = NHI >= C0 ? NHI - C0 + 1 : 0; // narrow columns held
     static constexpr size_t kWideBytes = (size_t)NWC * NP * sizeof(R), kNarrowBytes = (size_t)NNC * NP * 4;
-    static constexpr size_t bytes() { return kWideBytes + kNarrowBytes + (size_t)(NWC + NNC) * kBucketTab; }
+    // bucket tables: the narrow columns' first, then the wide ones'
+    static constexpr uint32_t kTabN = bucket_tab_bytes(32), kTabW = bucket_tab_bytes(8 * (int)sizeof(R));
+    static constexpr size_t bytes() { return kWideBytes + kNarrowBytes + (size_t)NNC * kTabN + (size_t)NWC * kTabW; }
     const unsigned char *base;
     __device__ __forceinline__ explicit Pascal(const void *b) : base(reinterpret_cast<const unsigned char *>(b)) {}
     template <int c>
@@ -1240,7 +1276,8 @@ struct Pascal {
     }
     template <int c>
     __device__ __forceinline__ const uint8_t *tab() const {
-        return base + kWideBytes + kNarrowBytes + (size_t)(c - C0) * kBucketTab;
+        if constexpr (c >= NN) return base + kWideBytes + kNarrowBytes + (size_t)NNC * kTabN + (size_t)(c - WL) * kTabW;
+        else return base + kWideBytes + kNarrowBytes + (size_t)(c - C0) * kTabN;
     }
     // the search of a cut over column c, for NI candidates
     template <int c, int NI>
@@ -1370,7 +1407,7 @@ __device__ __forceinline__ void decode_batch(const KParams &p, const PC &pc, uin
 // type's largest value (so that the columns stay sorted), then the host's
 // bucket tables of those columns.  Narrow columns saturate at 2^32 - 1 (no
 // value of a column below 5 reaches it for n <= 255).
-template <int S, typename R, int H, int C0 = 2, int C1 = S - 1>
+template <int S, typename R, int H, int C0 = 2, int C1 = S - 1, int NT = kBlock>
 __device__ __forceinline__ void pascal_tables(const KParams &p, void *lds) {
     using PC = Pascal<S, R, H, C0, C1>;
     constexpr uint32_t NH = PC::NH, NP = PC::NP, NC = C1 >= C0 ? (uint32_t)(C1 - C0 + 1) : 0u;
@@ -1378,15 +1415,18 @@ __device__ __forceinline__ void pascal_tables(const KParams &p, void *lds) {
     R *ws = reinterpret_cast<R *>(b);
     uint32_t *ns = reinterpret_cast<uint32_t *>(b + PC::kWideBytes);
     const R *gb = reinterpret_cast<const R *>(p.binom);
-    for (uint32_t e = threadIdx.x; e < NC * NP; e += kBlock) {
+    for (uint32_t e = threadIdx.x; e < NC * NP; e += NT) {
         const uint32_t k = C0 + e / NP, i = e % NP;
         const R v = i < NH ? gb[k * kNB + i] : ~(R)0;
         if ((int)k >= PC::NN) ws[(k - PC::WL) * NP + i] = v;
         else ns[(k - C0) * NP + i] = v > (R)0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)v;
     }
-    const uint4 *gt = reinterpret_cast<const uint4 *>(p.btab + (size_t)C0 * kBucketTab);
     uint4 *lt = reinterpret_cast<uint4 *>(b + PC::kWideBytes + PC::kNarrowBytes);
-    for (uint32_t e = threadIdx.x; e < NC * (kBucketTab / 16); e += kBlock) lt[e] = gt[e];
+    constexpr uint32_t n16 = PC::kTabN / 16, w16 = PC::kTabW / 16;
+    for (uint32_t e = threadIdx.x; e < PC::NNC * n16; e += NT)
+        lt[e] = reinterpret_cast<const uint4 *>(p.btab + (size_t)(C0 + e / n16) * kBucketTab)[e % n16];
+    for (uint32_t e = threadIdx.x; e < PC::NWC * w16; e += NT)
+        lt[PC::NNC * n16 + e] = reinterpret_cast<const uint4 *>(p.btab + (size_t)(PC::WL + e / w16) * kBucketTab)[e % w16];
 }
 
 // LDS bytes of Pascal columns C0 .. C1 with their bucket tables
@@ -1424,9 +1464,8 @@ __device__ __forceinline__ void next_cuts(uint32_t L, uint32_t (&c)[S + 1]) {
 }
 
 template <int S, typename R, int H, typename PC>
-__device__ __forceinline__ void decode_succ(const KParams &p, const PC &pc, uint32_t base, bool &bad) {
-    static_assert(kIlp == 4, "one 16-byte store per code word");
-    constexpr int NW = Codes<S>::kWords;
+__device__ __forceinline__ void decode_succ_words(const KParams &p, const PC &pc, uint32_t base,
+                                                  uint32_t (&w)[kIlp][Codes<S>::kWords], bool &bad) {
     const uint64_t rank0 = p.first + (uint32_t)p.first_i + base;
     R q[1] = {decode_start<R>(p, (R)(rank0 < p.n_comp ? rank0 : 0))};
     uint32_t c[S + 1];
@@ -1439,7 +1478,6 @@ __device__ __forceinline__ void decode_succ(const KParams &p, const PC &pc, uint
         c[j] = cj[0];
     });
     if (S >= 2) c[S - 1] = p.L - (uint32_t)q[0];
-    uint32_t w[kIlp][NW];
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
         if (u > 0) next_cuts<S>(p.L, c);
@@ -1448,6 +1486,14 @@ __device__ __forceinline__ void decode_succ(const KParams &p, const PC &pc, uint
         bad |= act && !ok;
         pack_cuts<S>(c, ok, w[u]);
     }
+}
+
+template <int S, typename R, int H, typename PC>
+__device__ __forceinline__ void decode_succ(const KParams &p, const PC &pc, uint32_t base, bool &bad) {
+    static_assert(kIlp == 4, "one 16-byte store per code word");
+    constexpr int NW = Codes<S>::kWords;
+    uint32_t w[kIlp][NW];
+    decode_succ_words<S, R, H>(p, pc, base, w, bad);
     const uint32_t ccap = (uint32_t)p.ccap;
 #pragma unroll
     for (int k = 0; k < NW; ++k)
@@ -1496,6 +1542,33 @@ __device__ __forceinline__ void write_outputs(const KParams &p, uint32_t gi, boo
         const uint32_t w0 = (gi - (threadIdx.x & 63)) >> 5, nwords = (uint32_t)p.nwords;
         if ((threadIdx.x & 63) == 0 && w0 < nwords) __builtin_nontemporal_store((uint32_t)bits, p.feas_bits_out + w0);
         if ((threadIdx.x & 63) == 32 && w0 + 1 < nwords) __builtin_nontemporal_store((uint32_t)(bits >> 32), p.feas_bits_out + w0 + 1);
+    }
+}
+
+// The same for a wave whose lanes hold kIlp consecutive candidates each
+// (256 in all, from base = lane * kIlp on; gi their position in the call):
+// makespans as one 16-byte store where the caller's array allows it, and the
+// lanes' four feasibility bits joined to words of eight lanes.
+__device__ __forceinline__ void write_quad(const KParams &p, uint32_t gi, uint32_t base, uint32_t n_i,
+                                           const uint32_t (&T)[kIlp], uint32_t nib) {
+    static_assert(kIlp == 4, "one 16-byte store");
+    if (p.makespan_out) {
+        uint32_t *o = p.makespan_out + gi;
+        if (((uint64_t)(uintptr_t)p.makespan_out & 15u) == 0 && base + kIlp <= n_i) {   // (gi is a multiple of 4)
+            typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+            __builtin_nontemporal_store((v4){T[0], T[1], T[2], T[3]}, reinterpret_cast<v4 *>(o));
+        } else {
+#pragma unroll
+            for (int u = 0; u < kIlp; ++u)
+                if (base + u < n_i) __builtin_nontemporal_store(T[u], o + u);
+        }
+    }
+    if (p.feas_bits_out) {
+        uint32_t v = nib << (4 * (threadIdx.x & 7));
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) v |= __shfl_xor(v, o, 64);
+        const uint32_t word = gi >> 5;
+        if ((threadIdx.x & 7) == 0 && word < (uint32_t)p.nwords && base < n_i) __builtin_nontemporal_store(v, p.feas_bits_out + word);
     }
 }
 
@@ -1563,63 +1636,171 @@ struct FullList {
         : pos(p.flist), w(p.flist + p.ccap), asg(p.flist + (1 + Codes<S>::kWords) * p.ccap) {}
 };
 
-// (a2)-(a4), (a6) for the chunk: stage weights from the cut codes, memory
-// check, and the closed-form makespan (poseidon_closed.h).  Lanes whose value
-// is not proven go to the list that full_kernel evaluates by the recurrence.
-// VALU-bound: about 31 operations a stage, against 37 a stage for every one
-// of the recurrence's steady iterations (at least S of them before its first
-// settle check).  2^24 candidates of 16 stages: 0.35 ms (and 0.05 ms for the
-// list) against 1.09 ms and 0.51 ms for the recurrence and its later
-// checkpoints; Eager 1F1B 0.35 against 3.42 ms; 2^26 of 8 stages 0.76 ms
-// (0.07) against 1.42 ms (0.65).
-template <int S, bool AR, bool SCH, bool U24>
-__device__ __forceinline__ unsigned long long closed_all(const KParams &p, const Ent &tab, unsigned int &nq) {
-    constexpr int NW = Codes<S>::kWords;
-    unsigned long long best = ~0ull;
-    // 32-bit positions and word offsets, as in eval_kernel
-    const uint32_t stride = gridDim.x * kBlock, n_i = (uint32_t)p.n_i, ccap = (uint32_t)p.ccap;
-    const uint32_t first_i = (uint32_t)p.first_i, seg = blockIdx.x * (uint32_t)p.seg_cap;
-    const uint32_t span = (n_i + stride - 1) / stride;
-    uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    for (uint32_t it = 0; it < span; ++it, i += stride) {
-        const bool active = i < n_i;
-        const uint32_t gi = first_i + i;
-        uint32_t w[NW];
-#pragma unroll
-        for (int k = 0; k < NW; ++k) w[k] = active ? p.codes[k * ccap + i] : 0u;
-        uint32_t cut[S + 1], to[S], F[S], B[S], D[S], T;
-        const bool ok = unpack_cuts<S>(w, p.L, cut);
-        const uint32_t a = ok ? assign_of(p, gi) : 0u;
-        decode_toff<S>(p, tab, a, to);
-        const bool feas = stage_weights<S>(p, tab, cut, to, F, B) && ok && active;
-        if (AR) stage_allreduce<S>(p, tab, cut, to, D);
-        const bool proven = closed_form<S, SCH, AR, U24>(p, F, B, D, T) || !ok;
-        if (!ok) T = 0xFFFFFFFFu;
-        const bool write = active && proven;
-        const unsigned long long m = __ballot(active && !proven);
-        if (m) {
-            const unsigned int lane = threadIdx.x & 63;
-            unsigned int base = 0;
-            if (lane == 0) base = atomicAdd(&nq, (unsigned int)__popcll(m));
-            base = __shfl(base, 0, 64);
-            if (active && !proven) {
-                const uint32_t slot = seg + base + __popcll(lane ? (m & ((1ull << lane) - 1ull)) : 0ull);
-                const FullList<S> l(p);
-                l.pos[slot] = gi;
-#pragma unroll
-                for (int k = 0; k < NW; ++k) l.w[k * ccap + slot] = w[k];
-                l.asg[slot] = a;
-            }
-        }
-        write_outputs(p, gi, write, T, feas);
-        if (write) {
-            const unsigned long long key = make_key(feas, T, gi);
-            best = key < best ? key : best;
-        }
-    }
-    return best;
+// The kernel's arguments (its only parameter, at the start of the kernarg
+// segment) through a pointer the compiler cannot see through: fields read
+// through it are scalar loads at the point of use.  Read the plain way they
+// are loop invariants, some 100 of them in fused_kernel, that are loaded once
+// and then spilled into vector lanes (a VALU operation per reload).
+__device__ __forceinline__ const KParams &fresh_args() {
+    uint64_t a = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(a));
+    return *(const KParams *)reinterpret_cast<const __attribute__((address_space(4))) KParams *>(a);
 }
 
+// One candidate per lane of a wave from its cut codes w (all zero: invalid),
+// assignment a and position gi: stage weights, memory check, closed-form
+// makespan (poseidon_closed.h).  Lanes whose value is not proven go to the
+// block's segment of the list that full_kernel evaluates by the recurrence.
+// Returns whether T is the candidate's makespan; all lanes call it.
+template <int S, bool AR, bool SCH, bool U24>
+__device__ __forceinline__ bool closed_one(const KParams &p, const Ent &tab, uint32_t seg, unsigned int *nq,
+                                           bool active, uint32_t gi, uint32_t a,
+                                           const uint32_t (&w)[Codes<S>::kWords], uint32_t &T, bool &feas) {
+    constexpr int NW = Codes<S>::kWords;
+    uint32_t cut[S + 1], to[S], F[S], B[S], D[S];
+    const bool ok = unpack_cuts<S>(w, p.L, cut);
+    decode_toff<S>(p, tab, a, to);
+    feas = stage_weights<S>(p, tab, cut, to, F, B) && ok && active;
+    if (AR) stage_allreduce<S>(p, tab, cut, to, D);
+    const bool proven = closed_form<S, SCH, AR, U24>(p, F, B, D, T) || !ok;
+    if (!ok) T = 0xFFFFFFFFu;
+    const unsigned long long m = __ballot(active && !proven);
+    if (m) {
+        const unsigned int lane = threadIdx.x & 63;
+        unsigned int base = 0;
+        if (lane == 0) base = atomicAdd(nq, (unsigned int)__popcll(m));
+        base = __shfl(base, 0, 64);
+        if (active && !proven) {
+            const uint32_t slot = seg + base + __popcll(lane ? (m & ((1ull << lane) - 1ull)) : 0ull);
+            const FullList<S> l(p);
+            l.pos[slot] = gi;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) l.w[k * (uint32_t)p.ccap + slot] = w[k];
+            l.asg[slot] = a;
+        }
+    }
+    return active && proven;
+}
+
+// (a1)-(a4), (a6) for the chunk in one pass: every lane unranks kIlp
+// candidates together (the decode's LDS chains overlap) and takes the closed
+// form of one after the other from their packed cuts, which never leave its
+// registers.  VALU-bound (79-89 % issue): about 26 operations a stage for
+// the weights and the closed form and 15 a search, against 5 a stage for
+// every one of the recurrence's steady iterations, at least S of them.
+// 2^24 candidates of 16 stages: 401 us (decode 161 and closed form 346 as
+// two kernels; decode 159 and the recurrence 1091 + 510 before); 2^26 of 8
+// stages 776 us (297 + 761; 307 + 1415 + 653); the exhaustive 8-stage range
+// 599 us (131 + 593; 133 + 1175 + 416).
+// LDS: the Pascal columns at offset 0 (a compile-time size), then the stage
+// entries at a constant offset (it folds into the loads' immediates; static
+// __shared__ variables would move both), then a few words.  The columns have
+// 2^7 or 2^8 rows: the shorter forms of the decode kernel save little here.
+// 512 threads share one copy of the tables.
+constexpr int kFuseBlock = (int)kFuseThreads;
+constexpr size_t kFuseTail = 128;   // wave minima, list counter
+__host__ __device__ constexpr uint32_t fuse_levels(uint32_t L) { return L > 128 ? 8u : 7u; }
+
+template <int S, typename R, bool AR, bool SCH, int H>
+__device__ __forceinline__ void fused_all(const KParams &p, unsigned char *smem) {
+    using PC = Pascal<S, R, H>;
+    constexpr int NW = Codes<S>::kWords, NT = kFuseBlock;
+    static_assert(PC::bytes() % 16 == 0, "entries follow the columns at 16 bytes");
+    pascal_tables<S, R, H, 2, S - 1, NT>(p, smem);
+    unsigned char *tail = smem + PC::bytes() + p.ent_lds;
+    unsigned long long *part = reinterpret_cast<unsigned long long *>(tail);
+    unsigned int *nq = reinterpret_cast<unsigned int *>(tail + NT / 64 * 8);
+    if (threadIdx.x == 0) *nq = 0;
+    const Ent tab = entry_tables<NT>(p, smem + PC::bytes());   // (its barrier publishes all of it)
+    const PC pc(smem);
+    const uint32_t n_i = (uint32_t)p.n_i, first_i = (uint32_t)p.first_i, lane = threadIdx.x & 63;
+    const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap;
+    unsigned long long best = ~0ull;
+    bool bad = false;
+    if (!p.comp_rank && p.A == 1) {
+        // consecutive ranks: a lane takes kIlp of them, the first unranked,
+        // the others by the lexicographic successor
+        const uint32_t stride = gridDim.x * NT * kIlp;
+        for (uint32_t wb = (blockIdx.x * NT + (threadIdx.x - lane)) * kIlp; wb < n_i; wb += stride) {   // (wave-uniform)
+            const uint32_t base = wb + lane * kIlp;
+            uint32_t w[kIlp][NW];
+            decode_succ_words<S, R, H>(fresh_args(), pc, base, w, bad);
+            uint32_t Tq[kIlp], nib = 0;
+#pragma unroll
+            for (int u = 0; u < kIlp; ++u) Tq[u] = 0;
+#pragma unroll 1
+            for (uint32_t u = 0; u < (uint32_t)kIlp; ++u) {
+                uint32_t T;
+                bool feas;
+                const bool done = closed_one<S, AR, SCH, true>(fresh_args(), tab, seg, nq, base + u < n_i, first_i + base + u, 0u, w[0], T, feas);
+                // (an unproven lane's value is overwritten by full_kernel, which runs after this one)
+                nib |= (feas ? 1u : 0u) << u;
+                if (done) {
+                    const unsigned long long key = make_key(feas, T, first_i + base + u);
+                    best = key < best ? key : best;
+                }
+                // the next candidate's words, and the values in order (no dynamic register index)
+#pragma unroll
+                for (int v = 0; v + 1 < kIlp; ++v) {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) w[v][k] = w[v + 1][k];
+                    Tq[v] = Tq[v + 1];
+                }
+                Tq[kIlp - 1] = T;
+            }
+            write_quad(fresh_args(), first_i + base, base, n_i, Tq, nib);
+        }
+    } else {
+        const uint32_t stride = gridDim.x * NT;
+        for (uint32_t wb = blockIdx.x * NT + (threadIdx.x - lane); wb < n_i; wb += kIlp * stride) {   // (wave-uniform)
+            bool act[kIlp], ok[kIlp];
+            uint32_t asg[kIlp], w[kIlp][NW];
+            decode_ilp<S, R, H>(fresh_args(), pc, wb + lane, stride, act, ok, asg, w);
+#pragma unroll
+            for (int u = 0; u < kIlp; ++u) bad |= act[u] && !ok[u];
+#pragma unroll 1
+            for (uint32_t u = 0; u < (uint32_t)kIlp; ++u) {
+                const uint32_t i = wb + u * stride + lane;
+                if (wb + u * stride >= n_i) break;   // (wave-uniform)
+                uint32_t T;
+                bool feas;
+                const KParams &q = fresh_args();
+                const bool write = closed_one<S, AR, SCH, true>(q, tab, seg, nq, i < n_i, first_i + i, asg[0], w[0], T, feas);
+                write_outputs(q, first_i + i, write, T, feas);
+                if (write) {
+                    const unsigned long long key = make_key(feas, T, first_i + i);
+                    best = key < best ? key : best;
+                }
+#pragma unroll
+                for (int v = 0; v + 1 < kIlp; ++v) {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) w[v][k] = w[v + 1][k];
+                    asg[v] = asg[v + 1];
+                }
+            }
+        }
+    }
+    if (bad) atomicOr(p.err, 1u);
+    __syncthreads();
+    if (threadIdx.x == 0) p.fcount[blockIdx.x] = *nq;
+    block_min<NT>(best, p.acc, part);
+}
+
+// (128 VGPRs: two blocks of eight waves a CU at S = 16)
+template <int S, typename R, bool AR, bool SCH>
+__global__ __launch_bounds__(kFuseBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void fused_kernel(KParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (fuse_levels(p.L) == 8) fused_all<S, R, AR, SCH, 8>(p, smem);
+    else fused_all<S, R, AR, SCH, 7>(p, smem);
+}
+
+template <int S, typename R>
+__host__ __device__ constexpr size_t fused_lds(uint32_t L, size_t ent_lds) {
+    return (fuse_levels(L) == 8 ? Pascal<S, R, 8>::bytes() : Pascal<S, R, 7>::bytes()) + ent_lds + kFuseTail;
+}
+
+// The closed form from the decode kernel's cut codes, for stage weights above
+// 24 bits (32-bit products).
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void closed_kernel(KParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1627,7 +1808,26 @@ __global__ __launch_bounds__(kBlock) void closed_kernel(KParams p) {
     __shared__ unsigned int nq;
     if (threadIdx.x == 0) nq = 0;
     __syncthreads();
-    const unsigned long long best = p.g24 ? closed_all<S, AR, SCH, true>(p, tab, nq) : closed_all<S, AR, SCH, false>(p, tab, nq);
+    constexpr int NW = Codes<S>::kWords;
+    unsigned long long best = ~0ull;
+    // 32-bit positions and word offsets, as in eval_kernel
+    const uint32_t stride = gridDim.x * kBlock, n_i = (uint32_t)p.n_i, ccap = (uint32_t)p.ccap;
+    const uint32_t first_i = (uint32_t)p.first_i, seg = blockIdx.x * (uint32_t)p.seg_cap, lane = threadIdx.x & 63;
+    for (uint32_t wb = blockIdx.x * kBlock + (threadIdx.x - lane); wb < n_i; wb += stride) {   // (wave-uniform)
+        const uint32_t i = wb + lane, gi = first_i + i;
+        const bool active = i < n_i;
+        uint32_t w[NW], T;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = active ? p.codes[k * ccap + i] : 0u;
+        bool feas;
+        const uint32_t a = (w[0] & 0xFFu) ? assign_of(p, gi) : 0u;
+        const bool write = closed_one<S, AR, SCH, false>(p, tab, seg, &nq, active, gi, a, w, T, feas);
+        write_outputs(p, gi, write, T, feas);
+        if (write) {
+            const unsigned long long key = make_key(feas, T, gi);
+            best = key < best ? key : best;
+        }
+    }
     __syncthreads();
     if (threadIdx.x == 0) p.fcount[blockIdx.x] = nq;
     block_min_and_finish(best, p.acc, p.done, p.result, nullptr, false);
@@ -1837,7 +2037,7 @@ __device__ __forceinline__ void stage1_limits(const KParams &p, const Ent &tab, 
 // Type of stage 1 of assignment a (valid a).
 template <int S>
 __device__ __forceinline__ uint32_t first_stage_type(const KParams &p, uint32_t a) {
-    if (p.assign_mode == kAssignFixed) return p.fixed_types[0];
+    if (p.assign_mode == kAssignFixed) return p.fixed_word[0] & 0xFFu;
     if (p.assign_mode == kAssignTable) return p.assign[(uint64_t)a * S];
     // the top base-T digit: floor(a / T^(S-1)), from a multiply-high that
     // gives it or one more
@@ -2287,6 +2487,7 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
 }
 
 constexpr size_t kLdsBlockMax = 64 * 1024;   // LDS bytes one block of these kernels may use
+constexpr size_t kLdsCu = 160 * 1024;          // (fused_kernel: all a CU has)
 
 // host-side launchers
 // ---------------------------------------------------------------------------
@@ -2323,6 +2524,28 @@ hipError_t launch_closed_s(const KParams &p, const LaunchCfg &lc, hipStream_t st
         hipLaunchKernelGGL((closed_kernel<S, decltype(ar)::value, decltype(sch)::value>), dim3(lc.grid), dim3(kBlock),
                            lc.lds_bytes, st, p);
         return hipGetLastError();
+    });
+}
+
+template <int S, typename R>
+hipError_t launch_fused_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    const size_t lds = fused_lds<S, R>(p.L, p.ent_lds);
+    return with_variant(p, [&](auto ar, auto sch) {
+        hipLaunchKernelGGL((fused_kernel<S, R, decltype(ar)::value, decltype(sch)::value>), dim3(lc.grid),
+                           dim3(kFuseBlock), lds, st, p);
+        return hipGetLastError();
+    });
+}
+
+// Resident blocks per CU of fused_kernel (0: its tables exceed a CU's LDS).
+template <int S, typename R>
+hipError_t fused_occupancy_s(const KParams &p, int *blocks) {
+    const size_t lds = fused_lds<S, R>(p.L, p.ent_lds);
+    *blocks = 0;
+    if (lds > kLdsCu) return hipSuccess;
+    return with_variant(p, [&](auto ar, auto sch) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fused_kernel<S, R, decltype(ar)::value, decltype(sch)::value>,
+                                                            kFuseBlock, lds);
     });
 }
 
