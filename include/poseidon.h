@@ -263,8 +263,8 @@ int poseidon_argmin(poseidon_ctx *ctx, const uint32_t *makespan, const uint32_t 
  * best_out and stats_out are HOST pointers (either may be NULL); the call
  * synchronises the stream wherever it reads a level's size back (levels
  * that may need more than one frontier piece) and at its end.  The frontier
- * memory, 4 Mi partial configurations per stage of (6 + 4 ceil((S-1)/4))
- * bytes each (1.5 GB at S = 16), is allocated on the first call and kept by
+ * memory, 4 Mi partial configurations of (6 + 4 ceil((S-1)/4)) bytes for each
+ * of S-2 stages (1.3 GB at S = 16), is allocated on the first call and kept by
  * the context.  The work grows with the pruned tree, which for many stages
  * and a loose bound can be very large (Sec. 4.2.3). */
 enum {

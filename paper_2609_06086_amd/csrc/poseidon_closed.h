@@ -156,14 +156,15 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
 #pragma unroll
         for (int x = 0; x < S; ++x) {
             const uint32_t r = F[x] + B[x];
-            K[x] = (P[x] + cc.at<kCE2n>(x) >= Tm) | (r + cc.at<kCE2>(x) >= rm);
+            // (bitwise throughout: no branch per stage)
+            K[x] = (int)(P[x] + cc.at<kCE2n>(x) >= Tm) | (int)(r + cc.at<kCE2>(x) >= rm);
             low = min(low, K[x] ? r : 0xFFFFFFFFu);
         }
         bool ok = true;
 #pragma unroll
         for (int x = 0; x < S; ++x) {
-            ok &= K[x] | (F[x] + B[x] + cc.at<kCE2>(x) <= low);
-            if (x > 0) ok &= !(K[x] & K[x > 0 ? x - 1 : 0]);
+            ok &= (bool)((int)K[x] | (int)(F[x] + B[x] + cc.at<kCE2>(x) <= low));
+            if (x > 0) ok &= !((int)K[x] & (int)K[x > 0 ? x - 1 : 0]);
         }
         return ok;
     }

@@ -1279,23 +1279,33 @@ struct SearchWs {
     unsigned int *tot[pk::kSMax];
     unsigned long long *off[pk::kSMax];
     uint16_t *node[pk::kSMax];
+    unsigned long long *slot_key;
+    uint32_t *slot_row, *slot_w;
     unsigned long long *words;
 };
 
-// Per level: rows, cut codes, block counts and offsets; then the state words.
+// Levels of nodes a search stores: 0 .. S-3, and 0 for S <= 2 (the last pass
+// expands level S-3, or S-2, to complete configurations in place).
+uint32_t search_levels(const poseidon_ctx *ctx) { return ctx->S > 2 ? ctx->S - 2 : 1; }
+
+// Per level: rows, cut codes, block counts and offsets; then the last pass's
+// slots and the state words.
 SearchWs search_layout(poseidon_ctx *ctx, size_t *bytes) {
     SearchWs w;
     memset(&w, 0, sizeof(w));
     const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
     unsigned char *b = (unsigned char *)ctx->sws;
     size_t o = 0;
-    for (uint32_t l = 0; l < ctx->S; ++l) {
+    for (uint32_t l = 0; l < search_levels(ctx); ++l) {
         w.row[l] = (uint32_t *)(b + o); o += kSearchCap * 4;
         w.codes[l] = (uint32_t *)(b + o); o += words * kSearchCap * 4;
         w.tot[l] = (unsigned int *)(b + o); o += (size_t)kSearchBlk * 4;
         w.node[l] = (uint16_t *)(b + o); o += kSearchCap * 2;
         w.off[l] = (unsigned long long *)(b + o); o += ((size_t)kSearchBlk + 1) * 8;
     }
+    w.slot_key = (unsigned long long *)(b + o); o += pk::kSlotMax * 8;
+    w.slot_row = (uint32_t *)(b + o); o += pk::kSlotMax * 4;
+    w.slot_w = (uint32_t *)(b + o); o += words * pk::kSlotMax * 4;
     w.words = (unsigned long long *)(b + o); o += SW_COUNT * 8;
     if (bytes) *bytes = o;
     return w;
@@ -1318,14 +1328,6 @@ int search_read_total(SearchRun &r, uint32_t x, unsigned long long *total) {
     return POSEIDON_OK;
 }
 
-// The level before the one that fixes the last cut (x = S - 3) is expanded
-// together with it when one block's grandchildren, at most 256 (L - 1)^2,
-// always fit a frontier piece.
-bool search_fused(const poseidon_ctx *ctx, uint32_t x) {
-    const uint64_t L = ctx->L;
-    return ctx->S >= 3 && x + 3 == ctx->S && 256 * (L - 1) * (L - 1) <= kSearchCap;
-}
-
 // Expand the nodes at level x (stored in the level's arrays) depth first:
 // n of them, or, with n_dev, at most n, their number being on the device.
 // When every child of the level fits one frontier piece (n times the most
@@ -1343,35 +1345,33 @@ int search_expand(SearchRun &r, uint32_t x, uint64_t n, const unsigned long long
     q.level = x;
     const uint32_t grid = (uint32_t)((n + 255) / 256);
     const size_t lds = r.ctx->lds_bytes;
-    // the count and write kernels add three per-type tables (fb, mfb, hm)
-    const size_t lds_cw = lds + 3 * (size_t)r.ctx->T * (r.ctx->L + 1) * 4;
-    if (x + 1 == S) {
-        // (S > 1: a grid that strides over the piece and takes the stage
-        // entries; a lone stage is tested there too, one candidate a thread)
-        const uint32_t lgrid = S > 1 ? std::min(grid, r.ctx->grid_max) : grid;
-        if (pk::launch_search(pk::kSearchOpLeaf, r.kp, q, lgrid, S > 1 ? r.ctx->ent_lds_bytes : lds, r.st) != hipSuccess ||
-            pk::launch_search(pk::kSearchOpMerge, r.kp, q, 1, 0, r.st) != hipSuccess)
-            return POSEIDON_E_DEVICE;
+    // the count kernel adds three per-type tables (fb, mfb, hm), the last pass the stage entries behind them
+    const size_t tabs = 3 * (size_t)r.ctx->T * (r.ctx->L + 1) * 4;
+    if (x + 1 == search_levels(r.ctx)) {
+        // (S > 1: a grid that strides over the piece; a lone stage takes one candidate a thread)
+        const uint32_t lgrid = S > 1 ? std::min(grid, std::min(r.ctx->grid_max, pk::kSlotMax)) : grid;
+        const size_t llds = S > 1 ? lds + ((tabs + 15) & ~(size_t)15) + r.ctx->ent_lds_bytes : lds;
+        if (pk::launch_search(pk::kSearchOpLast, r.kp, q, lgrid, llds, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
+        q.n_in = lgrid;   // (the merge's slots)
+        if (pk::launch_search(pk::kSearchOpMerge, r.kp, q, 1, 0, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
         return POSEIDON_OK;
     }
+    const size_t lds_cw = lds + tabs;
     q.blk_tot = r.w.tot[x];
     q.blk_off = r.w.off[x];
     q.node_cnt = r.w.node[x];
-    // a fused step writes level x + 2 (complete configurations when x = S - 3)
-    const uint32_t step = search_fused(r.ctx, x) ? 2 : 1;
-    q.fused = step == 2;
-    q.out_row = r.w.row[x + step];
-    q.out_codes = r.w.codes[x + step];
+    q.out_row = r.w.row[x + 1];
+    q.out_codes = r.w.codes[x + 1];
     q.out_cap = kSearchCap;
     q.total = r.w.words + SW_TOTAL + x;
     if (pk::launch_search(pk::kSearchOpCount, r.kp, q, grid, lds_cw, r.st) != hipSuccess ||
         pk::launch_search_scan(q, grid, r.st) != hipSuccess)
         return POSEIDON_E_DEVICE;
-    const uint64_t most = step == 2 ? (uint64_t)(r.ctx->L - 1) * (r.ctx->L - 1) : r.ctx->L - 1;
+    const uint64_t most = r.ctx->L - 1;
     if (n * most <= kSearchCap) {
         q.blk_base = 0;
-        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, grid, lds_cw, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
-        return search_expand(r, x + step, n * most, q.total);
+        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, grid, 0, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
+        return search_expand(r, x + 1, n * most, q.total);
     }
     unsigned long long total = 0;
     int rc = search_read_total(r, x, &total);
@@ -1379,12 +1379,11 @@ int search_expand(SearchRun &r, uint32_t x, uint64_t n, const unsigned long long
     if (total == 0) return POSEIDON_OK;
     if (total <= kSearchCap) {
         q.blk_base = 0;
-        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, grid, lds_cw, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
-        return search_expand(r, x + step, total, nullptr);
+        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, grid, 0, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
+        return search_expand(r, x + 1, total, nullptr);
     }
     // more children than a level holds: write and expand them in pieces of
-    // whole blocks (one block has at most 256 (L - 1) < kSearchCap children,
-    // or 256 (L - 1)^2 <= kSearchCap when fused)
+    // whole blocks (one block has at most 256 (L - 1) < kSearchCap children)
     // (into the pinned words, grid + 1 <= kSearchBlk + 1 of them; the pieces'
     // own expansions reuse those words, so the offsets are copied out first)
     if (hipMemcpyAsync(r.ctx->shost, q.blk_off, (grid + 1) * 8, hipMemcpyDeviceToHost, r.st) != hipSuccess ||
@@ -1396,9 +1395,9 @@ int search_expand(SearchRun &r, uint32_t x, uint64_t n, const unsigned long long
         uint32_t b1 = b0 + 1;
         while (b1 < grid && off[b1 + 1] - off[b0] <= kSearchCap) ++b1;
         q.blk_base = b0;
-        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, b1 - b0, lds_cw, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
+        if (pk::launch_search(pk::kSearchOpWrite, r.kp, q, b1 - b0, 0, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
         if (off[b1] > off[b0]) {
-            rc = search_expand(r, x + step, off[b1] - off[b0], nullptr);
+            rc = search_expand(r, x + 1, off[b1] - off[b0], nullptr);
             if (rc != POSEIDON_OK) return rc;
         }
         b0 = b1;
@@ -1445,6 +1444,9 @@ extern "C" int poseidon_search(poseidon_ctx *ctx, uint64_t first_row, uint64_t n
     r.q.stats_part = r.w.words + SW_PART;
     r.q.acc = r.w.words + SW_ACC;
     r.q.best = r.w.words + SW_BEST;
+    r.q.slot_key = r.w.slot_key;
+    r.q.slot_row = r.w.slot_row;
+    r.q.slot_w = r.w.slot_w;
     r.q.bound = (uint32_t *)(r.w.words + SW_BOUND);
     if (pk::launch_fill(r.q.stats, 5, 0ull, st) != hipSuccess ||
         pk::launch_fill(r.q.stats_part, 5 * pk::kStatSlots, 0ull, st) != hipSuccess ||

@@ -174,18 +174,21 @@ struct SearchParams {
     uint16_t *node_cnt;               // children each node keeps (count kernel -> write kernel)
     uint32_t blk_base;                // first block a write launch covers
     uint32_t flags;                   // kSearchRidge | kSearchNoStage
-    uint32_t fused;                   // level S-3 expanded together with the level that fixes the last cut
     uint32_t *bound;                  // the current chunk's bound
     unsigned long long *stats;        // visited, evaluated, pruned by memory / ridge / bound
     unsigned long long *stats_part;   // [5][kStatSlots] the same counters from the count kernels:
                                       // block b adds to slot b % kStatSlots (the host sums them)
-    unsigned long long *acc;          // best (T << 32 | position) of a leaf piece
+    unsigned long long *acc;          // best (T << 32 | node) of a piece of the last pass
+    unsigned long long *slot_key;     // [kSlotMax] its blocks' bests, with the configuration that has each
+    uint32_t *slot_row, *slot_w;      // [kSlotMax], [words][kSlotMax]
     unsigned long long *best;         // makespan, row, composition rank of the best so far
     unsigned long long *total;        // children of the scanned level piece (one word per level)
     uint32_t root_first;              // first row of a root piece
 };
 
-enum SearchOp { kSearchOpCount = 0, kSearchOpWrite = 1, kSearchOpLeaf = 2, kSearchOpMerge = 3, kSearchOpRoot = 4 };
+constexpr uint32_t kSlotMax = 2048;   // blocks of the last pass
+
+enum SearchOp { kSearchOpCount = 0, kSearchOpWrite = 1, kSearchOpLast = 2, kSearchOpMerge = 3, kSearchOpRoot = 4 };
 
 // Stage entries of the evaluation kernels: per device type a block of
 // field rows of kEntRow uint32 (end points 0..L <= 256, padded), so that a

@@ -176,6 +176,11 @@ __device__ __forceinline__ uint32_t search_tab_offset(const KParams &p) {
     return (n * 8 + (p.L + 1) * 4 + p.T * 4 + (p.has_ar ? n * 4 : 0) + 15) & ~15u;
 }
 
+// where search_last_kernel's stage entries start, behind the search tables
+__device__ __forceinline__ uint32_t search_ent_offset(const KParams &p) {
+    return search_tab_offset(p) + ((3 * p.T * (p.L + 1) * 4 + 15) & ~15u);
+}
+
 __device__ __forceinline__ SearchTab search_tables(const KParams &p, const Lds &tab, unsigned char *smem) {
     const uint32_t row = p.L + 1, n = p.T * row;
     uint32_t *fb = reinterpret_cast<uint32_t *>(smem + search_tab_offset(p)), *mfb = fb + n, *hm = mfb + n;
@@ -280,8 +285,10 @@ __device__ __forceinline__ uint32_t search_accepted(const KParams &p, const Lds 
 // Children lo+1 .. lo+k of a node at the level that fixes the last cut
 // (x + 2 == S): each fixes every cut, so the last stage [hi, L) is tested
 // here (memory in closed form through last_lo, then ridge, then Eq. 2) and
-// only children that pass it are kept; lp counts the outcomes.  With WRITE
-// the kept children go to positions base, base + 1, ... in order.
+// only children that pass it are kept; lp counts the outcomes.
+// search_last_range gives the kept ones as a range [g0, h1] (its return
+// value is their number) where the closed form below applies; elsewhere
+// search_last_test tries one end point.
 //
 // Without all-reduce times the last stage's Eq. 2 splits into a per-node
 // constant and a function of hi alone:
@@ -304,107 +311,101 @@ __device__ __forceinline__ void search_write_child(const SearchParams &q, uint64
     }
 }
 
-template <int S, bool AR, bool WRITE, bool MONO>
-__device__ __forceinline__ uint32_t search_last_children(const KParams &p, const Lds &tab, const SearchTab &sx,
-                                                         const SearchNode &n, uint32_t x, uint32_t k, uint32_t flags,
-                                                         uint32_t bound,
-                                                         LastStage &lp, const SearchParams &q, uint64_t base,
-                                                         const uint32_t (&w)[Codes<S>::kWords]) {
-    const uint32_t row_len = p.L + 1;
-    // the last stage [hi, L) exceeds its cap exactly for hi < last_lo[type]
-    const uint32_t mem_lo = p.last_lo[n.tS];
-    const uint32_t h0 = max(n.lo + 1, mem_lo), h1 = n.lo + k;
+// the end points memory allows: hi < last_lo[type] exceeds the last stage's cap
+__device__ __forceinline__ void search_last_limits(const KParams &p, const SearchNode &n, uint32_t k, LastStage &lp,
+                                                   uint32_t &h0, uint32_t &h1) {
+    h0 = max(n.lo + 1, p.last_lo[n.tS]);
+    h1 = n.lo + k;
     lp.mem += (h0 <= h1 ? h0 : h1 + 1) - (n.lo + 1);
+}
+
+__device__ __forceinline__ uint32_t search_last_range(const KParams &p, const SearchTab &sx, const SearchNode &n,
+                                                      uint32_t x, uint32_t h0, uint32_t h1, uint32_t flags,
+                                                      uint32_t bound, LastStage &lp, uint32_t &g0out) {
+    const uint32_t row_len = p.L + 1;
     const bool ridge = (flags & kSearchRidge) != 0, stage = !(flags & kSearchNoStage);
     const bool same = n.t == n.tS;
-    if (!AR && (MONO || ((p.g_mono >> (8 * n.t + n.tS)) & 1ull))) {
-        if (h0 > h1) return 0;
-        // ridge: the end points below r0 fail
-        uint32_t r0 = h0;
-        if (ridge) {
-            if (same) {
-                // counts of type t fall before lo + last_lS (or throughout), and the
-                // last stage is then longer than stage S-1 below ceil((L + lo) / 2)
-                const uint32_t e1 = (p.L + n.lo + 1) / 2;
-                const uint32_t e2 = n.fallingS ? 0xFFFFFFFFu : (n.last_lS >= 0 ? n.lo + (uint32_t)n.last_lS : 0u);
-                r0 = max(h0, min(e1, e2));
-            } else if (n.last_lS >= 0 && n.fallingS) {
-                r0 = max(h0, p.L - (uint32_t)n.last_lS);
-            }
-            r0 = min(r0, h1 + 1);
-            lp.ridge += r0 - h0;
+    if (h0 > h1) return 0;
+    // ridge: the end points below r0 fail
+    uint32_t r0 = h0;
+    if (ridge) {
+        if (same) {
+            // counts of type t fall before lo + last_lS (or throughout), and the
+            // last stage is then longer than stage S-1 below ceil((L + lo) / 2)
+            const uint32_t e1 = (p.L + n.lo + 1) / 2;
+            const uint32_t e2 = n.fallingS ? 0xFFFFFFFFu : (n.last_lS >= 0 ? n.lo + (uint32_t)n.last_lS : 0u);
+            r0 = max(h0, min(e1, e2));
+        } else if (n.last_lS >= 0 && n.fallingS) {
+            r0 = max(h0, p.L - (uint32_t)n.last_lS);
         }
-        // Eq. 2: the end points below g0 fail
-        uint32_t g0 = r0;
-        if (stage && r0 <= h1) {
-            const uint32_t *ft = sx.fb + n.t * row_len, *ms = sx.mfb + n.tS * row_len;
-            // g(hi) = C + G(hi), G(hi) = fb_t[hi] - mfb_tS[hi].  g is an Eq. 2
-            // value, below 2^31 like every path weight (checked at load), so
-            // C + G evaluates exactly in 32-bit modular arithmetic
-            const uint32_t C = n.pre_f - ft[n.lo] + (x == 0 ? 0u : n.inner + n.last_b) + ms[p.L];
-            const uint32_t len = h1 + 1 - r0;
-            // g is smallest at h1: if even that fails, every end point does
-            // (the usual case, so the search below mostly runs on no lane)
-            uint32_t j = len;
-            if (C + ft[h1] - ms[h1] <= bound) {
-                const int H = (int)decode_levels(p.L);
-                j = 0;
+        r0 = min(r0, h1 + 1);
+        lp.ridge += r0 - h0;
+    }
+    // Eq. 2: the end points below g0 fail
+    uint32_t g0 = r0;
+    if (stage && r0 <= h1) {
+        const uint32_t *ft = sx.fb + n.t * row_len, *ms = sx.mfb + n.tS * row_len;
+        // g(hi) = C + G(hi), G(hi) = fb_t[hi] - mfb_tS[hi].  g is an Eq. 2
+        // value, below 2^31 like every path weight (checked at load), so
+        // C + G evaluates exactly in 32-bit modular arithmetic
+        const uint32_t C = n.pre_f - ft[n.lo] + (x == 0 ? 0u : n.inner + n.last_b) + ms[p.L];
+        const uint32_t len = h1 + 1 - r0;
+        // g is smallest at h1: if even that fails, every end point does
+        // (the usual case, so the search below mostly runs on no lane)
+        uint32_t j = len;
+        if (C + ft[h1] - ms[h1] <= bound) {
+            const int H = (int)decode_levels(p.L);
+            j = 0;
 #pragma unroll
-                for (int b = 7; b >= 0; --b) {
-                    if (b >= H) continue;
-                    const uint32_t t = j + (1u << b);
-                    const uint32_t h = r0 + min(t, len) - 1;
-                    j = ((t <= len) & (C + ft[h] - ms[h] > bound)) ? t : j;
-                }
+            for (int b = 7; b >= 0; --b) {
+                if (b >= H) continue;
+                const uint32_t t = j + (1u << b);
+                const uint32_t h = r0 + min(t, len) - 1;
+                j = ((t <= len) & (C + ft[h] - ms[h] > bound)) ? t : j;
             }
-            g0 = r0 + j;
-            lp.bound += j;
         }
-        lp.pass += h1 + 1 - g0;
-        if (WRITE) {
-            for (uint32_t hi = g0; hi <= h1; ++hi) search_write_child<S>(q, base + (hi - g0), n.row, x, hi, w);
-        }
-        return h1 + 1 - g0;
+        g0 = r0 + j;
+        lp.bound += j;
     }
-    const uint64_t *ct = tab.cost + n.t * row_len, *cs = tab.cost + n.tS * row_len;
-    const uint64_t cl = ct[n.lo], cL = cs[p.L];
-    const uint32_t *pdt = tab.pd + n.t * row_len, *pds = tab.pd + n.tS * row_len;
-    const uint32_t dl = AR ? pdt[n.lo] : 0u, dL = AR ? pds[p.L] : 0u;
-    const uint32_t carry = n.inner + n.last_b;
-    uint32_t out = 0;
-    for (uint32_t hi = h0; hi <= h1; ++hi) {
-        if (ridge) {
-            // type tS's counts with stage x+1 appended when it has that type
-            const int32_t l = (int32_t)(hi - n.lo);
-            int32_t ll = n.last_lS;
-            bool fall = n.fallingS;
-            if (same) {
-                fall = fall || (ll >= 0 && l < ll);
-                ll = l;
-            }
-            if (ll >= 0 && fall && (int32_t)(p.L - hi) > ll) {
-                lp.ridge += 1;
-                continue;
-            }
+    lp.pass += h1 + 1 - g0;
+    g0out = g0;
+    return h1 + 1 - g0;
+}
+
+template <bool AR>
+__device__ __forceinline__ bool search_last_test(const KParams &p, const Lds &tab, const SearchNode &n, uint32_t x,
+                                                 uint32_t hi, uint32_t flags, uint32_t bound, LastStage &lp) {
+    const uint32_t row_len = p.L + 1;
+    if (flags & kSearchRidge) {
+        // type tS's counts with stage x+1 appended when it has that type
+        const int32_t l = (int32_t)(hi - n.lo);
+        int32_t ll = n.last_lS;
+        bool fall = n.fallingS;
+        if (n.t == n.tS) {
+            fall = fall || (ll >= 0 && l < ll);
+            ll = l;
         }
-        if (stage) {
-            const uint64_t ch = ct[hi], sh = cs[hi];
-            const uint32_t f = (uint32_t)ch - (uint32_t)cl, b = (uint32_t)(ch >> 32) - (uint32_t)(cl >> 32);
-            const uint32_t d = AR ? pdt[hi] - dl : 0u;
-            const uint32_t inn = x == 0 ? d : max(carry, d);
-            const uint32_t fS = (uint32_t)cL - (uint32_t)sh, bS = (uint32_t)(cL >> 32) - (uint32_t)(sh >> 32);
-            const uint32_t dS = AR ? dL - pds[hi] : 0u;
-            // Eq. 2 for the last stage: g(S_S) = sum_{i<S} F_i + M (F_S + B_S) + max(inner + B_{S-1}, d_S)
-            if (n.pre_f + f + p.M * (fS + bS) + max(inn + b, dS) > bound) {
-                lp.bound += 1;
-                continue;
-            }
+        if (ll >= 0 && fall && (int32_t)(p.L - hi) > ll) {
+            lp.ridge += 1;
+            return false;
         }
-        lp.pass += 1;
-        if (WRITE) search_write_child<S>(q, base + out, n.row, x, hi, w);
-        ++out;
     }
-    return out;
+    if (!(flags & kSearchNoStage)) {
+        const uint64_t *ct = tab.cost + n.t * row_len, *cs = tab.cost + n.tS * row_len;
+        const uint64_t cl = ct[n.lo], cL = cs[p.L], ch = ct[hi], sh = cs[hi];
+        const uint32_t f = (uint32_t)ch - (uint32_t)cl, b = (uint32_t)(ch >> 32) - (uint32_t)(cl >> 32);
+        const uint32_t d = AR ? tab.pd[n.t * row_len + hi] - tab.pd[n.t * row_len + n.lo] : 0u;
+        const uint32_t inn = x == 0 ? d : max(n.inner + n.last_b, d);
+        const uint32_t fS = (uint32_t)cL - (uint32_t)sh, bS = (uint32_t)(cL >> 32) - (uint32_t)(sh >> 32);
+        const uint32_t dS = AR ? tab.pd[n.tS * row_len + p.L] - tab.pd[n.tS * row_len + hi] : 0u;
+        // Eq. 2 for the last stage: g(S_S) = sum_{i<S} F_i + M (F_S + B_S) + max(inner + B_{S-1}, d_S)
+        if (n.pre_f + f + p.M * (fS + bS) + max(inn + b, dS) > bound) {
+            lp.bound += 1;
+            return false;
+        }
+    }
+    lp.pass += 1;
+    return true;
 }
 
 __device__ __forceinline__ void search_flush(const SearchParams &q, unsigned int visited, unsigned int evaluated,
@@ -456,7 +457,7 @@ __device__ __forceinline__ uint32_t search_n_in(const SearchParams &q) {
 // kernel waits on chains of dependent LDS loads (binary searches), so it
 // asks for 7 waves per SIMD (72 VGPRs, no spills for any S) rather than the
 // compiler's choice of 6.
-template <int S, bool AR, bool MONO>
+template <int S, bool AR>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) void search_count_kernel(KParams p, SearchParams q) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t n_in = search_n_in(q);
@@ -472,56 +473,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) 
     const uint32_t bound = *q.bound;
     uint32_t row, w[Codes<S>::kWords], ty[S], cut[S + 1];
     search_load<S>(q, i, active, row, w);
-    uint32_t cnt = 0, visited = 0;
-    LastStage lp;
-    uint32_t why_mem = 0, why_ridge = 0, why_bound = 0;
+    uint32_t cnt = 0, why_mem = 0, why_ridge = 0, why_bound = 0;
     if (active) {
         const uint32_t x = q.level;
         const SearchNode n = search_node<S, AR>(p, tab, row, w, x, ty, cut);
         const uint32_t hmax = p.L - (S - 1 - x);   // every later stage keeps one layer
-        const uint32_t acc = search_accepted<AR>(p, tab, sx, n, x, hmax, q.flags, bound);
+        cnt = search_accepted<AR>(p, tab, sx, n, x, hmax, q.flags, bound);
         // the rule that stopped the range (0: it ran to its structural end)
-        const int why = search_stop<AR>(p, tab, sx, n, x, acc, hmax, q.flags, bound);
-        visited = acc;
+        const int why = search_stop<AR>(p, tab, sx, n, x, cnt, hmax, q.flags, bound);
         why_mem = why == 1;
         why_ridge = why == 2;
         why_bound = why == 3;
-        if (q.fused) {
-            // x + 3 == S: each child fixes stage S-2 and is expanded here at
-            // once; its children fix the last cut, and those that pass the last
-            // stage are kept (complete configurations)
-            for (uint32_t c = n.lo + 1; c <= n.lo + acc; ++c) {
-                const SearchNode m = search_child<AR>(p, tab, n, x, c);
-                const uint32_t acc2 = search_accepted<AR>(p, tab, sx, m, x + 1, p.L - 1, q.flags, bound);
-                const int why2 = search_stop<AR>(p, tab, sx, m, x + 1, acc2, p.L - 1, q.flags, bound);
-                visited += acc2;
-                why_mem += why2 == 1;
-                why_ridge += why2 == 2;
-                why_bound += why2 == 3;
-                cnt += search_last_children<S, AR, false, MONO>(p, tab, sx, m, x + 1, acc2, q.flags, bound, lp, q, 0, w);
-            }
-        } else {
-            cnt = x + 2 == (uint32_t)S ? search_last_children<S, AR, false, MONO>(p, tab, sx, n, x, acc, q.flags, bound, lp, q, 0, w)
-                                       : acc;
-        }
-        q.node_cnt[i] = (uint16_t)cnt;   // at most (L - 1)^2 < 2^16 children (fused), else L - 1
+        q.node_cnt[i] = (uint16_t)cnt;   // at most L - 1 children
     }
     __shared__ unsigned int tot;
     if (threadIdx.x == 0) tot = 0;
     __syncthreads();
     const unsigned int wsum = (unsigned int)wave_sum_u32(cnt);
     if ((threadIdx.x & 63) == 0 && wsum) atomicAdd(&tot, wsum);
-    // a child that completes the configuration and passes the last stage
-    // counts as visited twice (its stage x+1 and its stage S) and evaluated.
-    search_block_counts(q, visited + lp.pass, lp.pass, why_mem + lp.mem, why_ridge + lp.ridge, why_bound + lp.bound);
+    search_block_counts(q, cnt, 0, why_mem, why_ridge, why_bound);
     if (threadIdx.x == 0) q.blk_tot[blockIdx.x] = tot;
 }
 
 // Write the children of blocks [blk_base, blk_base + gridDim.x) in node
 // order, the first one at position 0 of the output.
-template <int S, bool AR, bool MONO>
+template <int S>
 __global__ __launch_bounds__(kBlock) void search_write_kernel(KParams p, SearchParams q) {
-    extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t blk = q.blk_base + blockIdx.x;
     const uint32_t n_in = search_n_in(q);
     if (blk * kBlock >= n_in) return;   // past the level's nodes
@@ -529,171 +506,355 @@ __global__ __launch_bounds__(kBlock) void search_write_kernel(KParams p, SearchP
     const uint32_t i = blk * kBlock + threadIdx.x;
     const bool active = i < n_in;
     const uint32_t x = q.level;
-    // the count kernel left each node's number of children: nodes without
-    // any (most of them at the level that fixes the last cut) do nothing
+    // the count kernel left each node's number of children
     const uint32_t cnt = active ? q.node_cnt[i] : 0u;
     unsigned long long total;
     const unsigned long long local = block_exclusive_scan_u64(cnt, total);
-    if (total == 0) return;   // no child in the block (most blocks of the last-cut level)
+    if (total == 0) return;   // no child in the block
     const uint64_t blk0 = q.blk_off[blk] - q.blk_off[q.blk_base];
-    if (!q.fused && x + 2 != (uint32_t)S) {
-        // every accepted choice is a child: c_{x+1} = lo+1 .. lo+cnt.  The
-        // wave writes the children of its nodes together, 64 consecutive ones
-        // per store: lane j takes child o0 + j of the wave's run, and its
-        // parent is the first lane whose inclusive count exceeds that
-        // (a binary search over the lanes)
-        uint32_t row, w[NW];
-        search_load<S>(q, i, active, row, w);
-        uint32_t lo = 0;
+    // every accepted choice is a child: c_{x+1} = lo+1 .. lo+cnt.  The
+    // wave writes the children of its nodes together, 64 consecutive ones
+    // per store: lane j takes child o0 + j of the wave's run, and its
+    // parent is the first lane whose inclusive count exceeds that
+    // (a binary search over the lanes)
+    uint32_t row, w[NW];
+    search_load<S>(q, i, active, row, w);
+    uint32_t lo = 0;
 #pragma unroll
-        for (int s = 1; s < S; ++s)
-            if ((uint32_t)s == x) lo = (w[(s - 1) >> 2] >> (8 * ((s - 1) & 3))) & 0xFFu;
-        const uint32_t lane = threadIdx.x & 63;
-        const unsigned long long l0 = __shfl(local, 0, 64);
-        const uint32_t incl = (uint32_t)(local - l0) + cnt;
-        const uint32_t wtot = __shfl(incl, 63, 64);
-        for (uint32_t o0 = 0; o0 < wtot; o0 += 64) {
-            const uint32_t o = o0 + lane;
-            uint32_t pl = 0;
+    for (int s = 1; s < S; ++s)
+        if ((uint32_t)s == x) lo = (w[(s - 1) >> 2] >> (8 * ((s - 1) & 3))) & 0xFFu;
+    const uint32_t lane = threadIdx.x & 63;
+    const unsigned long long l0 = __shfl(local, 0, 64);
+    const uint32_t incl = (uint32_t)(local - l0) + cnt;
+    const uint32_t wtot = __shfl(incl, 63, 64);
+    for (uint32_t o0 = 0; o0 < wtot; o0 += 64) {
+        const uint32_t o = o0 + lane;
+        uint32_t pl = 0;
 #pragma unroll
-            for (uint32_t b = 32; b; b >>= 1) pl = __shfl(incl, (int)(pl + b - 1), 64) <= o ? pl + b : pl;
-            const uint32_t first = __shfl(incl - cnt, (int)pl, 64);
-            const uint32_t prow = __shfl(row, (int)pl, 64), plo = __shfl(lo, (int)pl, 64);
-            uint32_t pw[NW];
+        for (uint32_t b = 32; b; b >>= 1) pl = __shfl(incl, (int)(pl + b - 1), 64) <= o ? pl + b : pl;
+        const uint32_t first = __shfl(incl - cnt, (int)pl, 64);
+        const uint32_t prow = __shfl(row, (int)pl, 64), plo = __shfl(lo, (int)pl, 64);
+        uint32_t pw[NW];
 #pragma unroll
-            for (int k = 0; k < NW; ++k) pw[k] = __shfl(w[k], (int)pl, 64);
-            if (o < wtot) search_write_child<S>(q, blk0 + l0 + o, prow, x, plo + 1 + (o - first), pw);
-        }
-        return;
-    }
-    const Lds tab = stage_tables(p, smem);
-    const SearchTab sx = search_tables(p, tab, smem);
-    const uint32_t bound = *q.bound;
-    if (cnt) {
-        uint32_t row, w[NW], ty[S], cut[S + 1];
-        search_load<S>(q, i, true, row, w);
-        const uint64_t base = blk0 + local;
-        if (q.fused) {
-            // the complete configurations under each child, child by child
-            LastStage lp;
-            const SearchNode n = search_node<S, AR>(p, tab, row, w, x, ty, cut);
-            const uint32_t acc = search_accepted<AR>(p, tab, sx, n, x, p.L - (S - 1 - x), q.flags, bound);
-            uint64_t o = base;
-            for (uint32_t c = n.lo + 1; c <= n.lo + acc; ++c) {
-                const SearchNode m = search_child<AR>(p, tab, n, x, c);
-                const uint32_t acc2 = search_accepted<AR>(p, tab, sx, m, x + 1, p.L - 1, q.flags, bound);
-                uint32_t wc[NW];
-#pragma unroll
-                for (int k = 0; k < NW; ++k) wc[k] = (uint32_t)k == (x >> 2) ? (w[k] | (c << (8 * (x & 3)))) : w[k];
-                o += search_last_children<S, AR, true, MONO>(p, tab, sx, m, x + 1, acc2, q.flags, bound, lp, q, o, wc);
-            }
-        } else {   // x + 2 == S
-            LastStage lp;
-            const SearchNode n = search_node<S, AR>(p, tab, row, w, x, ty, cut);
-            const uint32_t acc = search_accepted<AR>(p, tab, sx, n, x, p.L - (S - 1 - x), q.flags, bound);
-            search_last_children<S, AR, true, MONO>(p, tab, sx, n, x, acc, q.flags, bound, lp, q, base, w);
-        }
+        for (int k = 0; k < NW; ++k) pw[k] = __shfl(w[k], (int)pl, 64);
+        if (o < wtot) search_write_child<S>(q, blk0 + l0 + o, prow, x, plo + 1 + (o - first), pw);
     }
 }
 
-// Complete configurations (level S-1; for S > 1 the level that fixed the
-// last cut already tested the last stage, for S = 1 it is tested here):
-// their makespans, closed form first.  Reduces (T << 32 | position) over the
-// candidates with T <= bound into *q.acc.  The grid strides over the piece;
-// almost every candidate ends with its closed form (2^22 of 8 stages: 225 us
-// with the recurrence for each).
-template <int S, bool AR, bool SCH>
-__global__ __launch_bounds__(kBlock) void search_leaf_kernel(KParams p, SearchParams q) {
+// The last levels in one pass: the nodes of level S-3 (S >= 3), or S-2
+// (S = 2), are expanded through the level that fixes the last cut, and the
+// complete configurations that pass the last stage are evaluated at once, so
+// the widest level is neither written nor read, needs no frontier memory and
+// no host round trip per piece of it.  Each lane expands one node; the kept
+// end points of one choice of stage S-1 are a run [hi0, hi0 + cnt), and the
+// wave's runs gather in LDS until it hands them out, 64 configurations at a
+// time whichever node they come from.  Most configurations end with their
+// closed form; see Pend for the others.  Ties go to the first in search
+// order: (node, end point of stage S-2's choice, last cut).
+// (Before: a count and a scan of those nodes, then some 90 write launches of
+// 110 us, 90-170 blocks wide each, and as many leaf launches of 42 us; the
+// 8-stage search with 3.8e8 complete configurations took 33.9 ms, now 16.)
+// Held to 128 VGPRs for S <= 8: 299 us a launch against 355 us at the 130 the
+// compiler takes (3 waves a SIMD) and 424 us at 96 (spills).
+constexpr uint32_t kRunCap = 192;   // runs a wave gathers: handed out from 128 on
+template <int S>
+struct LastPend {
+    uint32_t row[128], node[128], low[128], w[Codes<S>::kWords][128];
+};
+template <int S>
+struct LastLds {
+    uint32_t run[kWaves][kRunCap];
+    LastPend<S> pend[kWaves];
+    unsigned long long known;
+    unsigned long long key[kWaves];
+    uint32_t sub[kWaves], row[kWaves], w[kWaves][Codes<S>::kWords];
+};
+
+template <int S, bool AR, bool MONO, bool SCH>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ? 4 : 3, 8))) void search_last_kernel(KParams p, SearchParams q) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t n_in = search_n_in(q);
-    if (blockIdx.x * kBlock >= n_in) return;   // past the level's nodes
+    if (blockIdx.x * kBlock >= n_in) {   // past the level's nodes
+        if (threadIdx.x == 0) q.slot_key[blockIdx.x] = ~0ull;
+        return;
+    }
     constexpr int NW = Codes<S>::kWords;
-    const uint32_t bound = *q.bound;
-    if constexpr (S == 1) {
-        const Lds tab = stage_tables(p, smem);
-        const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-        uint32_t row, w[NW], ty[S], cut[S + 1];
-        search_load<S>(q, i, i < n_in, row, w);
-        int why = 4;
-        unsigned long long key = ~0ull;
-        if (i < n_in) {
-            const SearchNode n = search_node<S, AR>(p, tab, row, w, S - 1, ty, cut);
-            why = search_try<AR>(p, tab, n, S - 1, p.L, q.flags, bound);
-            if (why == 0) {
-                uint32_t F[S], B[S];
-                stage_weights<S>(p, tab, cut, ty, F, B);
-                const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, load_comm<S>(p), w, row);
-                if (T <= bound) key = ((unsigned long long)T << 32) | i;
-            }
-        }
-        search_flush(q, why == 0, why == 0, why == 1, why == 2, why == 3);
-        block_min_and_finish(key, q.acc, nullptr, nullptr, nullptr, false);
-    } else {
-        __shared__ PendLds pend;
-        // a makespan above the bound or not below the best of the earlier
-        // pieces never becomes the result
-        const unsigned long long had = q.best[0];
-        if (had == 0) return;
-        const uint32_t most = had <= bound ? (uint32_t)had - 1u : bound;
-        Pend l = pend_init(pend, (unsigned long long)most << 32 | 0xFFFFFFFFu);
-        const Ent tab = entry_tables(p, smem);   // (its barrier publishes pend)
-        const Comm<S> comm = load_comm<S>(p);
-        auto full = [&](uint32_t i) {
-            uint32_t row, w[NW], cut[S + 1], to[S], F[S], B[S];
-            search_load<S>(q, i, true, row, w);
+    constexpr uint32_t x = S >= 3 ? S - 3 : 0;   // the nodes' level
+    __shared__ LastLds<S> sh;
+    const Lds tab = stage_tables(p, smem);
+    const SearchTab sx = search_tables(p, tab, smem);
+    const Ent ent_tab = entry_tables(p, smem + search_ent_offset(p));
+    const Comm<S> comm = load_comm<S>(p);
+    const uint32_t bound = *q.bound, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long lanes_below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    // a makespan above the bound or not below the best of the earlier pieces
+    // never becomes the result
+    const unsigned long long had = q.best[0];
+    const uint32_t most = had <= bound ? (had ? (uint32_t)had - 1u : 0u) : bound;
+    if (threadIdx.x == 0) sh.known = (unsigned long long)most << 32 | 0xFFFFFFFFu;
+    __syncthreads();
+    uint32_t *run = sh.run[wave];
+    LastPend<S> &pend = sh.pend[wave];
+    uint32_t nrun = 0, npend = 0;   // (wave-uniform)
+    // the thread's best: (T << 32 | node), then the two cuts, then what names it
+    unsigned long long best = ~0ull;
+    uint32_t bsub = 0, brow = 0, bw[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) bw[k] = 0;
+    auto sub_of = [](const uint32_t (&w)[NW]) __attribute__((always_inline)) {   // the cuts the pass fixed, the first most significant
+        uint32_t v = 0;
+#pragma unroll
+        for (int j = (S >= 3 ? S - 2 : 1); j <= S - 1; ++j) v = v << 8 | ((w[(j - 1) / 4] >> (8 * ((j - 1) % 4))) & 0xFFu);
+        return v;
+    };
+    auto offer = [&](uint32_t T, uint32_t node, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
+        const unsigned long long key = make_key(true, T, node);
+        if (key > best) return;
+        const uint32_t sub = sub_of(w);
+        if (key == best && sub >= bsub) return;
+        best = key;
+        bsub = sub;
+        brow = row;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) bw[k] = w[k];
+        if (key < sh.known) atomicMin(&sh.known, key);
+    };
+    auto run_pend = [&](uint32_t first, uint32_t n) __attribute__((always_inline)) {   // the recurrence for n <= 64 kept entries
+        wave_lds_sync();
+        if (lane < n && (unsigned long long)pend.low[first + lane] << 32 <= sh.known) {
+            const uint32_t e = first + lane, row = pend.row[e];
+            uint32_t w[NW], cut[S + 1], to[S], F[S], B[S];
+#pragma unroll
+            for (int k = 0; k < NW; ++k) w[k] = pend.w[k][e];
             unpack_cuts<S>(w, p.L, cut);
-            decode_toff<S>(p, tab, row, to);
-            stage_weights<S>(p, tab, cut, to, F, B);
-            const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, row);
-            return make_key(true, T, i);
-        };
-        unsigned long long best = ~0ull;
-        const uint32_t lane = threadIdx.x & 63;
-        for (uint32_t i0 = blockIdx.x * kBlock + (threadIdx.x - lane); i0 < n_in; i0 += gridDim.x * kBlock) {   // (wave-uniform)
-            const uint32_t i = i0 + lane;
-            uint32_t T = 0;
-            bool proven = false;
-            if (i < n_in) {
-                uint32_t row, w[NW], cut[S + 1], to[S], F[S], B[S];
-                search_load<S>(q, i, true, row, w);
-                unpack_cuts<S>(w, p.L, cut);
-                decode_toff<S>(p, tab, row, to);
-                stage_weights<S>(p, tab, cut, to, F, B);
-                proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
-            }
-            pend_add(l, i < n_in, proven, i, T, i, best, full);
+            decode_toff<S>(p, ent_tab, row, to);
+            stage_weights<S>(p, ent_tab, cut, to, F, B);
+            offer(dp_full_settle<S, SCH, AR>(p, ent_tab, F, B, comm, w, row), pend.node[e], row, w);
         }
-        best = pend_finish(l, best, q.acc, full);
-        block_min_and_finish((uint32_t)(best >> 32) <= bound ? best : ~0ull, q.acc, nullptr, nullptr, nullptr, false);
+        wave_lds_sync();
+    };
+    // hand out the gathered runs (row, w: the lanes' nodes base + lane)
+    auto hand_out = [&](uint32_t base, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
+        wave_lds_sync();
+        for (uint32_t r0 = 0; r0 < nrun; r0 += 64) {
+            const uint32_t rw = r0 + lane < nrun ? run[r0 + lane] : 0u, cnt = rw >> 22;
+            uint32_t incl = cnt;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t u = __shfl_up(incl, o, 64);
+                if (lane >= (uint32_t)o) incl += u;
+            }
+            const uint32_t total = __shfl(incl, 63, 64);
+            for (uint32_t o0 = 0; o0 < total; o0 += 64) {
+                const uint32_t o = o0 + lane;
+                uint32_t pl = 0;   // the run that holds configuration o: the first whose inclusive count exceeds it
+#pragma unroll
+                for (uint32_t b = 32; b; b >>= 1) pl = __shfl(incl, (int)(pl + b - 1), 64) <= o ? pl + b : pl;
+                const bool on = o < total;
+                pl = on ? pl : 0u;
+                const uint32_t rp = __shfl(rw, (int)pl, 64), first = __shfl(incl - cnt, (int)pl, 64);
+                const uint32_t src = rp & 63u, hi = ((rp >> 14) & 0xFFu) + (on ? o - first : 0u);
+                const uint32_t prow = __shfl(row, (int)src, 64);
+                uint32_t pw[NW];
+#pragma unroll
+                for (int k = 0; k < NW; ++k) pw[k] = __shfl(w[k], (int)src, 64);
+                if constexpr (S >= 3) {
+                    pw[x / 4] |= ((rp >> 6) & 0xFFu) << (8 * (x % 4));
+                    pw[(x + 1) / 4] |= hi << (8 * ((x + 1) % 4));
+                } else {
+                    pw[0] |= hi;
+                }
+                uint32_t cut[S + 1], to[S], F[S], B[S], T;
+                unpack_cuts<S>(pw, p.L, cut);
+                decode_toff<S>(p, ent_tab, prow, to);
+                stage_weights<S>(p, ent_tab, cut, to, F, B);
+                const bool proven = closed_or_bound<S, AR, SCH>(p, ent_tab, cut, to, F, B, T);
+                if (on && proven && T <= bound) offer(T, base + src, prow, pw);
+                const bool keep = on && !proven && (unsigned long long)T << 32 <= sh.known;
+                const unsigned long long m = __ballot(keep);
+                if (m) {
+                    if (keep) {
+                        const uint32_t e = npend + (uint32_t)__popcll(m & lanes_below);
+                        pend.row[e] = prow;
+                        pend.node[e] = base + src;
+                        pend.low[e] = T;
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) pend.w[k][e] = pw[k];
+                    }
+                    npend += (uint32_t)__popcll(m);
+                    if (npend >= 64) {
+                        npend -= 64;
+                        run_pend(npend, 64u);
+                    }
+                }
+            }
+        }
+        nrun = 0;
+        wave_lds_sync();
+    };
+    uint32_t visited = 0, why_mem = 0, why_ridge = 0, why_bound = 0;
+    LastStage lp;
+    for (uint32_t base = blockIdx.x * kBlock + wave * 64; base < n_in; base += gridDim.x * kBlock) {   // (wave-uniform)
+        const uint32_t i = base + lane;
+        const bool active = i < n_in;
+        uint32_t row, w[NW], ty[S], cut[S + 1];
+        search_load<S>(q, i, active, row, w);
+        const SearchNode n = search_node<S, AR>(p, tab, row, w, x, ty, cut);
+        auto add_run = [&](bool want, uint32_t c, uint32_t hi0, uint32_t cnt) __attribute__((always_inline)) {
+            const unsigned long long m = __ballot(want);
+            if (m == 0) return;
+            if (want) run[nrun + (uint32_t)__popcll(m & lanes_below)] = lane | c << 6 | hi0 << 14 | cnt << 22;
+            nrun += (uint32_t)__popcll(m);
+        };
+        // the kept children of a node at the level that fixes the last cut, as runs
+        auto last_children = [&](bool on, const SearchNode &m, uint32_t lx, uint32_t acc, uint32_t c) __attribute__((always_inline)) {
+            uint32_t h0 = 1, h1 = 0;
+            if (on) search_last_limits(p, m, acc, lp, h0, h1);
+            bool range = !AR;
+            if (!AR && !MONO) range = (p.g_mono >> (8 * m.t + m.tS)) & 1ull;
+            uint32_t g0 = 0, cnt = 0;
+            if (on && range) cnt = search_last_range(p, sx, m, lx, h0, h1, q.flags, bound, lp, g0);
+            add_run(cnt != 0, c, g0, cnt);
+            if constexpr (AR || !MONO) {
+                for (uint32_t hi = h0; __ballot(on && !range && hi <= h1); ++hi) {
+                    const bool t = on && !range && hi <= h1;
+                    if (nrun > kRunCap - 64) hand_out(base, row, w);
+                    add_run(t && search_last_test<AR>(p, tab, m, lx, hi, q.flags, bound, lp), c, hi, 1u);
+                }
+            }
+        };
+        const uint32_t hmax = p.L - (S - 1 - x);   // every later stage keeps one layer
+        const uint32_t acc = active ? search_accepted<AR>(p, tab, sx, n, x, hmax, q.flags, bound) : 0u;
+        // the rule that stopped the range (0: it ran to its structural end)
+        const int why = active ? search_stop<AR>(p, tab, sx, n, x, acc, hmax, q.flags, bound) : 0;
+        visited += acc;
+        why_mem += why == 1;
+        why_ridge += why == 2;
+        why_bound += why == 3;
+        // (the runs are handed out when the next choice's might not fit, and
+        // at the end, before the lanes move on to other nodes)
+        for (uint32_t k = 1;; ++k) {
+            const bool more = S >= 3 ? __ballot(k <= acc) != 0 : k == 1;
+            if (more) {
+                if constexpr (S >= 3) {
+                    const bool on = k <= acc;
+                    const uint32_t c = n.lo + (on ? k : 0u);
+                    SearchNode m = n;
+                    uint32_t acc2 = 0;
+                    if (on) {
+                        m = search_child<AR>(p, tab, n, x, c);
+                        acc2 = search_accepted<AR>(p, tab, sx, m, x + 1, p.L - 1, q.flags, bound);
+                        const int why2 = search_stop<AR>(p, tab, sx, m, x + 1, acc2, p.L - 1, q.flags, bound);
+                        visited += acc2;
+                        why_mem += why2 == 1;
+                        why_ridge += why2 == 2;
+                        why_bound += why2 == 3;
+                    }
+                    last_children(on, m, x + 1, acc2, c);
+                } else {
+                    last_children(active, n, x, acc, 0u);
+                }
+            }
+            if (!more || nrun > kRunCap - 64) hand_out(base, row, w);
+            if (!more) break;
+        }
+    }
+    // what the lists still hold, against the best of the block and the piece
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMin(&sh.known, __hip_atomic_load(q.acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    __syncthreads();
+    run_pend(0u, npend);
+    // a makespan from the recurrence can lie above the bound
+    if ((uint32_t)(best >> 32) > bound) best = ~0ull;
+    // a configuration that passes the last stage counts as visited twice (its
+    // stages S-1 and S) and evaluated
+    search_block_counts(q, visited + lp.pass, lp.pass, why_mem + lp.mem, why_ridge + lp.ridge, why_bound + lp.bound);
+    // the block's best, with the configuration that has it (nodes are not
+    // shared between waves, so only lanes of one wave can tie on the key)
+    const unsigned long long wbest = wave_min(best);
+    uint32_t s = best == wbest ? bsub : 0xFFFFFFFFu;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) s = min(s, (uint32_t)__shfl_xor((int)s, o, 64));
+    const unsigned long long win = __ballot(best == wbest && bsub == s);
+    if (lane == (uint32_t)__ffsll((long long)win) - 1u) {
+        sh.key[wave] = wbest;
+        sh.row[wave] = brow;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) sh.w[wave][k] = bw[k];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int v = 0;
+#pragma unroll
+        for (int k = 1; k < kWaves; ++k) v = sh.key[k] < sh.key[v] ? k : v;
+        q.slot_key[blockIdx.x] = sh.key[v];
+        q.slot_row[blockIdx.x] = sh.row[v];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) q.slot_w[k * kSlotMax + blockIdx.x] = sh.w[v][k];
+        if (sh.key[v] != ~0ull) atomicMin(q.acc, sh.key[v]);
     }
 }
 
-// After a leaf piece: the piece's best candidate replaces the best so far
-// only if strictly better (earlier pieces and chunks come first in search
-// order).  best[0..2] = makespan, row, composition rank.
-template <typename R>
-__global__ void search_merge_kernel(KParams p, SearchParams q) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const unsigned long long key = *q.acc;
-    *q.acc = ~0ull;
-    if (key == ~0ull) return;
-    const uint64_t T = key >> 32;
-    const uint32_t pos = (uint32_t)key;
-    if (T >= q.best[0]) return;
-    const R *binom = reinterpret_cast<const R *>(p.binom);
-    const uint32_t S = p.S, L = p.L;
-    // rank = sum_j C(L - 1 - c_{j-1}, S - j) - C(L - c_j, S - j)   (hockey-stick identity)
-    uint64_t rank = 0;
-    uint32_t prev = 0;
-    for (uint32_t j = 1; j < S; ++j) {
-        const uint32_t wj = q.in_codes[(uint64_t)((j - 1) >> 2) * q.in_cap + pos];
-        const uint32_t c = (wj >> (8 * ((j - 1) & 3))) & 0xFFu;
-        const uint32_t k = S - j;
-        rank += (uint64_t)binom[k * kNB + (L - 1 - prev)] - (uint64_t)binom[k * kNB + (L - c)];
-        prev = c;
+// A lone stage (S = 1): one configuration per row, tested here like any
+// stage, then evaluated; block b's best goes to slot b.
+template <bool AR, bool SCH>
+__global__ __launch_bounds__(kBlock) void search_leaf_kernel(KParams p, SearchParams q) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t n_in = search_n_in(q), bound = *q.bound;
+    const Lds tab = stage_tables(p, smem);
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    uint32_t row, w[1], ty[1], cut[2];
+    search_load<1>(q, i, i < n_in, row, w);
+    int why = 4;
+    unsigned long long key = ~0ull;
+    if (i < n_in) {
+        const SearchNode n = search_node<1, AR>(p, tab, row, w, 0, ty, cut);
+        why = search_try<AR>(p, tab, n, 0, p.L, q.flags, bound);
+        if (why == 0) {
+            uint32_t F[1], B[1];
+            stage_weights<1>(p, tab, cut, ty, F, B);
+            const uint32_t T = dp_full_settle<1, SCH, AR>(p, tab, F, B, load_comm<1>(p), w, row);
+            if (T <= bound) key = ((unsigned long long)T << 32) | i;
+        }
     }
-    q.best[0] = T;
-    q.best[1] = q.in_row[pos];
+    search_flush(q, why == 0, why == 0, why == 1, why == 2, why == 3);
+    block_min_and_finish(key, q.acc, nullptr, nullptr, nullptr, false);
+}
+
+// After a piece: its best configuration replaces the best so far only if
+// strictly better (earlier pieces and chunks come first in search order).
+// best[0..2] = makespan, row, composition rank.  The configuration is in the
+// slot whose key is the piece's best (S = 1: there is no cut, and the row is
+// the one at that position).
+template <typename R>
+__global__ __launch_bounds__(kBlock) void search_merge_kernel(KParams p, SearchParams q, uint32_t nslot) {
+    const unsigned long long key = *q.acc;
+    __syncthreads();
+    if (threadIdx.x == 0) *q.acc = ~0ull;
+    if (key == ~0ull || (key >> 32) >= q.best[0]) return;
+    const uint32_t S = p.S, L = p.L;
+    uint64_t rank = 0;
+    uint32_t row = 0;
+    if (S == 1) {
+        if (threadIdx.x != 0) return;
+        row = q.in_row[(uint32_t)key];
+    } else {
+        uint32_t b = threadIdx.x;
+        while (b < nslot && q.slot_key[b] != key) b += kBlock;
+        if (b >= nslot) return;   // (one thread goes on: a node is one block's)
+        row = q.slot_row[b];
+        const R *binom = reinterpret_cast<const R *>(p.binom);
+        // rank = sum_j C(L - 1 - c_{j-1}, S - j) - C(L - c_j, S - j)   (hockey-stick identity)
+        uint32_t prev = 0;
+        for (uint32_t j = 1; j < S; ++j) {
+            const uint32_t c = (q.slot_w[((j - 1) >> 2) * kSlotMax + b] >> (8 * ((j - 1) & 3))) & 0xFFu;
+            const uint32_t k = S - j;
+            rank += (uint64_t)binom[k * kNB + (L - 1 - prev)] - (uint64_t)binom[k * kNB + (L - c)];
+            prev = c;
+        }
+    }
+    q.best[0] = key >> 32;
+    q.best[1] = row;
     q.best[2] = rank;
 }
 
@@ -714,24 +875,22 @@ hipError_t launch_search_s(int op, const KParams &p, const SearchParams &q, uint
     const dim3 g(grid), b(kBlock);
     switch (op) {
     case kSearchOpCount:
-        if (p.has_ar) hipLaunchKernelGGL((search_count_kernel<S, true, false>), g, b, lds, st, p, q);
-        else if (p.g_mono_all) hipLaunchKernelGGL((search_count_kernel<S, false, true>), g, b, lds, st, p, q);
-        else hipLaunchKernelGGL((search_count_kernel<S, false, false>), g, b, lds, st, p, q);
+        if (p.has_ar) hipLaunchKernelGGL((search_count_kernel<S, true>), g, b, lds, st, p, q);
+        else hipLaunchKernelGGL((search_count_kernel<S, false>), g, b, lds, st, p, q);
         break;
-    case kSearchOpWrite:
-        if (p.has_ar) hipLaunchKernelGGL((search_write_kernel<S, true, false>), g, b, lds, st, p, q);
-        else if (p.g_mono_all) hipLaunchKernelGGL((search_write_kernel<S, false, true>), g, b, lds, st, p, q);
-        else hipLaunchKernelGGL((search_write_kernel<S, false, false>), g, b, lds, st, p, q);
-        break;
-    case kSearchOpLeaf: {
-        const bool sch = p.sched != 0;
-        if (p.has_ar && sch) hipLaunchKernelGGL((search_leaf_kernel<S, true, true>), g, b, lds, st, p, q);
-        else if (p.has_ar) hipLaunchKernelGGL((search_leaf_kernel<S, true, false>), g, b, lds, st, p, q);
-        else if (sch) hipLaunchKernelGGL((search_leaf_kernel<S, false, true>), g, b, lds, st, p, q);
-        else hipLaunchKernelGGL((search_leaf_kernel<S, false, false>), g, b, lds, st, p, q);
-        break;
-    }
-    case kSearchOpMerge: hipLaunchKernelGGL((search_merge_kernel<R>), dim3(1), dim3(64), 0, st, p, q); break;
+    case kSearchOpWrite: hipLaunchKernelGGL((search_write_kernel<S>), g, b, 0, st, p, q); break;
+    case kSearchOpLast:
+        return with_variant(p, [&](auto arc, auto schc) {
+            constexpr bool ar = decltype(arc)::value, sch = decltype(schc)::value;
+            if constexpr (S == 1) {
+                hipLaunchKernelGGL((search_leaf_kernel<ar, sch>), g, b, lds, st, p, q);
+            } else {
+                if (!ar && p.g_mono_all) hipLaunchKernelGGL((search_last_kernel<S, ar, !ar, sch>), g, b, lds, st, p, q);
+                else hipLaunchKernelGGL((search_last_kernel<S, ar, false, sch>), g, b, lds, st, p, q);
+            }
+            return hipGetLastError();
+        });
+    case kSearchOpMerge: hipLaunchKernelGGL((search_merge_kernel<R>), dim3(1), dim3(kBlock), 0, st, p, q, q.n_in); break;
     case kSearchOpRoot: hipLaunchKernelGGL((search_root_kernel<S>), g, b, 0, st, q, q.root_first, q.n_in); break;
     default: return hipErrorInvalidValue;
     }

@@ -90,3 +90,26 @@ def test_identical_layers():
         prob.fwd = np.stack([np.full(L, 1000, np.uint32), np.full(L, 1400, np.uint32)])
         prob.bwd = 2 * prob.fwd
         _check(prob, W.random_candidates(rng, prob, 20000), noalloc=False)
+
+
+@pytest.mark.parametrize("S", [1, 2, 3, 4, 7, 12, 16])
+def test_search_ties_and_runs(S):
+    """The search's last pass on models whose layers tie (the first optimum in search order counts), with few
+    and with many kept configurations a node, more nodes than a wave and than a block takes at a time, and
+    bounds from loose to the optimum and below it."""
+    rng = np.random.default_rng(7300 + S)
+    L = {1: 9, 2: 90, 3: 40, 4: 24, 7: 15, 12: 17, 16: 20}[S]
+    for schedule, M in ((P.SCHEDULE_1F1B, 2 * S + 3), (P.SCHEDULE_EAGER_1F1B, 4 * S + 2), (P.SCHEDULE_1F1B, S)):
+        prob = W.random_problem(rng, L, S, M, 2, cost_hi=3, comm_hi=2, mem_hi=2, cap=[L, 2 * L], assign_rows=5)
+        prob.schedule = schedule
+        ctx = P.poseidon_load_costs(prob, 0)
+        best = coracle.search(prob, 2 ** 31 - 1)["best"]
+        bounds = [2 ** 31 - 1] + ([best[1], best[1] - 1, best[1] + 3] if best else [])
+        for bound in bounds:
+            for ridge in (False, True):
+                b, st = P.poseidon_search(ctx, bound, rows_per_chunk=2, ridge=ridge)
+                o = coracle.search(prob, bound, rows_per_chunk=2, ridge=ridge)
+                assert ((b.index, b.makespan) if b.index is not None else None) == o["best"], (bound, ridge)
+                assert (st.visited, st.evaluated, st.pruned_memory, st.pruned_ridge, st.pruned_bound) == \
+                    (o["visited"], o["evaluated"], o["pruned_memory"], o["pruned_ridge"], o["pruned_bound"])
+        ctx.close()
