@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <array>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -317,6 +318,42 @@ bool closed_form_check(int S, int M, int schedule) {
 
 }  // namespace
 
+// Pinned host words that the kernels write results to: one page for the
+// process, a slot per live context (given back by poseidon_free).  Contexts
+// beyond its slots, or without the page, read their results with a copy.
+namespace {
+struct HostPool {
+    static constexpr int kSlots = 64;
+    std::mutex mu;
+    unsigned long long *page = nullptr;
+    bool tried = false, used[kSlots] = {};
+    unsigned long long *take() {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!tried) {
+            tried = true;
+            void *q = nullptr;
+            if (hipHostMalloc(&q, sizeof(unsigned long long) * pk::kHostWords * kSlots,
+                              hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+                page = (unsigned long long *)q;
+            else
+                (void)hipGetLastError();
+        }
+        for (int i = 0; page && i < kSlots; ++i)
+            if (!used[i]) {
+                used[i] = true;
+                return page + (size_t)i * pk::kHostWords;
+            }
+        return nullptr;
+    }
+    void give(unsigned long long *w) {
+        if (!w) return;
+        std::lock_guard<std::mutex> lock(mu);
+        used[(w - page) / pk::kHostWords] = false;
+    }
+};
+HostPool g_host_pool;
+}  // namespace
+
 struct poseidon_ctx;
 namespace {
 uint64_t noalloc_chunk_for(const poseidon_ctx *ctx);
@@ -346,6 +383,7 @@ struct poseidon_ctx {
     void *sws;             // search frontiers (allocated on the first poseidon_search)
     unsigned long long *shost;   // pinned host words for the search's read-backs (level totals
                                  // and block offsets), allocated with sws
+    unsigned long long *hostw;   // pinned host words for results (HostPool), or null
     uint64_t result_base = 0;    // added to the position the last evaluation or argmin published:
                                  // `first` in range mode (the joint index), else 0 or index_base
     void *scratch;               // the library's fixed scratch on this device (allocation-free calls)
@@ -757,6 +795,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     ctx->A = A; ctx->n_comp = n_comp; ctx->wide = wide; ctx->NB = NB;
     ctx->base = kp;
     ctx->dmem = d;
+    ctx->hostw = g_host_pool.take();
     // the allocation-free evaluation's scratch on this device (looked up once
     // per device) and the chunk size whose workspace fits it
     ctx->scratch = pk::noalloc_scratch(hip_device);
@@ -775,6 +814,8 @@ void poseidon_free(poseidon_ctx *ctx) {
         (void)hipFree(ctx->dmem);
         (void)hipSetDevice(prev);
     }
+    // (the device's work on this context has ended: hipFree waits for it)
+    g_host_pool.give(ctx->hostw);
     delete ctx;
 }
 
@@ -804,20 +845,13 @@ struct DeviceGuard {
     }
 };
 
-// The device word holds (T << 32 | position within the call); the index
-// returned is base + position.
-int read_best(poseidon_ctx *ctx, hipStream_t st, unsigned long long word_index, uint64_t base,
-              poseidon_best *best) {
-    unsigned long long w[W_COUNT];
-    if (hipMemcpyAsync(w, ctx->state, sizeof(w), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return POSEIDON_E_DEVICE;
-    if (w[W_ERR] & 0xFFFFFFFFull) {
+// A call's result from its error flag and key.
+int best_of(poseidon_ctx *ctx, unsigned long long err, unsigned long long k, uint64_t base, poseidon_best *best) {
+    if (err & 0xFFFFFFFFull) {
         const unsigned long long zero = 0;
         (void)hipMemcpy(ctx->state + W_ERR, &zero, 8, hipMemcpyHostToDevice);
         return POSEIDON_E_INVAL;
     }
-    const unsigned long long k = w[word_index];
     if (k == ~0ull || (k >> 32) == 0xFFFFFFFFull) {
         best->index = UINT64_MAX;
         best->makespan = 0xFFFFFFFFu;
@@ -828,6 +862,17 @@ int read_best(poseidon_ctx *ctx, hipStream_t st, unsigned long long word_index, 
     best->makespan = (uint32_t)(k >> 32);
     best->feasible = 1;
     return POSEIDON_OK;
+}
+
+// The device word holds (T << 32 | position within the call); the index
+// returned is base + position.
+int read_best(poseidon_ctx *ctx, hipStream_t st, unsigned long long word_index, uint64_t base,
+              poseidon_best *best) {
+    unsigned long long w[W_COUNT];
+    if (hipMemcpyAsync(w, ctx->state, sizeof(w), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return POSEIDON_E_DEVICE;
+    return best_of(ctx, w[W_ERR], w[word_index], base, best);
 }
 
 // Largest number of candidates one launch sequence handles; longer calls
@@ -1039,6 +1084,7 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
     kp.feas_bits_out = feasible_bits_out;
     kp.nwords = (cands->count + 31) / 32;
     split_first(ctx, cands, kp);
+    kp.host_words = best_out ? ctx->hostw : nullptr;
     kp.codes = m.codes;
     kp.ccap = m.cap;
     if (kp.closed) {
@@ -1082,8 +1128,10 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         for (uint32_t l = 1; l <= kp.nlevels; ++l)
             if (pk::launch_ilv_resume(kp, lc, st, l) != hipSuccess) return rearm(ctx, st);
     }
-    if (best_out) return read_best(ctx, st, W_RESULT, ctx->result_base, best_out);
-    return POSEIDON_OK;
+    if (!best_out) return POSEIDON_OK;
+    if (!kp.host_words) return read_best(ctx, st, W_RESULT, ctx->result_base, best_out);
+    if (hipStreamSynchronize(st) != hipSuccess) return POSEIDON_E_DEVICE;
+    return best_of(ctx, kp.host_words[pk::kHostErr], kp.host_words[pk::kHostKey], ctx->result_base, best_out);
 }
 
 }  // namespace
@@ -1174,6 +1222,7 @@ int poseidon_eval_candidates_bounded(poseidon_ctx *ctx, const poseidon_cands *ca
     kp.assign_idx = cands->assign_idx;
     split_first(ctx, cands, kp);
     const uint64_t n = cands->count;
+    kp.host_words = n ? ctx->hostw : nullptr;   // (nothing to evaluate: no kernel writes them)
     if (chunk == 0 || chunk > n) chunk = n;
     // the survivor list has room for the survivors of kChunk candidates; a
     // longer chunk is filtered in pieces that all see the bound in force at
@@ -1209,9 +1258,15 @@ int poseidon_eval_candidates_bounded(poseidon_ctx *ctx, const poseidon_cands *ca
         }
     }
     unsigned long long w[W_COUNT];
-    if (hipMemcpyAsync(w, ctx->state, sizeof(w), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
+    if (kp.host_words) {
+        if (hipStreamSynchronize(st) != hipSuccess) return POSEIDON_E_DEVICE;
+        w[W_RUN] = kp.host_words[pk::kHostKey];
+        w[W_ERR] = kp.host_words[pk::kHostErr];
+        for (int i = 0; i < 3; ++i) w[W_STAT_EVAL + i] = kp.host_words[pk::kHostStats + i];
+    } else if (hipMemcpyAsync(w, ctx->state, sizeof(w), hipMemcpyDeviceToHost, st) != hipSuccess ||
+               hipStreamSynchronize(st) != hipSuccess) {
         return POSEIDON_E_DEVICE;
+    }
     if (stats_out) {
         stats_out->evaluated = w[W_STAT_EVAL];
         stats_out->pruned = w[W_STAT_PRUNED];

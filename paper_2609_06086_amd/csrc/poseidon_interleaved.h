@@ -539,7 +539,7 @@ __global__ __launch_bounds__(kBlock) void ilv_kernel(KParams p) {
         __syncthreads();
         if (threadIdx.x == 0) p.qcount[blockIdx.x] = nq;   // entries for level 1
     }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, p.nlevels == 0, p.accumulate);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, p.nlevels == 0, p.accumulate, nullptr, 0, host_out(p));
 }
 
 // Level `lvl` of the Interleaved 1F1B cascade: resume the queued lanes from
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void ilv_resume_kernel(KParams p, uint32_t 
         __syncthreads();
         if (threadIdx.x == 0) p.qcount[(uint64_t)lvl * p.nseg + blockIdx.x] = nq;
     }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, lvl == p.nlevels, p.accumulate);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, lvl == p.nlevels, p.accumulate, nullptr, 0, host_out(p));
 }
 
 }  // namespace pk

@@ -45,6 +45,9 @@ __host__ __device__ constexpr unsigned __int128 bucket_hi(uint32_t key) {
 constexpr int kMaxLevels = 6;   // cascade checkpoints of the steady loop
 constexpr uint32_t kSearchScanMax = 16384;   // blocks of one search level piece (search_scan_kernel's LDS)
 
+// Words of KParams::host_words.
+enum HostWord : int { kHostKey = 0, kHostErr = 1, kHostStats = 2, kHostWords = 8 };
+
 enum AssignMode : uint32_t { kAssignFixed = 0, kAssignTable = 1, kAssignDigits = 2 };
 
 // Rows of the closed form's constant table, per 0-based stage x with
@@ -114,6 +117,7 @@ struct KParams {
     unsigned long long *snap;         // early stop: run_best as of the previous chunk
     unsigned long long *stats;   // evaluated, pruned, infeasible
     unsigned int *err;
+    unsigned long long *host_words;   // pinned host words of a call whose caller waits for its result, or null
     // early stop: the caller's bound, and the list of the candidates that
     // pass the memory and Eq. 2 tests (call index, cut codes in `codes`), in
     // per-block segments of seg_cap entries with their counts in scount;

@@ -971,6 +971,24 @@ __device__ __forceinline__ void block_min(unsigned long long v, unsigned long lo
     }
 }
 
+// The words a host that waits for a call's result reads, written straight to
+// its pinned memory by the call's last block: key, error flag, early-stop
+// counters (earlier kernels' writes).  A copy after the kernels costs another
+// launch and its wait, about 8 us of a small call's 30.
+struct HostOut {
+    unsigned long long *words = nullptr;   // null: nobody waits
+    const unsigned int *err = nullptr;
+    const unsigned long long *stats = nullptr;
+};
+__device__ __forceinline__ HostOut host_out(const KParams &p) { return HostOut{p.host_words, p.err, p.stats}; }
+__device__ __forceinline__ void publish_host(const HostOut &h, unsigned long long key) {
+    h.words[kHostKey] = key;
+    h.words[kHostErr] = __hip_atomic_load(h.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < 3; ++i)
+        h.words[kHostStats + i] = __hip_atomic_load(h.stats + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence_system();
+}
+
 // Block min of `v`, folded into *acc.  When `finalize` is set (the last
 // kernel of an evaluation chunk), the last block of the grid also moves *acc
 // to *result (or folds it in, for the second and later chunks of a call,
@@ -981,7 +999,8 @@ __device__ __forceinline__ void block_min_and_finish(unsigned long long v, unsig
                                                      unsigned long long *run_best, bool finalize,
                                                      bool accumulate = false,
                                                      unsigned long long *snap = nullptr,
-                                                     uint32_t nblocks = 0) {
+                                                     uint32_t nblocks = 0,
+                                                     HostOut host = HostOut{}) {
     __shared__ unsigned long long part[kWaves];
     v = wave_min(v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -998,15 +1017,22 @@ __device__ __forceinline__ void block_min_and_finish(unsigned long long v, unsig
             if (ticket == (nblocks ? nblocks : gridDim.x) - 1) {
                 __threadfence();
                 const unsigned long long k = atomicExch(acc, ~0ull);
+                unsigned long long out = k;
                 if (result) {
-                    if (accumulate) atomicMin(result, k);
-                    else atomicExch(result, k);
+                    if (accumulate) {
+                        const unsigned long long old = atomicMin(result, k);
+                        out = old < k ? old : k;
+                    } else {
+                        atomicExch(result, k);
+                    }
                 }
                 if (run_best) {
                     const unsigned long long old = atomicMin(run_best, k);
-                    if (snap) atomicExch(snap, old < k ? old : k);
+                    out = old < k ? old : k;
+                    if (snap) atomicExch(snap, out);
                 }
                 atomicExch(done, 0u);
+                if (host.words) publish_host(host, out);
             }
         }
     }
@@ -1622,7 +1648,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(KParams p) {
             best = key < best ? key : best;
         }
     }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate, nullptr, 0, host_out(p));
 }
 
 // The list of candidates without a closed-form proof, arrays of lcap
@@ -1951,7 +1977,7 @@ __global__ __launch_bounds__(kBlock) void full_kernel(KParams p, uint32_t nseg) 
             k0 = k1;
         }
     }
-    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate, nullptr, need);
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate, nullptr, need, host_out(p));
 }
 
 // Early stop (Eq. 2 / Theorem 1) over one piece of a chunk.  Against the
@@ -2375,7 +2401,7 @@ __device__ __forceinline__ void pend_run(const Pend &l, uint32_t first, uint32_t
 // `want` set are kept; then the wave runs a full batch if it has one.
 template <typename F>
 __device__ __forceinline__ void pend_add(Pend &l, bool want, bool proven, uint32_t at, uint32_t T, uint32_t pos,
-                                         unsigned long long &best, F &&f) {
+                                         unsigned long long &best, F &&f, uint32_t batch = 64) {
     const uint32_t lane = threadIdx.x & 63;
     if (want && proven) {
         const unsigned long long key = make_key(true, T, pos);
@@ -2393,9 +2419,10 @@ __device__ __forceinline__ void pend_add(Pend &l, bool want, bool proven, uint32
         l.low[j] = T;
     }
     l.n += __popcll(m);
-    if (l.n >= 64) {
-        l.n -= 64;
-        pend_run(l, l.n, 64u, best, f);   // (the last 64: the rest stays in place)
+    if (l.n >= batch) {   // (without a closed form: every batch at once)
+        const uint32_t n = min(l.n, 64u);
+        l.n -= n;
+        pend_run(l, l.n, n, best, f);   // (the last ones: the rest stays in place)
     }
 }
 
@@ -2476,14 +2503,16 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
                 else hi = mid;
             }
             at = lo * (uint32_t)p.seg_cap + (k - pre[lo]);
-            uint32_t a, w[NW], cut[S + 1], to[S], F[S], B[S];
-            load(at, i, a, w, cut, to, F, B);
-            proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
+            if (p.closed) {
+                uint32_t a, w[NW], cut[S + 1], to[S], F[S], B[S];
+                load(at, i, a, w, cut, to, F, B);
+                proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
+            }
         }
-        pend_add(l, k < n, proven, at, T, i, best, full);
+        pend_add(l, k < n, proven, at, T, i, best, full, p.closed ? 64u : 1u);
     }
     best = pend_finish(l, best, p.acc, full);
-    block_min_and_finish(best, p.acc, p.done, nullptr, p.run_best, true, false, publish ? p.snap : nullptr, need);
+    block_min_and_finish(best, p.acc, p.done, nullptr, p.run_best, true, false, publish ? p.snap : nullptr, need, host_out(p));
 }
 
 constexpr size_t kLdsBlockMax = 64 * 1024;   // LDS bytes one block of these kernels may use
