@@ -26,6 +26,17 @@ namespace pk {
 constexpr int kBlock = 256;            // 4 waves of 64
 constexpr int kWaves = kBlock / 64;
 
+// The kernel's arguments (its only parameter, at the start of the kernarg
+// segment) through a pointer the compiler cannot see through: fields read
+// through it are scalar loads at the point of use.  Read the plain way they
+// are loop invariants, some 100 of them in fused_kernel, that are loaded once
+// and then spilled into vector lanes (a VALU operation per reload).
+__device__ __forceinline__ const KParams &fresh_args() {
+    uint64_t a = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(a));
+    return *(const KParams *)reinterpret_cast<const __attribute__((address_space(4))) KParams *>(a);
+}
+
 // ---------------------------------------------------------------------------
 // LDS image of the context's tables (one copy per block)
 // ---------------------------------------------------------------------------
@@ -809,35 +820,50 @@ __device__ __forceinline__ Comm<S> load_comm(const KParams &p) {
 // ---------------------------------------------------------------------------
 // Classification of a candidate against the bound b over its stages
 // 0 .. X-1 in pipeline order, as the search of Sec. 4.2.3 discards a
-// partial configuration: 0 if no stage fails; 1 if the first failing stage
-// exceeds its device's memory (tested first at a stage); 2 if its g(S_x)
-// exceeds b.  The stage weights come from the stage entries.
-template <int S, bool AR, int X, bool G24>
-__device__ __forceinline__ uint32_t classify_g(const KParams &p, const Ent &t, const uint32_t (&cut)[S + 1],
-                                               const uint32_t (&to)[S], uint32_t b) {
-    uint32_t pre = 0, inner = 0, bprev = 0, mm = 0, gm = 0;
+// partial configuration: out = some stage fails; over = the first failing
+// stage exceeds its device's memory (tested first at a stage), not only
+// g(S_x) <= b.  Both are lane masks in scalar registers, so that a stage
+// costs two compares and no other vector operation for its tests.  The stage
+// weights come from the stage entries.  Without all-reduce times the inner
+// max of Eq. 2 is its whole sum, so g(S_x) = sum_{i<x} (F_i + B_i)
+// + M (F_x + B_x) and the two times are needed only as their sum: field
+// kEPf holds Pf + Pb then (SUM), or both are read.
+template <int S, bool AR, int X, bool G24, bool SUM>
+__device__ __forceinline__ void classify_g(const KParams &p, const Ent &t, const uint32_t (&cut)[S + 1],
+                                           const uint32_t (&to)[S], uint32_t b, bool &out, bool &over) {
+    uint32_t pre = 0, inner = 0, bprev = 0;
+    const uint32_t M = p.M;
+    out = over = false;
 #pragma unroll
     for (int x = 0; x < X; ++x) {
-        const uint32_t F = ent<kEPf>(t, cut[x + 1], to[x]) - ent<kEPf>(t, cut[x], to[x]);
-        const uint32_t B = ent<kEPb>(t, cut[x + 1], to[x]) - ent<kEPb>(t, cut[x], to[x]);
-        const uint32_t D = AR ? ent<kEPd>(t, cut[x + 1], to[x]) - ent<kEPd>(t, cut[x], to[x]) : 0u;
-        if (cut[x + 1] > ent<kEHm>(t, cut[x], to[x])) mm |= 1u << x;
-        inner = x == 0 ? D : max(inner + bprev, D);
-        // M (F + B) is below 2^31 like every path weight: a full-rate 24-bit
-        // multiply when both factors fit
-        const uint32_t G = G24 ? __umul24(p.M, F + B) : p.M * (F + B);
-        if (pre + G + inner > b) gm |= 1u << x;
-        pre += F;
-        bprev = B;
+        const uint32_t lo = cut[x], hi = cut[x + 1], tx = to[x];
+        const bool m = hi > ent<kEHm>(t, lo, tx);
+        uint32_t W = ent<kEPf>(t, hi, tx) - ent<kEPf>(t, lo, tx);
+        uint32_t g;
+        if constexpr (AR) {
+            const uint32_t F = W, B = ent<kEPb>(t, hi, tx) - ent<kEPb>(t, lo, tx);
+            const uint32_t D = ent<kEPd>(t, hi, tx) - ent<kEPd>(t, lo, tx);
+            inner = x == 0 ? D : max(inner + bprev, D);
+            // M (F + B) is below 2^31 like every path weight: a full-rate
+            // 24-bit multiply when both factors fit
+            g = pre + inner + (G24 ? __umul24(M, F + B) : M * (F + B));
+            pre += F;
+            bprev = B;
+        } else {
+            if constexpr (!SUM) W += ent<kEPb>(t, hi, tx) - ent<kEPb>(t, lo, tx);
+            g = pre + (G24 ? __umul24(M, W) : M * W);
+            pre += W;
+        }
+        over |= m & !out;
+        out |= m | (g > b);
     }
-    const uint32_t f = mm | gm;
-    return f == 0u ? 0u : (mm & f & (0u - f)) ? 1u : 2u;
 }
 
-template <int S, bool AR, int X>
-__device__ __forceinline__ uint32_t classify(const KParams &p, const Ent &t, const uint32_t (&cut)[S + 1],
-                                             const uint32_t (&to)[S], uint32_t b) {
-    return p.g24 ? classify_g<S, AR, X, true>(p, t, cut, to, b) : classify_g<S, AR, X, false>(p, t, cut, to, b);
+template <int S, bool AR, int X, bool SUM>
+__device__ __forceinline__ void classify(const KParams &p, const Ent &t, const uint32_t (&cut)[S + 1],
+                                         const uint32_t (&to)[S], uint32_t b, bool &out, bool &over) {
+    if (p.g24) classify_g<S, AR, X, true, SUM>(p, t, cut, to, b, out, over);
+    else classify_g<S, AR, X, false, SUM>(p, t, cut, to, b, out, over);
 }
 
 // ---------------------------------------------------------------------------
@@ -1332,17 +1358,92 @@ __device__ __forceinline__ R decode_start(const KParams &p, R r) {
     return (R)(p.n_comp - (uint64_t)r);
 }
 
+// The rank and the assignment index of kIlp list entries, loaded before any
+// is used: candidate() on one after the other waits for memory kIlp times
+// (early stop on 2^26 candidates at S = 8: 587 us so, 491 us loaded together).
+template <typename R>
+__device__ __forceinline__ void check_entries(const KParams &p, const uint64_t (&rank)[kIlp], const uint32_t (&idx)[kIlp],
+                                              const bool (&act)[kIlp], bool (&ok)[kIlp], uint32_t (&asg)[kIlp],
+                                              R (&r)[kIlp]) {
+#pragma unroll
+    for (int u = 0; u < kIlp; ++u) {
+        const bool in = rank[u] < p.n_comp && idx[u] < p.A;
+        r[u] = in ? (R)rank[u] : (R)0;
+        asg[u] = in ? idx[u] : 0u;
+        ok[u] = in & act[u];
+    }
+}
+
+// Candidates base + u * stride + lane (u < kIlp) of the piece, base the same
+// for every lane of the wave (a list is then read at a scalar base and a
+// 32-bit lane offset): call positions, ranks and assignment indices (0 where
+// out of range: ok = false).  Lanes past the end take the last candidate,
+// act = ok = false.
+template <typename R>
+__device__ __forceinline__ void load_candidates(const KParams &p, uint32_t base, uint32_t stride, uint32_t lane,
+                                                bool (&act)[kIlp], bool (&ok)[kIlp], uint32_t (&pos)[kIlp],
+                                                uint32_t (&asg)[kIlp], R (&r)[kIlp]) {
+    const uint32_t n = (uint32_t)p.n_i, first_i = (uint32_t)p.first_i;
+    uint32_t wb[kIlp], l[kIlp];
+#pragma unroll
+    for (int u = 0; u < kIlp; ++u) {
+        const uint32_t i = base + u * stride;
+        wb[u] = min(i, n - 1);
+        l[u] = min(lane, n - 1 - wb[u]);
+        wb[u] += first_i;
+        act[u] = i + lane < n;
+        pos[u] = wb[u] + l[u];
+    }
+    if (p.comp_rank) {
+        uint64_t rank[kIlp];
+        uint32_t idx[kIlp];
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u)
+            rank[u] = *reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(p.comp_rank + wb[u]) + (l[u] << 3));
+        if (p.assign_idx) {
+#pragma unroll
+            for (int u = 0; u < kIlp; ++u)
+                idx[u] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(p.assign_idx + wb[u]) + (l[u] << 2));
+        } else {
+#pragma unroll
+            for (int u = 0; u < kIlp; ++u) idx[u] = 0u;
+        }
+        check_entries<R>(p, rank, idx, act, ok, asg, r);
+    } else {
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) ok[u] = candidate<R>(p, pos[u], r[u], asg[u]) & act[u];
+    }
+}
+
+// The same at any call positions pos (valid positions also for lanes with
+// act = false).
+template <typename R>
+__device__ __forceinline__ void gather_candidates(const KParams &p, const uint32_t (&pos)[kIlp], const bool (&act)[kIlp],
+                                                  bool (&ok)[kIlp], uint32_t (&asg)[kIlp], R (&r)[kIlp]) {
+    if (p.comp_rank) {
+        uint64_t rank[kIlp];
+        uint32_t idx[kIlp];
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) rank[u] = p.comp_rank[pos[u]];
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) idx[u] = p.assign_idx ? p.assign_idx[pos[u]] : 0u;
+        check_entries<R>(p, rank, idx, act, ok, asg, r);
+    } else {
+#pragma unroll
+        for (int u = 0; u < kIlp; ++u) ok[u] = candidate<R>(p, pos[u], r[u], asg[u]) & act[u];
+    }
+}
+
 template <int S, typename R, int H, typename PC>
 __device__ __forceinline__ void decode_ilp(const KParams &p, const PC &pc, uint32_t base,
                                            uint32_t stride, bool (&act)[kIlp], bool (&ok)[kIlp],
                                            uint32_t (&asg)[kIlp], uint32_t (&w)[kIlp][Codes<S>::kWords]) {
     constexpr int NW = Codes<S>::kWords;
     R q[kIlp];
+    uint32_t pos[kIlp];
+    load_candidates<R>(p, base, stride, threadIdx.x & 63, act, ok, pos, asg, q);
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
-        const uint32_t i = base + u * stride;
-        act[u] = i < (uint32_t)p.n_i;
-        ok[u] = candidate<R>(p, (uint32_t)p.first_i + (act[u] ? i : 0u), q[u], asg[u]) && act[u];
         q[u] = decode_start<R>(p, q[u]);
 #pragma unroll
         for (int k = 0; k < NW; ++k) w[u][k] = 0;
@@ -1400,9 +1501,9 @@ __device__ __forceinline__ void decode_cuts(const KParams &p, const PC &pc,
                                             const uint32_t (&pos)[kIlp], const bool (&act)[kIlp],
                                             bool (&ok)[kIlp], uint32_t (&asg)[kIlp], R (&q)[kIlp],
                                             uint32_t (&cut)[kIlp][S + 1]) {
+    gather_candidates<R>(p, pos, act, ok, asg, q);
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
-        ok[u] = candidate<R>(p, pos[u], q[u], asg[u]) && act[u];
         q[u] = decode_start<R>(p, q[u]);
         cut[u][0] = 0;
         cut[u][S] = p.L;
@@ -1416,7 +1517,7 @@ __device__ __forceinline__ void decode_batch(const KParams &p, const PC &pc, uin
     constexpr int NW = Codes<S>::kWords;
     bool act[kIlp], ok[kIlp];
     uint32_t asg[kIlp], w[kIlp][NW];
-    decode_ilp<S, R, H>(p, pc, base, stride, act, ok, asg, w);
+    decode_ilp<S, R, H>(p, pc, __builtin_amdgcn_readfirstlane(base), stride, act, ok, asg, w);
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
         const uint32_t i = base + u * stride;
@@ -1662,17 +1763,6 @@ struct FullList {
         : pos(p.flist), w(p.flist + p.ccap), asg(p.flist + (1 + Codes<S>::kWords) * p.ccap) {}
 };
 
-// The kernel's arguments (its only parameter, at the start of the kernarg
-// segment) through a pointer the compiler cannot see through: fields read
-// through it are scalar loads at the point of use.  Read the plain way they
-// are loop invariants, some 100 of them in fused_kernel, that are loaded once
-// and then spilled into vector lanes (a VALU operation per reload).
-__device__ __forceinline__ const KParams &fresh_args() {
-    uint64_t a = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
-    asm volatile("" : "+s"(a));
-    return *(const KParams *)reinterpret_cast<const __attribute__((address_space(4))) KParams *>(a);
-}
-
 // One candidate per lane of a wave from its cut codes w (all zero: invalid),
 // assignment a and position gi: stage weights, memory check, closed-form
 // makespan (poseidon_closed.h).  Lanes whose value is not proven go to the
@@ -1778,10 +1868,11 @@ __device__ __forceinline__ void fused_all(const KParams &p, unsigned char *smem)
         }
     } else {
         const uint32_t stride = gridDim.x * NT;
-        for (uint32_t wb = blockIdx.x * NT + (threadIdx.x - lane); wb < n_i; wb += kIlp * stride) {   // (wave-uniform)
+        const uint32_t wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64;
+        for (uint32_t wb = blockIdx.x * NT + wave0; wb < n_i; wb += kIlp * stride) {   // (wave-uniform)
             bool act[kIlp], ok[kIlp];
             uint32_t asg[kIlp], w[kIlp][NW];
-            decode_ilp<S, R, H>(fresh_args(), pc, wb + lane, stride, act, ok, asg, w);
+            decode_ilp<S, R, H>(fresh_args(), pc, wb, stride, act, ok, asg, w);
 #pragma unroll
             for (int u = 0; u < kIlp; ++u) bad |= act[u] && !ok[u];
 #pragma unroll 1
@@ -2036,11 +2127,11 @@ struct AList {
 // compare decides it before any cut is decoded.  thr[2t], thr[2t+1] = those
 // two limits for every type t (threads t < T; the caller's barrier
 // publishes them).
-template <int S, typename R>
+template <int S, typename R, bool SUM>
 __device__ __forceinline__ void stage1_limits(const KParams &p, const Ent &tab, uint32_t b, unsigned long long *thr) {
     if (threadIdx.x >= p.T) return;
     const uint32_t to = threadIdx.x * p.erow, L = p.L, hmax = L - S + 1;   // hmax: the largest c_1
-    const uint32_t pf0 = ent<kEPf>(tab, 0, to), pb0 = ent<kEPb>(tab, 0, to);
+    // (the prefix sums start at 0)
     const uint32_t pd0 = p.has_ar ? ent<kEPd>(tab, 0, to) : 0u;
     // g(S_1) is nondecreasing in c_1: the largest passing end point by halving
     // steps (hb = 0: none passes; every c_1 is at least 1)
@@ -2048,10 +2139,10 @@ __device__ __forceinline__ void stage1_limits(const KParams &p, const Ent &tab, 
     for (uint32_t st = 128; st; st >>= 1) {
         const uint32_t c = hb + st;
         if (c <= hmax) {
-            const uint32_t F = ent<kEPf>(tab, c, to) - pf0, B = ent<kEPb>(tab, c, to) - pb0;
+            const uint32_t W = ent<kEPf>(tab, c, to) + (SUM ? 0u : ent<kEPb>(tab, c, to));
             const uint32_t D = p.has_ar ? ent<kEPd>(tab, c, to) - pd0 : 0u;
             // M (F + B) + d_1 is an Eq. 2 value, below 2^31 like every path weight
-            if (p.M * (F + B) + D <= b) hb = c;
+            if (p.M * W + D <= b) hb = c;
         }
     }
     const uint32_t hm = min(ent<kEHm>(tab, 0, to), hmax), h1 = min(hb, hm);
@@ -2097,10 +2188,22 @@ __host__ __device__ constexpr size_t filter_static_lds() {
     return filter_screens<S, AR, MODE>() ? (size_t)kScreenBuf * 4 * (kBlock / 64) + 16 * kTypesMax : 0;
 }
 
+// Of the set lanes of m, those below this lane.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Word at byte offset o of an array whose start is the same for every lane
+// (a scalar base and a 32-bit lane offset: no 64-bit address per lane).
+__device__ __forceinline__ uint32_t &word_at(uint32_t *a, uint32_t o) {
+    return *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(a) + o);
+}
+
 // The tests of kIlp decoded candidates of one lane (cuts 1 .. X of
 // filter_all's mode in cut[u]): classification, counts, and the list entry
-// of each candidate kept (the prefix list, or the survivor list).
-template <int S, typename R, bool AR, int MODE>
+// of each candidate kept (the prefix list, or the survivor list).  Every
+// lane of the wave comes here; the counts are the wave's.
+template <int S, typename R, bool AR, bool SUM, int MODE>
 __device__ __forceinline__ void filter_emit(const KParams &p, const Ent &tab, uint32_t b, unsigned int *nq,
                                             const bool (&act)[kIlp], const bool (&ok)[kIlp],
                                             const uint32_t (&pos)[kIlp], const uint32_t (&asg)[kIlp],
@@ -2110,51 +2213,56 @@ __device__ __forceinline__ void filter_emit(const KParams &p, const Ent &tab, ui
     constexpr int X = MODE == kFilterPrefix ? X0 : S;   // stages decided, cuts 1 .. X decoded
     constexpr int NW = Codes<S>::kWords;
     constexpr int AW = (X0 + 3) / 4;                    // code words of the prefix cuts
-    const AList al(p);
     const unsigned int lane = threadIdx.x & 63;
-    const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap, ccap = (uint32_t)p.ccap;
+    unsigned long long m[kIlp];
+    uint32_t total = 0;
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
         uint32_t to[S];
         decode_toff<S>(p, tab, ok[u] ? asg[u] : 0u, to);
-        const uint32_t cls = classify<S, AR, X>(p, tab, cut[u], to, b);
-        bool keep = false;
-        if (act[u]) {
-            if (!ok[u]) bad = true;
-            else if (cls == 1) ++n_infeas;
-            else if (cls == 2) ++n_pruned;
-            else keep = true;
-        }
-        const unsigned long long m = __ballot(keep);
-        if (m) {
-            unsigned int slot0 = 0;
-            if (lane == 0) slot0 = atomicAdd(nq, (unsigned int)__popcll(m));
-            slot0 = __shfl(slot0, 0, 64);
-            if (keep) {
-                const unsigned long long below = lane ? (m & ((1ull << lane) - 1ull)) : 0ull;
-                const uint32_t o = seg + slot0 + (uint32_t)__popcll(below);
-                if constexpr (MODE == kFilterPrefix) {
-                    uint32_t w[AW];
+        bool out, over;
+        classify<S, AR, X, SUM>(p, tab, cut[u], to, b, out, over);
+        bad |= act[u] & !ok[u];
+        const bool valid = act[u] & ok[u];
+        m[u] = __ballot(valid & !out);
+        n_infeas += (uint32_t)__popcll(__ballot(valid & over));
+        n_pruned += (uint32_t)__popcll(__ballot(valid & out & !over));
+        total += (uint32_t)__popcll(m[u]);
+    }
+    if (total == 0) return;
+    if (MODE != kFilterPrefix) n_keep += total;
+    uint32_t slot0 = 0;
+    if (lane == 0) slot0 = atomicAdd(nq, total);
+    slot0 = __builtin_amdgcn_readfirstlane(slot0);
+    // (32-bit word offsets of a segment: each list holds fewer than 2^32
+    // words; byte offsets inside a segment, seg_cap entries, fit too)
+    const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap, ccap = (uint32_t)p.ccap;
+    const AList al(p);
 #pragma unroll
-                    for (int k = 0; k < AW; ++k) w[k] = 0;
+    for (int u = 0; u < kIlp; ++u) {
+        if ((m[u] >> lane) & 1) {
+            const uint32_t o = (slot0 + lanes_below(m[u])) << 2;
+            if constexpr (MODE == kFilterPrefix) {
+                uint32_t w[AW];
 #pragma unroll
-                    for (int j = 1; j <= X0; ++j) w[(j - 1) / 4] |= cut[u][j] << (8 * ((j - 1) % 4));
-                    al.pos[o] = pos[u];
-                    al.asg[o] = asg[u];
-                    al.rlo[o] = (uint32_t)r[u];
-                    if (sizeof(R) == 8) al.rhi[o] = (uint32_t)((uint64_t)r[u] >> 32);
+                for (int k = 0; k < AW; ++k) w[k] = 0;
 #pragma unroll
-                    for (int k = 0; k < AW; ++k) al.w[k * ccap + o] = w[k];
-                } else {
-                    uint32_t w[NW];
-                    pack_cuts<S>(cut[u], true, w);
-                    p.sidx[o] = pos[u];
+                for (int j = 1; j <= X0; ++j) w[(j - 1) / 4] |= cut[u][j] << (8 * ((j - 1) % 4));
+                word_at(al.pos + seg, o) = pos[u];
+                word_at(al.asg + seg, o) = asg[u];
+                word_at(al.rlo + seg, o) = (uint32_t)r[u];
+                if (sizeof(R) == 8) word_at(al.rhi + seg, o) = (uint32_t)((uint64_t)r[u] >> 32);
 #pragma unroll
-                    for (int k = 0; k < NW; ++k) p.codes[k * ccap + o] = w[k];
-                }
+                for (int k = 0; k < AW; ++k) word_at(al.w + (k * ccap + seg), o) = w[k];
+            } else {
+                uint32_t w[NW];
+                pack_cuts<S>(cut[u], true, w);
+                word_at(p.sidx + seg, o) = pos[u];
+#pragma unroll
+                for (int k = 0; k < NW; ++k) word_at(p.codes + (k * ccap + seg), o) = w[k];
             }
-            if (MODE != kFilterPrefix) n_keep += lane == 0 ? (uint32_t)__popcll(m) : 0u;
         }
+        slot0 += (uint32_t)__popcll(m[u]);
     }
 }
 
@@ -2164,52 +2272,46 @@ __device__ __forceinline__ void filter_emit(const KParams &p, const Ent &tab, ui
 // and decodes and tests them kIlp * 64 at a time, so that the searches of
 // the first cuts run only for candidates that pass stage 1 (about two in
 // three on the workloads here) and every lane has a candidate to decode.
-template <int S, typename R, int H, bool AR, typename PC>
-__device__ __forceinline__ void filter_screened(const KParams &p, const PC &pc, const Ent &tab,
+template <int S, typename R, int H, bool AR, bool SUM, typename PC>
+__device__ __forceinline__ void filter_screened(const KParams &p0, const PC &pc, const Ent &tab,
                                                 uint32_t b, unsigned int *nq, uint32_t *buf,
                                                 const unsigned long long *thr, uint32_t &n_keep,
                                                 uint32_t &n_pruned, uint32_t &n_infeas, bool &bad) {
     constexpr int X0 = filter_prefix<S>();
     constexpr uint32_t kTile = kIlp * 64;
     const unsigned int lane = threadIdx.x & 63;
-    const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
     // 32-bit positions: a piece holds at most 2^26 candidates, a call fewer than 2^32
-    const uint32_t n = (uint32_t)p.n_i, first_i = (uint32_t)p.first_i;
+    const uint32_t n = (uint32_t)p0.n_i, first_i = (uint32_t)p0.first_i;
     const uint32_t nwave = gridDim.x * (kBlock / 64);
-    uint32_t tile = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);   // next tile of the stream
+    // next tile of the stream (the same for every lane)
+    uint32_t tile = blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t cnt = 0;                                                  // positions in buf
     for (;;) {
         // screen tiles until a batch is buffered or the stream ends
         while (cnt < kTile && tile * kTile < n) {
+            const KParams &p = fresh_args();
             const uint32_t t0 = tile * kTile;
             tile += nwave;
-            bool keep[kIlp];
+            bool act[kIlp], ok[kIlp];
+            uint32_t pos[kIlp], a[kIlp];
+            R r[kIlp];
+            load_candidates<R>(p, t0, 64, lane, act, ok, pos, a, r);
 #pragma unroll
             for (int u = 0; u < kIlp; ++u) {
-                const uint32_t i = t0 + (uint32_t)u * 64 + lane;
-                keep[u] = false;
-                if (i < n) {
-                    R r;
-                    uint32_t a;
-                    if (!candidate<R>(p, first_i + i, r, a)) {
-                        keep[u] = true;   // out of range: the batch raises the error flag
-                    } else {
-                        const uint32_t t = first_stage_type<S>(p, a);
-                        const uint64_t rk = (uint64_t)r;
-                        if (rk < thr[2 * t]) keep[u] = true;
-                        else if (rk >= thr[2 * t + 1]) ++n_infeas;
-                        else ++n_pruned;
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kIlp; ++u) {
-                const unsigned long long m = __ballot(keep[u]);
-                if (keep[u]) buf[cnt + (uint32_t)__popcll(m & below)] = t0 + (uint32_t)u * 64 + lane;
+                const uint32_t t = first_stage_type<S>(p, a[u]);
+                const uint64_t rk = (uint64_t)r[u];
+                const bool fail = rk >= thr[2 * t], over = rk >= thr[2 * t + 1];
+                // (out of range: kept, the batch raises the error flag)
+                const bool keep = act[u] & !(ok[u] & fail);
+                const unsigned long long m = __ballot(keep);
+                n_infeas += (uint32_t)__popcll(__ballot(ok[u] & fail & over));
+                n_pruned += (uint32_t)__popcll(__ballot(ok[u] & fail & !over));
+                if (keep) buf[cnt + lanes_below(m)] = pos[u] - first_i;
                 cnt += (uint32_t)__popcll(m);
             }
         }
         if (cnt == 0) break;
+        const KParams &p = fresh_args();
         wave_lds_sync();
         const uint32_t nb = cnt < kTile ? cnt : kTile;
         bool act[kIlp], ok[kIlp];
@@ -2222,7 +2324,7 @@ __device__ __forceinline__ void filter_screened(const KParams &p, const PC &pc, 
             pos[u] = first_i + (act[u] ? buf[j] : 0u);   // (position 0 of the piece for idle lanes)
         }
         decode_cuts<S, R, H, X0>(p, pc, pos, act, ok, asg, r, cut);
-        filter_emit<S, R, AR, kFilterPrefix>(p, tab, b, nq, act, ok, pos, asg, r, cut, n_keep, n_pruned, n_infeas, bad);
+        filter_emit<S, R, AR, SUM, kFilterPrefix>(p, tab, b, nq, act, ok, pos, asg, r, cut, n_keep, n_pruned, n_infeas, bad);
         // the positions past the batch (fewer than kTile) move to the front
         if (cnt > kTile) {
             uint32_t v[kIlp];
@@ -2243,63 +2345,63 @@ __device__ __forceinline__ void filter_screened(const KParams &p, const PC &pc, 
     }
 }
 
-template <int S, typename R, int H, bool AR, int MODE>
+template <int S, typename R, int H, bool AR, bool SUM, int MODE>
 __device__ __forceinline__ void filter_all(const KParams &p, const R *pas, const Ent &tab, uint32_t b,
                                            unsigned int *nq, uint32_t *buf, const unsigned long long *thr,
                                            uint32_t &n_keep, uint32_t &n_pruned, uint32_t &n_infeas, bool &bad) {
     constexpr int X0 = filter_prefix<S>();
-    constexpr int NW = Codes<S>::kWords;
     constexpr int AW = (X0 + 3) / 4;                    // code words of the prefix cuts
     const Pascal<S, R, H, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()> pc(pas);
     if constexpr (filter_screens<S, AR, MODE>()) {
-        filter_screened<S, R, H, AR>(p, pc, tab, b, nq, buf, thr, n_keep, n_pruned, n_infeas, bad);
+        filter_screened<S, R, H, AR, SUM>(p, pc, tab, b, nq, buf, thr, n_keep, n_pruned, n_infeas, bad);
         return;
     }
-    const AList al(p);
     // 32-bit positions and word offsets: a piece holds at most 2^26
     // candidates, a call fewer than 2^32, and each list fewer than 2^32
     // words (fewer scalar registers than 64-bit ones)
     const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap, ccap = (uint32_t)p.ccap;
-    const uint32_t first_i = (uint32_t)p.first_i;
+    const uint32_t lane = threadIdx.x & 63;
     // full, prefix: the piece, kIlp candidates a lane, strided over the grid;
-    // gather: this block's segment of the list, strided over the block
+    // gather: this block's segment of the list, strided over the block.  The
+    // loop runs over whole waves: base is the same for every lane.
     const uint32_t n = MODE == kFilterGather ? p.acount[blockIdx.x] : (uint32_t)p.n_i;
     const uint32_t stride = MODE == kFilterGather ? (uint32_t)kBlock : gridDim.x * kBlock;
-    const uint32_t start = MODE == kFilterGather ? threadIdx.x : blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64;
+    const uint32_t start = MODE == kFilterGather ? wave0 : blockIdx.x * kBlock + wave0;
     for (uint32_t base = start; base < n; base += kIlp * stride) {
+        const KParams &p = fresh_args();
         bool act[kIlp], ok[kIlp];
         uint32_t pos[kIlp];
         uint32_t asg[kIlp], cut[kIlp][S + 1];
         R r[kIlp];
-        if constexpr (MODE == kFilterGather) {
+        if constexpr (MODE != kFilterGather) load_candidates<R>(p, base, stride, lane, act, ok, pos, asg, r);
 #pragma unroll
-            for (int u = 0; u < kIlp; ++u) {
-                const uint32_t i = base + u * stride;
-                act[u] = i < n;
+        for (int u = 0; u < kIlp; ++u) {
+            cut[u][0] = 0;
+            cut[u][S] = p.L;
+            if constexpr (MODE == kFilterGather) {
+                // lanes past the end take the last entry (not counted)
+                const uint32_t i = base + u * stride, wb = min(i, n - 1), l = min(lane, n - 1 - wb);
+                act[u] = i + lane < n;
+                const AList al(p);
+                const uint32_t s0 = seg + wb, o = l << 2;
                 ok[u] = act[u];
-                const uint32_t o = seg + (act[u] ? i : 0);
-                pos[u] = al.pos[o];
-                asg[u] = al.asg[o];
-                r[u] = sizeof(R) == 8 ? (R)(((uint64_t)al.rhi[o] << 32) | al.rlo[o]) : (R)al.rlo[o];
-                uint32_t w[NW];
+                pos[u] = word_at(al.pos + s0, o);
+                asg[u] = word_at(al.asg + s0, o);
+                r[u] = (R)word_at(al.rlo + s0, o);
+                if constexpr (sizeof(R) == 8) r[u] |= (R)((uint64_t)word_at(al.rhi + s0, o) << 32);
+                uint32_t w[AW + 1];
 #pragma unroll
-                for (int k = 0; k < NW; ++k) w[k] = k < AW ? al.w[k * ccap + o] : 0u;
-                cut[u][0] = 0;
-                cut[u][S] = p.L;
+                for (int k = 0; k < AW; ++k) w[k] = word_at(al.w + (k * ccap + s0), o);
 #pragma unroll
                 for (int j = 1; j <= X0; ++j) cut[u][j] = (w[(j - 1) / 4] >> (8 * ((j - 1) % 4))) & 0xFFu;
+            } else {
+                r[u] = decode_start<R>(p, r[u]);
             }
-            decode_range<S, R, H, X0, S - 1>(p, pc, r, cut);
-        } else {
-#pragma unroll
-            for (int u = 0; u < kIlp; ++u) {
-                const uint32_t i = base + u * stride;
-                act[u] = i < n;
-                pos[u] = first_i + (act[u] ? i : 0u);
-            }
-            decode_cuts<S, R, H, MODE == kFilterPrefix ? X0 : S - 1>(p, pc, pos, act, ok, asg, r, cut);
         }
-        filter_emit<S, R, AR, MODE>(p, tab, b, nq, act, ok, pos, asg, r, cut, n_keep, n_pruned, n_infeas, bad);
+        if constexpr (MODE == kFilterGather) decode_range<S, R, H, X0, S - 1>(p, pc, r, cut);
+        else decode_range<S, R, H, 0, MODE == kFilterPrefix ? X0 : S - 1>(p, pc, r, cut);
+        filter_emit<S, R, AR, SUM, MODE>(p, tab, b, nq, act, ok, pos, asg, r, cut, n_keep, n_pruned, n_infeas, bad);
     }
 }
 
@@ -2308,8 +2410,9 @@ __device__ __forceinline__ void filter_all(const KParams &p, const R *pas, const
 // block may use (the largest columns: L > 128 with 64-bit ranks).  LDS:
 // the stage entries first (unless GTAB), then the Pascal columns.
 template <int S, typename R, bool AR, bool GTAB, int MODE>
-__global__ __launch_bounds__(kBlock) void filter_kernel(KParams p) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void filter_kernel(KParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
+    constexpr bool SUM = !AR && !GTAB;   // field kEPf holds Pf + Pb (classify)
     const uint32_t H = decode_levels(p.L);
     Ent tab;
     R *pas;
@@ -2319,6 +2422,11 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(KParams p) {
     } else {
         pas = reinterpret_cast<R *>(smem + p.ent_lds);
         tab = entry_tables(p, smem);
+        if constexpr (SUM) {   // (the barrier after the Pascal columns publishes the sums)
+            uint32_t *e = reinterpret_cast<uint32_t *>(smem);
+            for (uint32_t t = 0; t < p.T; ++t, e += p.erow / 4)
+                for (uint32_t i = threadIdx.x; i < kEntRow; i += kBlock) e[i] += e[i + (kEPb - kEPf) * kEntRow];
+        }
     }
     // bound in force: min(caller's bound, best of the chunks before this one)
     const unsigned long long rb = __hip_atomic_load(p.snap, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2335,25 +2443,26 @@ __global__ __launch_bounds__(kBlock) void filter_kernel(KParams p) {
     if constexpr (filter_screens<S, AR, MODE>()) {
         __shared__ uint32_t screen_buf[kScreenBuf * (kBlock / 64)];
         __shared__ unsigned long long screen_thr[2 * kTypesMax];
-        stage1_limits<S, R>(p, tab, b, screen_thr);
+        if constexpr (SUM) __syncthreads();   // (the sums)
+        stage1_limits<S, R, SUM>(p, tab, b, screen_thr);
         buf = screen_buf + (threadIdx.x >> 6) * kScreenBuf;
         thr = screen_thr;
     }
     switch (H) {
-    case 8: pascal_tables<S, R, 8, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 8, AR, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
-    case 7: pascal_tables<S, R, 7, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 7, AR, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
-    case 6: pascal_tables<S, R, 6, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 6, AR, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
-    default: pascal_tables<S, R, 5, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 5, AR, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
+    case 8: pascal_tables<S, R, 8, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 8, AR, SUM, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
+    case 7: pascal_tables<S, R, 7, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 7, AR, SUM, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
+    case 6: pascal_tables<S, R, 6, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 6, AR, SUM, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
+    default: pascal_tables<S, R, 5, filter_col_lo<S, MODE>(), filter_col_hi<S, MODE>()>(p, pas); __syncthreads(); filter_all<S, R, 5, AR, SUM, MODE>(p, pas, tab, b, &nq, buf, thr, n_keep, n_pruned, n_infeas, bad); break;
     }
-    // per-block sums, one global atomic per counter and block
-    const unsigned long long sk = wave_sum_u32(n_keep), sp = wave_sum_u32(n_pruned), si = wave_sum_u32(n_infeas);
+    // per-block sums (the counts are the waves'), one global atomic per
+    // counter and block
     __shared__ unsigned long long cnt[3];
     if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
-        if (sk) atomicAdd(&cnt[0], sk);
-        if (sp) atomicAdd(&cnt[1], sp);
-        if (si) atomicAdd(&cnt[2], si);
+        if (n_keep) atomicAdd(&cnt[0], (unsigned long long)n_keep);
+        if (n_pruned) atomicAdd(&cnt[1], (unsigned long long)n_pruned);
+        if (n_infeas) atomicAdd(&cnt[2], (unsigned long long)n_infeas);
     }
     __syncthreads();
     if (threadIdx.x < 3 && cnt[threadIdx.x]) atomicAdd(&p.stats[threadIdx.x], cnt[threadIdx.x]);
