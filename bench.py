@@ -426,7 +426,7 @@ def profile_only(args):
 # ------------------------------------------------------------------ summaries
 
 PASS_KERNELS = {
-    "exhaustive": r"pk::(decode_kernel|eval_kernel|sched_kernel|resume_kernel|ilv_kernel|ilv_resume_kernel)",
+    "exhaustive": r"pk::(fused_kernel|closed_kernel|full_kernel|decode_kernel|eval_kernel|ilv_kernel|ilv_resume_kernel)",
     "early_stop": r"pk::(filter_kernel|surv_kernel|fill_u64)",
     "search": r"pk::(search_|fill_u64)",
 }

@@ -189,10 +189,9 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands,
  * POSEIDON_NOALLOC_SCRATCH_BYTES that the library holds once per GPU (from
  * its first poseidon_load_costs on that GPU until the process ends), and it
  * processes the call in chunks sized so that the cut codes and the lists of
- * one chunk fit that array (2^20 candidates per chunk for S = 16 under 1F1B
- * or Eager 1F1B with enough micro-batches for the closed form; more chunks
- * mean more launches
- * than poseidon_eval_candidates needs).  Nothing in the scratch needs clearing:
+ * one chunk fit that array (2^21 candidates per chunk for S = 16 under 1F1B,
+ * 2^20 under Eager 1F1B, with enough micro-batches for the closed form; more
+ * chunks mean more launches than poseidon_eval_candidates needs).  Nothing in the scratch needs clearing:
  * every word a kernel reads was written earlier in the same chunk.  All
  * calls on one GPU share its array, so calls of this function that overlap
  * in time on one GPU (other threads, other streams) race and give wrong

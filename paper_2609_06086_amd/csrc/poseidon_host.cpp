@@ -377,7 +377,7 @@ struct poseidon_ctx {
     uint32_t grid_max;
     uint32_t full_grid;    // blocks of the recurrence pass behind the closed form
     uint32_t fuse_grid;    // blocks of the fused decode and closed form (0: not used)
-    void *ws;              // cut codes + straggler queues of the steady-state cascade
+    void *ws;              // cut codes, lists and queues of the passes (see ensure_workspace)
     uint64_t ws_n;         // candidates per chunk the workspace is for
     uint64_t ws_cap;       // entries of its arrays (ws_n and slack for per-block segments)
     void *sws;             // search frontiers (allocated on the first poseidon_search)

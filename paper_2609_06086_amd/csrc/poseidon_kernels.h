@@ -5,7 +5,9 @@
 // Per lane the path is:
 //   (a1) decode: index -> (composition rank, assignment) -> cut points, types
 //   (a2) stage weights from per-type prefix sums held in LDS, memory check
-//   (a3) the longest path of the 1F1B DAG as a register stencil
+//   (a3) the longest path of the schedule's DAG: its closed form with a
+//        proof (poseidon_closed.h), and a register stencil for the lanes
+//        and problems without one
 //   (a4) a wave / block / grid min-reduction of (makespan, index) keys
 // and, for the early-stop variant, (a5) the Eq. 2 lower bound with
 // block-local compaction of the surviving candidates.
@@ -1018,8 +1020,7 @@ __device__ __forceinline__ void publish_host(const HostOut &h, unsigned long lon
 // Block min of `v`, folded into *acc.  When `finalize` is set (the last
 // kernel of an evaluation chunk), the last block of the grid also moves *acc
 // to *result (or folds it in, for the second and later chunks of a call,
-// and/or into *run_best) and re-arms *acc, *done and the straggler-queue
-// counters.
+// and/or into *run_best) and re-arms *acc and *done.
 __device__ __forceinline__ void block_min_and_finish(unsigned long long v, unsigned long long *acc,
                                                      unsigned int *done, unsigned long long *result,
                                                      unsigned long long *run_best, bool finalize,
@@ -1126,7 +1127,7 @@ __device__ __forceinline__ unsigned long long make_key(bool feasible, uint32_t T
 // kernels
 // ---------------------------------------------------------------------------
 
-// Layout of one straggler queue: idx[cap] | codes[kWords][cap] | asg[cap]
+// Layout of one straggler queue (Interleaved 1F1B): idx[cap] | codes[kWords][cap] | asg[cap]
 // (calls with a list of assignment indices) | Y[NX][cap].  The entry holds
 // the assignment index rather than the next level re-reading it from the
 // caller's list: a 4-byte read at a scattered index costs a whole memory
@@ -1358,9 +1359,9 @@ __device__ __forceinline__ R decode_start(const KParams &p, R r) {
     return (R)(p.n_comp - (uint64_t)r);
 }
 
-// The rank and the assignment index of kIlp list entries, loaded before any
-// is used: candidate() on one after the other waits for memory kIlp times
-// (early stop on 2^26 candidates at S = 8: 587 us so, 491 us loaded together).
+// The checks of kIlp list entries whose ranks and assignment indices were all
+// loaded before: candidate() on one after the other waits for memory kIlp
+// times (early stop on 2^26 candidates at S = 8: 587 us so, 491 us together).
 template <typename R>
 __device__ __forceinline__ void check_entries(const KParams &p, const uint64_t (&rank)[kIlp], const uint32_t (&idx)[kIlp],
                                               const bool (&act)[kIlp], bool (&ok)[kIlp], uint32_t (&asg)[kIlp],
@@ -1956,7 +1957,11 @@ __global__ __launch_bounds__(kBlock) void closed_kernel(KParams p) {
 // checkpoint of the steady part, the ones that have not settled are packed
 // into the block's queue and run to the next, and so on, so that the few
 // long transients share waves.  Queue entries carry position, cut codes,
-// assignment and the DP state; blocks share nothing.
+// assignment and the DP state; blocks share nothing.  Bound by latency: few
+// lanes (0.2-0.5 % of a chunk) on long serial chains, 18 % VALU issue.  It
+// takes 60 us of the 8-stage and 45 us of the 16-stage calls (2^26, 2^24);
+// the launches per checkpoint over the whole chunk's queue that it replaces
+// took 653 and 510 us for the 20 % of lanes the stencil left unsettled.
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void full_kernel(KParams p, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2093,6 +2098,12 @@ __global__ __launch_bounds__(kBlock) void full_kernel(KParams p, uint32_t nseg) 
 // candidates are discarded at one of their first stages, and only the rest
 // pay for the searches of their later cuts.  surv_kernel evaluates the
 // survivor list on the DAG (a3) and folds it into the running best (a4).
+//
+// The prefix pass on 2^26 candidates of 8 stages takes 351 us (394 before):
+// 62 % VALU issue at 130 wave operations a candidate (230 before), and the
+// LDS busy 53 % of the cycles, half of them bank conflicts of the searches'
+// per-lane addresses; its list alone is 155 us of memory.  2^24 of 16 stages
+// 173 us (232 before), the gather passes 64 and 34 us (86 and 44).
 enum FilterMode { kFilterFull = 0, kFilterPrefix = 1, kFilterGather = 2 };
 template <int S>
 __host__ __device__ constexpr int filter_prefix() { return S >= 4 ? S / 2 : 0; }
@@ -2568,6 +2579,8 @@ __device__ __forceinline__ bool closed_or_bound(const KParams &p, const Ent &tab
 // survivors spread over the whole grid, 64 to a wave.  Only the blocks the
 // list needs (one per kBlock survivors, at least one) go on: the others
 // leave before loading the entries and take no ticket on the done counter.
+// Bound by latency (14 % VALU issue: 0.1-0.8 % of the candidates come here):
+// 29 us at 8 stages, 42 us at 16 of calls of 491 and 287 us.
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publish, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];

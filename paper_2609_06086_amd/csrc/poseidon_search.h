@@ -19,13 +19,11 @@
 // block counts into offsets; search_write_kernel writes the children in
 // node order (a block-local scan places each node's range), so the next
 // frontier is again in search order (row, then composition rank).  The
-// level that fixes the last cut (x = S-2) also tests the last stage, which
-// that cut determines, and keeps only the children that pass, so the widest
-// level is never written in full.  When the children of one block always fit
-// a frontier piece, the level before it (x = S-3) is fused with it: the count
-// and write kernels expand each accepted child there at once (its prefix
-// quantities extended by one stage), so the widest level is not written at
-// all.  search_leaf_kernel runs the full DP on the complete configurations.
+// nodes of level S-3 go to search_last_kernel, which expands them through the
+// level that fixes the last cut, tests the last stage, which that cut
+// determines, and evaluates the configurations that pass, so neither of the
+// two widest levels is written.  search_leaf_kernel evaluates the single
+// configurations of S = 1.
 #include "poseidon_kernels.h"
 
 namespace pk {
