@@ -2185,14 +2185,17 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Buffered positions of one wave in the screened prefix mode: fewer than one
 // batch of kIlp * 64 before a screened tile of as many adds to it.
 constexpr uint32_t kScreenBuf = 2 * kIlp * 64;
-// The screen costs a second load of every kept candidate and the buffer's
-// bookkeeping, and saves the prefix work of the ones it discards.  It pays
-// when that work is large: five or more prefix cuts (S >= 10), or stage
-// tests with all-reduce terms (measured: 8 % faster at 16 stages, 6 % at 8
-// stages with all-reduce times, 3.5 % slower at 8 stages without).
+// The screen costs a second load of every kept candidate at a scattered index
+// and the buffer's bookkeeping, and saves the prefix work of the ones it
+// discards.  Early stop on lists of 2^24 (8 stages without all-reduce times:
+// 2^26), us with the screen / without: 6 stages 245 / 229, 8 stages 450 / 473,
+// 10 stages 216 / 218, 12 stages 290 / 266, 16 stages 291 / 260; with
+// all-reduce times 8 stages 205 / 226, 16 stages 351 / 307.  So: four or five
+// prefix cuts, or fewer with the dearer tests; with more cuts the loads and
+// the registers cost more than the searches saved.
 template <int S, bool AR, int MODE>
 __host__ __device__ constexpr bool filter_screens() {
-    return MODE == kFilterPrefix && (filter_prefix<S>() >= 5 || AR);
+    return MODE == kFilterPrefix && filter_prefix<S>() <= 5 && (AR || filter_prefix<S>() >= 4);
 }
 template <int S, bool AR, int MODE>
 __host__ __device__ constexpr size_t filter_static_lds() {
