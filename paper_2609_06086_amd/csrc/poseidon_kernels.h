@@ -517,14 +517,6 @@ __device__ __forceinline__ uint32_t dp_finish_t(const KParams &p, uint32_t (&Y)[
     return T;
 }
 
-template <int S>
-__device__ __forceinline__ void dp_1f1b(uint32_t M, bool u24, const uint32_t (&F)[S], const uint32_t (&B)[S],
-                                        const Comm<S> &c, uint32_t (&Y)[S]) {
-    dp_prologue<S>(Y, F, B, c, u24);
-    for (uint32_t it = S; it < M; ++it) dp_iter<S>(Y, F, B, c);
-    dp_finish<S>(Y, F, B, c);
-}
-
 // The steady iteration is one fixed map Y -> A(Y) built from max and +
 // only, so A(Y + c) = A(Y) + c for every constant c.  Once one iteration
 // raises every stage by the same amount d, every later iteration does the
@@ -787,16 +779,6 @@ __device__ __forceinline__ void eager_unpack(const uint32_t (&X)[2 * S], uint32_
     }
 }
 
-// registers after the whole DP (any M); SCH = the problem is not 1F1B
-template <int S, bool SCH>
-__device__ __forceinline__ void dp_full(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
-                                        const Comm<S> &c, uint32_t (&Y)[S]) {
-    if (SCH && p.nslots) dp_sched<S>(p, F, B, c, Y);
-    else if (SCH) dp_eager<S>(p.M, F, B, c, Y);
-    else if (p.M >= (uint32_t)S) dp_1f1b<S>(p.M, p.g24 != 0, F, B, c, Y);
-    else dp_table<S>(p, F, B, c, Y);
-}
-
 // The whole DP for the few lanes of a wave that survive the early-stop test:
 // the closed forms take the steady-state check every kSurvStep iterations,
 // and the wave leaves the steady loop as soon as all its active lanes have
@@ -967,8 +949,10 @@ __device__ __forceinline__ uint32_t dp_full_settle(const KParams &p, const TAB &
             if (__ballot(done) == act) break;
         }
         return dp_end<S, AR>(p, t, Y, F, B, c, w, a);
+    } else if constexpr (SCH) {
+        dp_sched<S>(p, F, B, c, Y);
     } else {
-        dp_full<S, SCH>(p, F, B, c, Y);
+        dp_table<S>(p, F, B, c, Y);
     }
     return end_time<S, AR>(p, t, Y, c, w, a);
 }
