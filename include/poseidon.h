@@ -263,7 +263,10 @@ int poseidon_argmin(poseidon_ctx *ctx, const uint32_t *makespan, const uint32_t 
  * synchronises the stream wherever it reads a level's size back (levels
  * that may need more than one frontier piece) and at its end.  The frontier
  * memory, 4 Mi partial configurations of (6 + 4 ceil((S-1)/4)) bytes for each
- * of S-2 stages (1.3 GB at S = 16), is allocated on the first call and kept by
+ * of S-2 stages (1.3 GB at S = 16), and, where M is too small for the closed
+ * form of the makespan (1F1B M < 2S + 2, Eager 1F1B M < 4S + 2), a list of
+ * 16 Mi complete configurations of (8 + 4 ceil((S-1)/4)) bytes (0.4 GB), is
+ * allocated on the first call and kept by
  * the context.  The work grows with the pruned tree, which for many stages
  * and a loose bound can be very large (Sec. 4.2.3). */
 enum {

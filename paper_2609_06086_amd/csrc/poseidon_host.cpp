@@ -1321,6 +1321,7 @@ namespace {
 constexpr uint64_t kSearchCap = 1ull << 22;            // nodes per frontier piece
 constexpr uint32_t kSearchBlk = kSearchCap / 256;      // blocks per piece
 static_assert(kSearchBlk <= pk::kSearchScanMax, "a level piece must fit the scan kernel");
+static_assert(kSearchCap <= 1ull << 24, "the last pass's keys hold a node and a cut in 32 bits");
 
 // state words: counters, leaf key, best, bound, one child total per level,
 // then the count kernels' counter slots
@@ -1337,6 +1338,8 @@ struct SearchWs {
     unsigned long long *slot_key;
     uint32_t *slot_row, *slot_w;
     unsigned long long *words;
+    unsigned int *list_n;   // problems without a closed form: the last pass's list
+    uint32_t *list;
 };
 
 // Levels of nodes a search stores: 0 .. S-3, and 0 for S <= 2 (the last pass
@@ -1362,6 +1365,10 @@ SearchWs search_layout(poseidon_ctx *ctx, size_t *bytes) {
     w.slot_row = (uint32_t *)(b + o); o += pk::kSlotMax * 4;
     w.slot_w = (uint32_t *)(b + o); o += words * pk::kSlotMax * 4;
     w.words = (unsigned long long *)(b + o); o += SW_COUNT * 8;
+    if (!ctx->base.closed) {
+        w.list_n = (unsigned int *)(b + o); o += pk::kListParts * 4;
+        w.list = (uint32_t *)(b + o); o += (2 + words) * pk::kListParts * pk::kListCap * 4;
+    }
     if (bytes) *bytes = o;
     return w;
 }
@@ -1372,7 +1379,6 @@ struct SearchRun {
     pk::SearchParams q;
     SearchWs w;
     hipStream_t st;
-    std::vector<unsigned long long> off;
 };
 
 int search_read_total(SearchRun &r, uint32_t x, unsigned long long *total) {
@@ -1403,10 +1409,19 @@ int search_expand(SearchRun &r, uint32_t x, uint64_t n, const unsigned long long
     // the count kernel adds three per-type tables (fb, mfb, hm), the last pass the stage entries behind them
     const size_t tabs = 3 * (size_t)r.ctx->T * (r.ctx->L + 1) * 4;
     if (x + 1 == search_levels(r.ctx)) {
-        // (S > 1: a grid that strides over the piece; a lone stage takes one candidate a thread)
-        const uint32_t lgrid = S > 1 ? std::min(grid, std::min(r.ctx->grid_max, pk::kSlotMax)) : grid;
-        const size_t llds = S > 1 ? lds + ((tabs + 15) & ~(size_t)15) + r.ctx->ent_lds_bytes : lds;
-        if (pk::launch_search(pk::kSearchOpLast, r.kp, q, lgrid, llds, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
+        if (S == 1) {   // one candidate a thread
+            if (pk::launch_search(pk::kSearchOpLast, r.kp, q, grid, lds, r.st) != hipSuccess ||
+                pk::launch_search(pk::kSearchOpMerge, r.kp, q, 1, 0, r.st) != hipSuccess)
+                return POSEIDON_E_DEVICE;
+            return POSEIDON_OK;
+        }
+        // a grid that strides over the nodes, down to one choice of stage S-2 a wave, four waves a block
+        const uint64_t most_items = n * (S > 2 ? r.ctx->L - S + 1 : 1);
+        const uint32_t lgrid = (uint32_t)std::min<uint64_t>((most_items + 3) / 4, std::min(r.ctx->grid_max, pk::kSlotMax));
+        const size_t llds = lds + ((tabs + 15) & ~(size_t)15) + r.ctx->ent_lds_bytes;
+        if (pk::launch_search(pk::kSearchOpLast, r.kp, q, lgrid, llds, r.st) != hipSuccess ||
+            (q.list && pk::launch_search(pk::kSearchOpList, r.kp, q, lgrid, r.ctx->ent_lds_bytes, r.st) != hipSuccess))
+            return POSEIDON_E_DEVICE;
         q.n_in = lgrid;   // (the merge's slots)
         if (pk::launch_search(pk::kSearchOpMerge, r.kp, q, 1, 0, r.st) != hipSuccess) return POSEIDON_E_DEVICE;
         return POSEIDON_OK;
@@ -1503,7 +1518,10 @@ extern "C" int poseidon_search(poseidon_ctx *ctx, uint64_t first_row, uint64_t n
     r.q.slot_row = r.w.slot_row;
     r.q.slot_w = r.w.slot_w;
     r.q.bound = (uint32_t *)(r.w.words + SW_BOUND);
-    if (pk::launch_fill(r.q.stats, 5, 0ull, st) != hipSuccess ||
+    r.q.list_n = r.w.list_n;
+    r.q.list = r.w.list;
+    if ((r.q.list_n && pk::launch_fill((unsigned long long *)r.q.list_n, pk::kListParts / 2, 0ull, st) != hipSuccess) ||
+        pk::launch_fill(r.q.stats, 5, 0ull, st) != hipSuccess ||
         pk::launch_fill(r.q.stats_part, 5 * pk::kStatSlots, 0ull, st) != hipSuccess ||
         pk::launch_fill(r.q.acc, 4, ~0ull, st) != hipSuccess)
         return POSEIDON_E_DEVICE;

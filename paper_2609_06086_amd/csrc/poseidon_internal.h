@@ -185,14 +185,20 @@ struct SearchParams {
     unsigned long long *acc;          // best (T << 32 | node) of a piece of the last pass
     unsigned long long *slot_key;     // [kSlotMax] its blocks' bests, with the configuration that has each
     uint32_t *slot_row, *slot_w;      // [kSlotMax], [words][kSlotMax]
+    unsigned int *list_n;             // [kListParts] entries offered to each part of the list (may exceed its room)
+    uint32_t *list;                   // [2 + words][kListParts kListCap]: node and choice, row, cut codes
     unsigned long long *best;         // makespan, row, composition rank of the best so far
     unsigned long long *total;        // children of the scanned level piece (one word per level)
     uint32_t root_first;              // first row of a root piece
 };
 
-constexpr uint32_t kSlotMax = 2048;   // blocks of the last pass
+constexpr uint32_t kSlotMax = 2048;   // blocks of the last pass and of the list's evaluation
 
-enum SearchOp { kSearchOpCount = 0, kSearchOpWrite = 1, kSearchOpLast = 2, kSearchOpMerge = 3, kSearchOpRoot = 4 };
+// the last pass's list of complete configurations (problems without a closed
+// form), in kListParts parts of kListCap entries (16 Mi in all)
+constexpr uint32_t kListParts = 64, kListCap = 1u << 18;
+
+enum SearchOp { kSearchOpCount = 0, kSearchOpWrite = 1, kSearchOpLast = 2, kSearchOpMerge = 3, kSearchOpRoot = 4, kSearchOpList = 5 };
 
 // Stage entries of the evaluation kernels: per device type a block of
 // field rows of kEntRow uint32 (end points 0..L <= 256, padded), so that a

@@ -920,13 +920,14 @@ __device__ __forceinline__ uint32_t dp_end(const KParams &p, const TAB &t, uint3
 // iterations (the wave leaves the steady loop once all its lanes settled),
 // ending in T (the end node: closed-form drain for 1F1B without all-reduce
 // times, else the full epilogue and the all-reduce nodes).
-template <int S, bool SCH, bool AR, typename TAB>
+// CLOSED: the problem has a closed form (no slot table).
+template <int S, bool SCH, bool AR, bool CLOSED = false, typename TAB>
 __device__ __forceinline__ uint32_t dp_full_settle(const KParams &p, const TAB &t, const uint32_t (&F)[S],
                                                    const uint32_t (&B)[S], const Comm<S> &c,
                                                    const uint32_t (&w)[Codes<S>::kWords], uint32_t a) {
     const unsigned long long act = __ballot(true);
     uint32_t Y[S];
-    if (SCH && !p.nslots) {
+    if (SCH && (CLOSED || !p.nslots)) {
         uint32_t Fn[S], Fp[S];
         eager_prologue<S>(Y, Fn, Fp, F, B, c);
         const uint32_t np = p.M - 2 * S + 1;
@@ -938,7 +939,7 @@ __device__ __forceinline__ uint32_t dp_full_settle(const KParams &p, const TAB &
             if (__ballot(done) == act) break;
         }
         eager_epilogue<S>(Y, Fn, Fp, F, B, c);
-    } else if (!SCH && p.M >= (uint32_t)S) {
+    } else if (!SCH && (CLOSED || p.M >= (uint32_t)S)) {
         dp_prologue<S>(Y, F, B, c, p.g24 != 0);
         const uint32_t nit = p.M - S;
         bool done = false;
@@ -2547,13 +2548,11 @@ __device__ __forceinline__ unsigned long long pend_finish(Pend &l, unsigned long
 }
 
 // One candidate's closed form on its stage weights: true if T is exact,
-// else T is a lower bound (0 without a closed form).
+// else T is a lower bound.
 template <int S, bool AR, bool SCH>
 __device__ __forceinline__ bool closed_or_bound(const KParams &p, const Ent &tab, const uint32_t (&cut)[S + 1],
                                                 const uint32_t (&to)[S], const uint32_t (&F)[S],
                                                 const uint32_t (&B)[S], uint32_t &T) {
-    T = 0;
-    if (!p.closed) return false;
     uint32_t D[S];
     if (AR) stage_allreduce<S>(p, tab, cut, to, D);
     return p.g24 ? closed_form<S, SCH, AR, true>(p, F, B, D, T) : closed_form<S, SCH, AR, false>(p, F, B, D, T);

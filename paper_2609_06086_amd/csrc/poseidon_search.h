@@ -370,9 +370,22 @@ __device__ __forceinline__ uint32_t search_last_range(const KParams &p, const Se
     return h1 + 1 - g0;
 }
 
+// The constant C of a node's g(hi) = C + fb_t[hi] - mfb_tS[hi] (above; the
+// formula itself needs no monotone pair), without all-reduce times.
+struct SearchLast {
+    uint32_t C;
+};
 template <bool AR>
-__device__ __forceinline__ bool search_last_test(const KParams &p, const Lds &tab, const SearchNode &n, uint32_t x,
-                                                 uint32_t hi, uint32_t flags, uint32_t bound, LastStage &lp) {
+__device__ __forceinline__ SearchLast search_last_one(const KParams &p, const SearchTab &sx, const SearchNode &n, uint32_t x) {
+    if constexpr (AR) return SearchLast{0u};
+    const uint32_t row_len = p.L + 1;
+    return SearchLast{n.pre_f - sx.fb[n.t * row_len + n.lo] + (x == 0 ? 0u : n.inner + n.last_b) + sx.mfb[n.tS * row_len + p.L]};
+}
+
+template <bool AR>
+__device__ __forceinline__ bool search_last_test(const KParams &p, const Lds &tab, const SearchTab &sx, const SearchNode &n,
+                                                 const SearchLast &one, uint32_t x, uint32_t hi, uint32_t flags,
+                                                 uint32_t bound, LastStage &lp) {
     const uint32_t row_len = p.L + 1;
     if (flags & kSearchRidge) {
         // type tS's counts with stage x+1 appended when it has that type
@@ -389,15 +402,21 @@ __device__ __forceinline__ bool search_last_test(const KParams &p, const Lds &ta
         }
     }
     if (!(flags & kSearchNoStage)) {
-        const uint64_t *ct = tab.cost + n.t * row_len, *cs = tab.cost + n.tS * row_len;
-        const uint64_t cl = ct[n.lo], cL = cs[p.L], ch = ct[hi], sh = cs[hi];
-        const uint32_t f = (uint32_t)ch - (uint32_t)cl, b = (uint32_t)(ch >> 32) - (uint32_t)(cl >> 32);
-        const uint32_t d = AR ? tab.pd[n.t * row_len + hi] - tab.pd[n.t * row_len + n.lo] : 0u;
-        const uint32_t inn = x == 0 ? d : max(n.inner + n.last_b, d);
-        const uint32_t fS = (uint32_t)cL - (uint32_t)sh, bS = (uint32_t)(cL >> 32) - (uint32_t)(sh >> 32);
-        const uint32_t dS = AR ? tab.pd[n.tS * row_len + p.L] - tab.pd[n.tS * row_len + hi] : 0u;
-        // Eq. 2 for the last stage: g(S_S) = sum_{i<S} F_i + M (F_S + B_S) + max(inner + B_{S-1}, d_S)
-        if (n.pre_f + f + p.M * (fS + bS) + max(inn + b, dS) > bound) {
+        uint32_t g;
+        if constexpr (!AR) {
+            g = one.C + sx.fb[n.t * row_len + hi] - sx.mfb[n.tS * row_len + hi];
+        } else {
+            const uint64_t *ct = tab.cost + n.t * row_len, *cs = tab.cost + n.tS * row_len;
+            const uint64_t cl = ct[n.lo], cL = cs[p.L], ch = ct[hi], sh = cs[hi];
+            const uint32_t f = (uint32_t)ch - (uint32_t)cl, b = (uint32_t)(ch >> 32) - (uint32_t)(cl >> 32);
+            const uint32_t d = tab.pd[n.t * row_len + hi] - tab.pd[n.t * row_len + n.lo];
+            const uint32_t inn = x == 0 ? d : max(n.inner + n.last_b, d);
+            const uint32_t fS = (uint32_t)cL - (uint32_t)sh, bS = (uint32_t)(cL >> 32) - (uint32_t)(sh >> 32);
+            const uint32_t dS = tab.pd[n.tS * row_len + p.L] - tab.pd[n.tS * row_len + hi];
+            // Eq. 2 for the last stage: g(S_S) = sum_{i<S} F_i + M (F_S + B_S) + max(inner + B_{S-1}, d_S)
+            g = n.pre_f + f + p.M * (fS + bS) + max(inn + b, dS);
+        }
+        if (g > bound) {
             lp.bound += 1;
             return false;
         }
@@ -539,40 +558,107 @@ __global__ __launch_bounds__(kBlock) void search_write_kernel(KParams p, SearchP
     }
 }
 
-// The last levels in one pass: the nodes of level S-3 (S >= 3), or S-2
-// (S = 2), are expanded through the level that fixes the last cut, and the
-// complete configurations that pass the last stage are evaluated at once, so
-// the widest level is neither written nor read, needs no frontier memory and
-// no host round trip per piece of it.  Each lane expands one node; the kept
-// end points of one choice of stage S-1 are a run [hi0, hi0 + cnt), and the
-// wave's runs gather in LDS until it hands them out, 64 configurations at a
-// time whichever node they come from.  Most configurations end with their
-// closed form; see Pend for the others.  Ties go to the first in search
-// order: (node, end point of stage S-2's choice, last cut).
-// (Before: a count and a scan of those nodes, then some 90 write launches of
-// 110 us, 90-170 blocks wide each, and as many leaf launches of 42 us; the
-// 8-stage search with 3.8e8 complete configurations took 33.9 ms, now 16.)
-// Held to 128 VGPRs for S <= 8: 299 us a launch against 355 us at the 130 the
-// compiler takes (3 waves a SIMD) and 424 us at 96 (spills).
+// c_{S-1} of complete cut codes
+template <int S>
+__device__ __forceinline__ uint32_t last_cut(const uint32_t (&w)[Codes<S>::kWords]) {
+    return (w[(S - 2) / 4] >> (8 * ((S - 2) % 4))) & 0xFFu;
+}
+
+// The block's best of its threads' bests, (key, last cut) the smallest, with
+// the configuration that has it, to the block's slot.
+template <int S>
+struct BlockBest {
+    unsigned long long key[kWaves];
+    uint32_t sub[kWaves], row[kWaves], w[kWaves][Codes<S>::kWords];
+};
+template <int S>
+__device__ __forceinline__ void block_best(const SearchParams &q, unsigned long long best, uint32_t bsub, uint32_t brow,
+                                           const uint32_t (&bw)[Codes<S>::kWords], BlockBest<S> &sh) {
+    constexpr int NW = Codes<S>::kWords;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long wbest = wave_min(best);
+    uint32_t s = best == wbest ? bsub : 0xFFFFFFFFu;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) s = min(s, (uint32_t)__shfl_xor((int)s, o, 64));
+    const unsigned long long win = __ballot(best == wbest && bsub == s);
+    if (lane == (uint32_t)__ffsll((long long)win) - 1u) {
+        sh.key[wave] = wbest;
+        sh.sub[wave] = s;
+        sh.row[wave] = brow;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) sh.w[wave][k] = bw[k];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int v = 0;
+#pragma unroll
+        for (int k = 1; k < kWaves; ++k) v = sh.key[k] < sh.key[v] || (sh.key[k] == sh.key[v] && sh.sub[k] < sh.sub[v]) ? k : v;
+        q.slot_key[blockIdx.x] = sh.key[v];
+        q.slot_row[blockIdx.x] = sh.row[v];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) q.slot_w[k * kSlotMax + blockIdx.x] = sh.w[v][k];
+        if (sh.key[v] != ~0ull) atomicMin(q.acc, sh.key[v]);
+    }
+}
+
 constexpr uint32_t kRunCap = 192;   // runs a wave gathers: handed out from 128 on
 template <int S>
 struct LastPend {
-    uint32_t row[128], node[128], low[128], w[Codes<S>::kWords][128];
+    uint32_t row[128], at[128], low[128], w[Codes<S>::kWords][128];
 };
 template <int S>
 struct LastLds {
     uint32_t run[kWaves][kRunCap];
     LastPend<S> pend[kWaves];
     unsigned long long known;
-    unsigned long long key[kWaves];
-    uint32_t sub[kWaves], row[kWaves], w[kWaves][Codes<S>::kWords];
+    BlockBest<S> best;
 };
 
-template <int S, bool AR, bool MONO, bool SCH>
+// The last levels in one pass: the nodes of level S-3 (S >= 3), or S-2
+// (S = 2), are expanded through the level that fixes the last cut, and the
+// complete configurations that pass the last stage are evaluated at once, so
+// the widest level is neither written nor read, needs no frontier memory and
+// no host round trip per piece of it.  The kept end points of one choice of
+// stage S-1 are a run [hi0, hi0 + cnt), and the wave's runs gather in LDS
+// until it hands them out, 64 configurations at a time whichever node they
+// come from.  Most configurations end with their closed form; see Pend for
+// the others.  Ties go to the first in search order: (node, end point of
+// stage S-2's choice, last cut).
+//
+// The pass's unit is an item: one of the `parts` equal shares of a node's
+// choices of stage S-2 (choices part + 1, part + 1 + parts, ..).  A wave
+// takes `width` items at a time.  With nodes for every lane of the grid a
+// node is one item.  With fewer, its choices spread over as many lanes as the
+// grid has, and the items over as many waves: one node of a 200-layer model
+// has 2e4 configurations, and a lane that expands them all and a wave that
+// hands them out leave the chip waiting (one row of 3 stages, 574 us so and
+// 81 now; 512 rows of 3 stages and 256 layers with all-reduce times 13.2 and
+// 1.0 ms).  Parts and spread nodes where the grid is full anyway cost more
+// (the 8-stage search below: 18.9 ms with 2 parts, 21 with spread nodes, 17.1):
+// neighbours are alike, and most nodes have few choices.
+//
+// Without a closed form (!CLOSED) a configuration costs its whole recurrence,
+// and the wave whose neighbours are wide would run thousands of them, so the
+// pass writes them to a list that search_list_kernel evaluates with the whole
+// grid (6 stages, 1 micro-batch, 1.4e6 configurations: 1.7 ms a search, 3.8
+// evaluated in place); those that the list has no room for are evaluated here.
+// (Before the pass: a count and a scan of those nodes, then some 90 write
+// launches of 110 us, 90-170 blocks wide each, and as many leaf launches of 42
+// us; the 8-stage search with 3.8e8 complete configurations took 33.9 ms, now
+// 16.)  Held to 128 VGPRs for S <= 8: 299 us a launch of that search against
+// 355 us at the 130 the compiler takes (3 waves a SIMD); 5 waves a SIMD spill
+// in every variant and are slower at every size tried (6 and 8 stages, with
+// and without all-reduce times).  At 128 the common variant of 8 stages has
+// no spills, those with all-reduce times or one-by-one last stages up to 44
+// registers.
+template <int S, bool AR, bool MONO, bool SCH, bool CLOSED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ? 4 : 3, 8))) void search_last_kernel(KParams p, SearchParams q) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t n_in = search_n_in(q);
-    if (blockIdx.x * kBlock >= n_in) {   // past the level's nodes
+    const uint32_t n_in = search_n_in(q), nwave = gridDim.x * kWaves;
+    const uint32_t parts = S >= 3 ? min(max(64 * nwave / max(n_in, 1u), 1u), p.L - S + 1) : 1u;   // (at most L-S+1 choices)
+    const uint32_t items = n_in * parts;   // (at most the larger of n_in and the grid's lanes)
+    const uint32_t width = min(max((items + nwave - 1) / nwave, 1u), 64u);
+    if (blockIdx.x * kWaves * width >= items) {   // past the level's nodes
         if (threadIdx.x == 0) q.slot_key[blockIdx.x] = ~0ull;
         return;
     }
@@ -593,22 +679,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
     __syncthreads();
     uint32_t *run = sh.run[wave];
     LastPend<S> &pend = sh.pend[wave];
-    uint32_t nrun = 0, npend = 0;   // (wave-uniform)
-    // the thread's best: (T << 32 | node), then the two cuts, then what names it
+    uint32_t nrun = 0, npend = CLOSED ? 0u : blockIdx.x * kWaves + wave;   // (wave-uniform)
+    // the thread's best: (T << 32 | node << 8 | end point of stage S-2's choice), then
+    // the last cut, then what names it
     unsigned long long best = ~0ull;
     uint32_t bsub = 0, brow = 0, bw[NW];
 #pragma unroll
     for (int k = 0; k < NW; ++k) bw[k] = 0;
-    auto sub_of = [](const uint32_t (&w)[NW]) __attribute__((always_inline)) {   // the cuts the pass fixed, the first most significant
-        uint32_t v = 0;
-#pragma unroll
-        for (int j = (S >= 3 ? S - 2 : 1); j <= S - 1; ++j) v = v << 8 | ((w[(j - 1) / 4] >> (8 * ((j - 1) % 4))) & 0xFFu);
-        return v;
-    };
-    auto offer = [&](uint32_t T, uint32_t node, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
-        const unsigned long long key = make_key(true, T, node);
+    auto offer = [&](uint32_t T, uint32_t at, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
+        const unsigned long long key = make_key(true, T, at);
         if (key > best) return;
-        const uint32_t sub = sub_of(w);
+        const uint32_t sub = last_cut<S>(w);
         if (key == best && sub >= bsub) return;
         best = key;
         bsub = sub;
@@ -627,12 +708,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
             unpack_cuts<S>(w, p.L, cut);
             decode_toff<S>(p, ent_tab, row, to);
             stage_weights<S>(p, ent_tab, cut, to, F, B);
-            offer(dp_full_settle<S, SCH, AR>(p, ent_tab, F, B, comm, w, row), pend.node[e], row, w);
+            offer(dp_full_settle<S, SCH, AR, true>(p, ent_tab, F, B, comm, w, row), pend.at[e], row, w);
         }
         wave_lds_sync();
     };
-    // hand out the gathered runs (row, w: the lanes' nodes base + lane)
-    auto hand_out = [&](uint32_t base, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
+    // hand out the gathered runs (node, row, w: the lanes' nodes)
+    auto hand_out = [&](uint32_t node, uint32_t row, const uint32_t (&w)[NW]) __attribute__((always_inline)) {
         wave_lds_sync();
         for (uint32_t r0 = 0; r0 < nrun; r0 += 64) {
             const uint32_t rw = r0 + lane < nrun ? run[r0 + lane] : 0u, cnt = rw >> 22;
@@ -643,6 +724,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
                 if (lane >= (uint32_t)o) incl += u;
             }
             const uint32_t total = __shfl(incl, 63, 64);
+            uint32_t slot = 0, lpart = 0;
+            if constexpr (!CLOSED) {   // room for all of them in one part of the list (the parts in turn)
+                lpart = npend++ % kListParts;
+                if (lane == 0) slot = atomicAdd(&q.list_n[lpart], total);
+                slot = __builtin_amdgcn_readfirstlane(slot);
+            }
             for (uint32_t o0 = 0; o0 < total; o0 += 64) {
                 const uint32_t o = o0 + lane;
                 uint32_t pl = 0;   // the run that holds configuration o: the first whose inclusive count exceeds it
@@ -653,6 +740,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
                 const uint32_t rp = __shfl(rw, (int)pl, 64), first = __shfl(incl - cnt, (int)pl, 64);
                 const uint32_t src = rp & 63u, hi = ((rp >> 14) & 0xFFu) + (on ? o - first : 0u);
                 const uint32_t prow = __shfl(row, (int)src, 64);
+                const uint32_t at = __shfl(node, (int)src, 64) << 8 | ((rp >> 6) & 0xFFu);
                 uint32_t pw[NW];
 #pragma unroll
                 for (int k = 0; k < NW; ++k) pw[k] = __shfl(w[k], (int)src, 64);
@@ -662,19 +750,39 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
                 } else {
                     pw[0] |= hi;
                 }
+                bool eval = on;
+                if constexpr (!CLOSED) {
+                    // to the list, while its part has room
+                    eval = on && slot + o >= kListCap;
+                    if (on && !eval) {
+                        uint32_t *l = q.list + lpart * kListCap + slot + o;
+                        l[0] = at;
+                        l[kListParts * kListCap] = prow;
+#pragma unroll
+                        for (int k = 0; k < NW; ++k) l[(2 + k) * kListParts * kListCap] = pw[k];
+                    }
+                    if (__ballot(eval) == 0) continue;
+                }
                 uint32_t cut[S + 1], to[S], F[S], B[S], T;
                 unpack_cuts<S>(pw, p.L, cut);
                 decode_toff<S>(p, ent_tab, prow, to);
                 stage_weights<S>(p, ent_tab, cut, to, F, B);
+                if constexpr (!CLOSED) {
+                    if (eval) {
+                        T = dp_full_settle<S, SCH, AR>(p, ent_tab, F, B, comm, pw, prow);
+                        if (T <= bound) offer(T, at, prow, pw);
+                    }
+                    continue;
+                }
                 const bool proven = closed_or_bound<S, AR, SCH>(p, ent_tab, cut, to, F, B, T);
-                if (on && proven && T <= bound) offer(T, base + src, prow, pw);
+                if (on && proven && T <= bound) offer(T, at, prow, pw);
                 const bool keep = on && !proven && (unsigned long long)T << 32 <= sh.known;
                 const unsigned long long m = __ballot(keep);
                 if (m) {
                     if (keep) {
                         const uint32_t e = npend + (uint32_t)__popcll(m & lanes_below);
                         pend.row[e] = prow;
-                        pend.node[e] = base + src;
+                        pend.at[e] = at;
                         pend.low[e] = T;
 #pragma unroll
                         for (int k = 0; k < NW; ++k) pend.w[k][e] = pw[k];
@@ -692,11 +800,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
     };
     uint32_t visited = 0, why_mem = 0, why_ridge = 0, why_bound = 0;
     LastStage lp;
-    for (uint32_t base = blockIdx.x * kBlock + wave * 64; base < n_in; base += gridDim.x * kBlock) {   // (wave-uniform)
-        const uint32_t i = base + lane;
-        const bool active = i < n_in;
+    for (uint32_t base = (blockIdx.x * kWaves + wave) * width; base < items; base += nwave * width) {   // (wave-uniform)
+        const bool active = lane < width && base + lane < items;
+        const uint32_t node = active ? (base + lane) / parts : 0u, part = active ? base + lane - node * parts : 0u;
         uint32_t row, w[NW], ty[S], cut[S + 1];
-        search_load<S>(q, i, active, row, w);
+        search_load<S>(q, node, active, row, w);
         const SearchNode n = search_node<S, AR>(p, tab, row, w, x, ty, cut);
         auto add_run = [&](bool want, uint32_t c, uint32_t hi0, uint32_t cnt) __attribute__((always_inline)) {
             const unsigned long long m = __ballot(want);
@@ -714,25 +822,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
             if (on && range) cnt = search_last_range(p, sx, m, lx, h0, h1, q.flags, bound, lp, g0);
             add_run(cnt != 0, c, g0, cnt);
             if constexpr (AR || !MONO) {
+                // one by one; consecutive end points that pass make a run
+                const SearchLast one = search_last_one<AR>(p, sx, m, lx);
+                cnt = 0;
                 for (uint32_t hi = h0; __ballot(on && !range && hi <= h1); ++hi) {
-                    const bool t = on && !range && hi <= h1;
-                    if (nrun > kRunCap - 64) hand_out(base, row, w);
-                    add_run(t && search_last_test<AR>(p, tab, m, lx, hi, q.flags, bound, lp), c, hi, 1u);
+                    const bool t = on && !range && hi <= h1 && search_last_test<AR>(p, tab, sx, m, one, lx, hi, q.flags, bound, lp);
+                    const bool flush = cnt != 0 && !t;
+                    if (nrun > kRunCap - 64) hand_out(node, row, w);
+                    add_run(flush, c, g0, cnt);
+                    g0 = cnt == 0 ? hi : g0;
+                    cnt = t ? cnt + 1 : 0u;
                 }
+                if (nrun > kRunCap - 64) hand_out(node, row, w);
+                add_run(cnt != 0, c, g0, cnt);
             }
         };
         const uint32_t hmax = p.L - (S - 1 - x);   // every later stage keeps one layer
         const uint32_t acc = active ? search_accepted<AR>(p, tab, sx, n, x, hmax, q.flags, bound) : 0u;
-        // the rule that stopped the range (0: it ran to its structural end)
-        const int why = active ? search_stop<AR>(p, tab, sx, n, x, acc, hmax, q.flags, bound) : 0;
-        visited += acc;
+        // the rule that stopped the range (0: it ran to its structural end), counted by the node's first item
+        const bool first = active && part == 0;
+        const int why = first ? search_stop<AR>(p, tab, sx, n, x, acc, hmax, q.flags, bound) : 0;
+        visited += first ? acc : 0u;
         why_mem += why == 1;
         why_ridge += why == 2;
         why_bound += why == 3;
         // (the runs are handed out when the next choice's might not fit, and
         // at the end, before the lanes move on to other nodes)
-        for (uint32_t k = 1;; ++k) {
-            const bool more = S >= 3 ? __ballot(k <= acc) != 0 : k == 1;
+        for (uint32_t k = 1 + part;; k += parts) {
+            const bool more = S >= 3 ? __ballot(k <= acc) != 0 : k == 1;   // (S = 2: one part)
             if (more) {
                 if constexpr (S >= 3) {
                     const bool on = k <= acc;
@@ -753,7 +870,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
                     last_children(active, n, x, acc, 0u);
                 }
             }
-            if (!more || nrun > kRunCap - 64) hand_out(base, row, w);
+            if (!more || nrun > kRunCap - 64) hand_out(node, row, w);
             if (!more) break;
         }
     }
@@ -761,36 +878,82 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
     __syncthreads();
     if (threadIdx.x == 0) atomicMin(&sh.known, __hip_atomic_load(q.acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     __syncthreads();
-    run_pend(0u, npend);
+    if constexpr (CLOSED) run_pend(0u, npend);
     // a makespan from the recurrence can lie above the bound
     if ((uint32_t)(best >> 32) > bound) best = ~0ull;
     // a configuration that passes the last stage counts as visited twice (its
     // stages S-1 and S) and evaluated
     search_block_counts(q, visited + lp.pass, lp.pass, why_mem + lp.mem, why_ridge + lp.ridge, why_bound + lp.bound);
-    // the block's best, with the configuration that has it (nodes are not
-    // shared between waves, so only lanes of one wave can tie on the key)
-    const unsigned long long wbest = wave_min(best);
-    uint32_t s = best == wbest ? bsub : 0xFFFFFFFFu;
+    block_best<S>(q, best, bsub, brow, bw, sh.best);
+}
+
+// Problems without a closed form: the list's configurations by the
+// recurrence, 64 to a wave, over the whole grid.
+template <int S, bool AR, bool SCH>
+__global__ __launch_bounds__(kBlock) void search_list_kernel(KParams p, SearchParams q) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ BlockBest<S> bb;
+    constexpr int NW = Codes<S>::kWords;
+    const uint32_t lane = threadIdx.x & 63, bound = *q.bound;
+    static_assert(kListParts == 64, "a lane per part");
+    uint32_t incl = min(q.list_n[lane], kListCap);
+    const uint32_t mine = incl;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s = min(s, (uint32_t)__shfl_xor((int)s, o, 64));
-    const unsigned long long win = __ballot(best == wbest && bsub == s);
-    if (lane == (uint32_t)__ffsll((long long)win) - 1u) {
-        sh.key[wave] = wbest;
-        sh.row[wave] = brow;
-#pragma unroll
-        for (int k = 0; k < NW; ++k) sh.w[wave][k] = bw[k];
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o, 64);
+        if (lane >= (uint32_t)o) incl += u;
     }
-    __syncthreads();
+    const uint32_t n = __shfl(incl, 63, 64);
+    if (blockIdx.x * kBlock >= n) return;   // (block-uniform; the slot keeps the last pass's best)
+    const Ent tab = entry_tables(p, smem);
+    const Comm<S> comm = load_comm<S>(p);
+    unsigned long long best = ~0ull;
+    uint32_t bsub = 0, brow = 0, bw[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) bw[k] = 0;
+    for (uint32_t k0 = blockIdx.x * kBlock + (threadIdx.x - lane); k0 < n; k0 += gridDim.x * kBlock) {   // (wave-uniform)
+        const uint32_t o = k0 + lane;
+        uint32_t pl = 0;   // the part that holds entry o
+#pragma unroll
+        for (uint32_t b = 32; b; b >>= 1) pl = __shfl(incl, (int)(pl + b - 1), 64) <= o ? pl + b : pl;
+        pl = o < n ? pl : 0u;
+        const uint32_t first = __shfl(incl - mine, (int)pl, 64);
+        if (o >= n) continue;
+        const uint32_t *l = q.list + pl * kListCap + (o - first);
+        const uint32_t at = l[0], row = l[kListParts * kListCap];
+        uint32_t w[NW], cut[S + 1], to[S], F[S], B[S];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = l[(2 + k) * kListParts * kListCap];
+        unpack_cuts<S>(w, p.L, cut);
+        decode_toff<S>(p, tab, row, to);
+        stage_weights<S>(p, tab, cut, to, F, B);
+        const uint32_t T = dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, row);
+        if (T > bound) continue;
+        const unsigned long long key = make_key(true, T, at);
+        const uint32_t sub = last_cut<S>(w);
+        if (key < best || (key == best && sub < bsub)) {
+            best = key;
+            bsub = sub;
+            brow = row;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) bw[k] = w[k];
+        }
+    }
+    // the slot holds the last pass's best of that block: the better one stays
     if (threadIdx.x == 0) {
-        int v = 0;
+        const unsigned long long key = q.slot_key[blockIdx.x];
+        uint32_t w[NW];
 #pragma unroll
-        for (int k = 1; k < kWaves; ++k) v = sh.key[k] < sh.key[v] ? k : v;
-        q.slot_key[blockIdx.x] = sh.key[v];
-        q.slot_row[blockIdx.x] = sh.row[v];
+        for (int k = 0; k < NW; ++k) w[k] = q.slot_w[k * kSlotMax + blockIdx.x];
+        if (key < best || (key == best && key != ~0ull && last_cut<S>(w) < bsub)) {
+            best = key;
+            bsub = last_cut<S>(w);
+            brow = q.slot_row[blockIdx.x];
 #pragma unroll
-        for (int k = 0; k < NW; ++k) q.slot_w[k * kSlotMax + blockIdx.x] = sh.w[v][k];
-        if (sh.key[v] != ~0ull) atomicMin(q.acc, sh.key[v]);
+            for (int k = 0; k < NW; ++k) bw[k] = w[k];
+        }
     }
+    block_best<S>(q, best, bsub, brow, bw, bb);
 }
 
 // A lone stage (S = 1): one configuration per row, tested here like any
@@ -826,10 +989,13 @@ __global__ __launch_bounds__(kBlock) void search_leaf_kernel(KParams p, SearchPa
 // the one at that position).
 template <typename R>
 __global__ __launch_bounds__(kBlock) void search_merge_kernel(KParams p, SearchParams q, uint32_t nslot) {
-    const unsigned long long key = *q.acc;
+    const unsigned long long key = *q.acc, had = q.best[0];
+    __shared__ uint32_t slot;
+    if (threadIdx.x == 0) slot = 0xFFFFFFFFu;
     __syncthreads();
     if (threadIdx.x == 0) *q.acc = ~0ull;
-    if (key == ~0ull || (key >> 32) >= q.best[0]) return;
+    if (q.list_n && threadIdx.x < kListParts) q.list_n[threadIdx.x] = 0u;
+    if (key == ~0ull || (key >> 32) >= had) return;   // (the same for every thread)
     const uint32_t S = p.S, L = p.L;
     uint64_t rank = 0;
     uint32_t row = 0;
@@ -837,9 +1003,14 @@ __global__ __launch_bounds__(kBlock) void search_merge_kernel(KParams p, SearchP
         if (threadIdx.x != 0) return;
         row = q.in_row[(uint32_t)key];
     } else {
-        uint32_t b = threadIdx.x;
-        while (b < nslot && q.slot_key[b] != key) b += kBlock;
-        if (b >= nslot) return;   // (one thread goes on: a node is one block's)
+        // the slot with that key (of equal ones the smallest last cut)
+        auto last = [&](uint32_t b) { return (q.slot_w[((S - 2) >> 2) * kSlotMax + b] >> (8 * ((S - 2) & 3))) & 0xFFu; };
+        static_assert(kSlotMax <= 1u << 16, "a slot in 16 bits");
+        for (uint32_t b = threadIdx.x; b < nslot; b += kBlock)
+            if (q.slot_key[b] == key) atomicMin(&slot, last(b) << 16 | b);
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        const uint32_t b = slot & 0xFFFFu;
         row = q.slot_row[b];
         const R *binom = reinterpret_cast<const R *>(p.binom);
         // rank = sum_j C(L - 1 - c_{j-1}, S - j) - C(L - c_j, S - j)   (hockey-stick identity)
@@ -883,9 +1054,16 @@ hipError_t launch_search_s(int op, const KParams &p, const SearchParams &q, uint
             if constexpr (S == 1) {
                 hipLaunchKernelGGL((search_leaf_kernel<ar, sch>), g, b, lds, st, p, q);
             } else {
-                if (!ar && p.g_mono_all) hipLaunchKernelGGL((search_last_kernel<S, ar, !ar, sch>), g, b, lds, st, p, q);
-                else hipLaunchKernelGGL((search_last_kernel<S, ar, false, sch>), g, b, lds, st, p, q);
+                if (!p.closed) hipLaunchKernelGGL((search_last_kernel<S, ar, false, sch, false>), g, b, lds, st, p, q);
+                else if (!ar && p.g_mono_all) hipLaunchKernelGGL((search_last_kernel<S, ar, !ar, sch, true>), g, b, lds, st, p, q);
+                else hipLaunchKernelGGL((search_last_kernel<S, ar, false, sch, true>), g, b, lds, st, p, q);
             }
+            return hipGetLastError();
+        });
+    case kSearchOpList:
+        return with_variant(p, [&](auto arc, auto schc) {
+            if constexpr (S > 1)
+                hipLaunchKernelGGL((search_list_kernel<S, decltype(arc)::value, decltype(schc)::value>), g, b, lds, st, p, q);
             return hipGetLastError();
         });
     case kSearchOpMerge: hipLaunchKernelGGL((search_merge_kernel<R>), dim3(1), dim3(kBlock), 0, st, p, q, q.n_in); break;

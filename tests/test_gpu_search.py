@@ -198,3 +198,58 @@ def test_search_workload4_full_golden(dev):
                 (g["visited"], g["evaluated"], g["pruned_memory"], g["pruned_ridge"], g["pruned_bound"])
     finally:
         ctx.close()
+
+
+def test_search_few_wide_nodes_use_the_chip(dev):
+    """One row of 3 stages and 200 layers: a single node above the last pass with 19,701 complete
+    configurations.  Its choices spread over the grid, so the search costs a few launches, as evaluating the
+    same candidates does (measured 2x that call; 14x when one lane expands the node and one wave evaluates
+    what it finds)."""
+    import time
+    prob = W.random_problem(np.random.default_rng(130), 200, 3, 40, 1, cost_lo=500, mem_hi=10, cap=10 ** 6,
+                            assign_rows=1)
+    check(prob, 2 ** 31 - 1, dev)
+    ctx = P.poseidon_load_costs(prob, 0)
+
+    def best_time(f):
+        f()
+        t = []
+        for _ in range(30):
+            t0 = time.perf_counter()
+            f()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+    ev = best_time(lambda: P.poseidon_eval_candidates(ctx, first=0, count=prob.n_candidates))
+    se = best_time(lambda: P.poseidon_search(ctx))
+    ctx.close()
+    assert se < 6 * ev, (se, ev)
+
+
+@pytest.mark.parametrize("S,L,M,rows", [(2, 250, 3, 3), (3, 256, 2, 700), (3, 40, 5, 9), (4, 60, 4, 1), (6, 24, 3, 7)])
+def test_search_list_of_configurations(dev, S, L, M, rows):
+    """Problems without a closed form: complete configurations go to the list (and beyond its room, at 700 rows of
+    32,385, are evaluated in place).  Every row but the last is the same slow type, so the counters are the oracle's
+    of one row times the rows, the first optimum of the slow rows is row 0's and, with the fast type, the last
+    row's, which the pass reaches when the list is full."""
+    rng = np.random.default_rng(131 + S)
+    for schedule in (P.SCHEDULE_1F1B, P.SCHEDULE_EAGER_1F1B):
+        prob = W.random_problem(rng, L, S, M, 2, cost_lo=1, cost_hi=4, comm_hi=2, mem_hi=5, cap=10 ** 6)
+        prob.fwd[1], prob.bwd[1] = prob.fwd[0] + 3, prob.bwd[0] + 3
+        prob.schedule = schedule
+        for last in (1, 0):
+            prob.assign = np.full((rows, S), 1, np.uint8)
+            prob.assign[-1] = last
+            ctx = P.poseidon_load_costs(prob, 0)
+            for ridge in (False, True):
+                b, st = P.poseidon_search(ctx, ridge=ridge)
+                got = np.array([st.visited, st.evaluated, st.pruned_memory, st.pruned_ridge, st.pruned_bound])
+                want, best = 0, None
+                for row, times in ((0, rows - 1), (rows - 1, 1)):
+                    o = coracle.search(prob, 2 ** 31 - 1, first_row=row, n_rows=1, ridge=ridge)
+                    want = want + times * np.array([o[k] for k in ("visited", "evaluated", "pruned_memory",
+                                                                   "pruned_ridge", "pruned_bound")])
+                    if times and o["best"] and (best is None or o["best"][1] < best[1]):
+                        best = o["best"]
+                assert np.array_equal(got, want), (got, want)
+                assert (b.index, b.makespan) == best, (last, ridge)
+            ctx.close()
