@@ -46,9 +46,15 @@
 // whenever no boundary weighs more than a stage's F or B.  The bounds on M
 // leave room for the walks between stages.
 //
-// Lanes without proof are evaluated by the recurrence.  On the synthetic
-// workloads (16 and 8 stages, 2-4 device types) 99.5 - 99.8 % of the
-// candidates have one, also when every layer costs the same.
+// Lanes without proof are evaluated by the recurrence.  How many those are
+// depends on the transfers.  1F1B, 16 and 8 stages of some 8-10 layers:
+// 0.2-0.5 % at cf + cb of a tenth to a third of a layer (also when every layer
+// costs the same), 5 and 2 % at 1-3 layers, 30 and 19 % at 3-10.  Eager 1F1B's
+// condition is the stricter one, over all stages and boundaries at once: none
+// while no boundary outweighs the lightest layer on the fastest type, 9 % of
+// the 16-stage synthetic workload, where some do, 88 and 53 % at a third of a
+// layer to one, and nearly all beyond.  (The value itself is exact for almost
+// all of them.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -61,9 +67,15 @@ namespace pk {
 // and branch once on it, so that no select merges the two products into one
 // slow 32-bit multiply.
 template <bool U24>
-__device__ __forceinline__ uint32_t mul_small(uint32_t x, uint32_t k) {
+__host__ __device__ __forceinline__ uint32_t mul_small(uint32_t x, uint32_t k) {
+#if defined(__HIP_DEVICE_COMPILE__)
     return U24 ? __umul24(x, k) : x * k;
+#else
+    return x * k;   // (both products are below 2^32)
+#endif
 }
+__host__ __device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__host__ __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 // m_x - 1 of 0-based stage x
 template <int S, bool EAGER>
@@ -84,6 +96,33 @@ struct ClosedConst {
     __device__ __forceinline__ uint32_t at(int x) const { return c[ROW * kSMax + x]; }
 };
 
+// The same in host memory.
+struct ClosedConstHost {
+    const uint32_t *c;
+    explicit ClosedConstHost(const KParams &p) : c(p.ctab) {}
+    template <int ROW>
+    uint32_t at(int x) const { return c[ROW * kSMax + x]; }
+};
+
+// The constants of a problem (host): fills ctab, and edge_max of p, from
+// p.S, p.M, p.cf, p.cb and p.closed.
+inline void closed_constants(KParams &p, uint32_t (&ctab)[kCRows * kSMax]) {
+    for (uint32_t &v : ctab) v = 0;
+    p.edge_max = 0;
+    for (uint32_t s = 0; s < p.S; ++s) {
+        auto row = [&](int r) { return ctab + (size_t)r * kSMax; };
+        const uint32_t lo = s > 0 ? row(kCE)[s - 1] : 0u, hi = s + 1 < p.S ? p.cf[s] + p.cb[s] : 0u;
+        row(kCE)[s] = hi;
+        row(kCSum)[s] = s > 0 ? row(kCSum)[s - 1] + lo : 0u;
+        row(kCE2)[s] = lo + hi;
+        // (1F1B, M > S; at most M times the boundaries' sum, below 2^31)
+        if (p.closed) row(kCE2n)[s] = (p.M - p.S + 1 + s) * (lo + hi);
+        row(kCCb)[s] = s + 1 < p.S ? p.cb[s] : 0u;
+        row(kCPsi)[s] = s > 0 ? row(kCPsi)[s - 1] + p.cb[s - 1] : 0u;
+        p.edge_max = umax(p.edge_max, hi);
+    }
+}
+
 // T = max_x T_x of one candidate (D: all-reduce weights, with AR); returns
 // whether it is proven to be the makespan.
 //
@@ -91,10 +130,10 @@ struct ClosedConst {
 // above their stage: U less Phi_x = cf_0 + .. + cf_{x-1}, V less Psi_x =
 // cb_0 + .. + cb_{x-1}.  An input from the stage below then carries e_x, and
 // T_x gains Phi_x + Psi_x = e_0 + .. + e_{x-1}.
-template <int S, bool EAGER, bool AR, bool U24>
-__device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
+template <int S, bool EAGER, bool AR, bool U24, typename CONST = ClosedConst>
+__host__ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F)[S], const uint32_t (&B)[S],
                                             const uint32_t (&D)[S], uint32_t &T) {
-    const ClosedConst cc(p);
+    const CONST cc(p);
     // P[x] = Fw_x (later T_x), X[x] = the drain of stage x from the start of
     // its first backward
     uint32_t P[S], X[S];
@@ -103,7 +142,7 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
 #pragma unroll
         for (int x = 0; x < S; ++x) {
             pre += F[x];
-            mx = max(mx, F[x]);
+            mx = umax(mx, F[x]);
             P[x] = pre + mul_small<U24>(mx, warm_steps<S, EAGER>(x));
         }
     }
@@ -114,17 +153,17 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
             const uint32_t h = warm_steps<S, EAGER>(x);
             pre += B[x];
             if constexpr (!AR) {
-                mx = max(mx, B[x]);
+                mx = umax(mx, B[x]);
                 X[x] = pre + mul_small<U24>(mx, h);
             } else {
                 // A[j] + h B_j (+ the path down to stage j): the drain that
                 // takes its h free steps at stage j and then goes on to the
                 // heaviest R
-                tail = x == 0 ? D[0] : max(D[x], tail + B[x > 0 ? x - 1 : 0] + cc.at<kCCb>(x > 0 ? x - 1 : 0));
-                A[x] = tail + B[x] - pre - cc.at<kCPsi>(x);
+                tail = x == 0 ? D[0] : umax(D[x], tail + B[x > 0 ? x - 1 : 0] + cc.template at<kCCb>(x > 0 ? x - 1 : 0));
+                A[x] = tail + B[x] - pre - cc.template at<kCPsi>(x);
                 uint32_t m = 0;
 #pragma unroll
-                for (int j = 0; j <= x; ++j) m = max(m, A[j] + mul_small<U24>(B[j], h));
+                for (int j = 0; j <= x; ++j) m = umax(m, A[j] + mul_small<U24>(B[j], h));
                 X[x] = pre + m;
             }
         }
@@ -135,20 +174,20 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
     for (int x = S - 1; x >= 0; --x) {
         if (x < S - 1) {
             const int b = x + 1 < S ? x + 1 : 0;   // the stage below
-            u = max(P[x], u + B[b] + cc.at<kCE>(x));
-            v = max(X[x], v + F[b] + cc.at<kCE>(x));
+            u = umax(P[x], u + B[b] + cc.template at<kCE>(x));
+            v = umax(X[x], v + F[b] + cc.template at<kCE>(x));
         }
         const uint32_t r = F[x] + B[x];
         P[x] = u + mul_small<U24>(r, p.M - 1 - warm_steps<S, EAGER>(x));
-        P[x] += v + cc.at<kCSum>(x);
-        Tm = max(Tm, P[x]);
-        rm = max(rm, r);
+        P[x] += v + cc.template at<kCSum>(x);
+        Tm = umax(Tm, P[x]);
+        rm = umax(rm, r);
     }
     T = Tm;
     if constexpr (EAGER) {
-        uint32_t mn = min(F[0], B[0]);
+        uint32_t mn = umin(F[0], B[0]);
 #pragma unroll
-        for (int x = 1; x < S; ++x) mn = min(mn, min(F[x], B[x]));
+        for (int x = 1; x < S; ++x) mn = umin(mn, umin(F[x], B[x]));
         return mn >= p.edge_max;
     } else {
         bool K[S];
@@ -157,13 +196,13 @@ __device__ __forceinline__ bool closed_form(const KParams &p, const uint32_t (&F
         for (int x = 0; x < S; ++x) {
             const uint32_t r = F[x] + B[x];
             // (bitwise throughout: no branch per stage)
-            K[x] = (int)(P[x] + cc.at<kCE2n>(x) >= Tm) | (int)(r + cc.at<kCE2>(x) >= rm);
-            low = min(low, K[x] ? r : 0xFFFFFFFFu);
+            K[x] = (int)(P[x] + cc.template at<kCE2n>(x) >= Tm) | (int)(r + cc.template at<kCE2>(x) >= rm);
+            low = umin(low, K[x] ? r : 0xFFFFFFFFu);
         }
         bool ok = true;
 #pragma unroll
         for (int x = 0; x < S; ++x) {
-            ok &= (bool)((int)K[x] | (int)(F[x] + B[x] + cc.at<kCE2>(x) <= low));
+            ok &= (bool)((int)K[x] | (int)(F[x] + B[x] + cc.template at<kCE2>(x) <= low));
             if (x > 0) ok &= !((int)K[x] & (int)K[x > 0 ? x - 1 : 0]);
         }
         return ok;

@@ -49,6 +49,8 @@ size_t noalloc_scratch_bytes() { return sizeof(scratch); }
 #define PK_EXTERN(S)                                                                                                  \
     extern template hipError_t launch_eval_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     extern template hipError_t launch_closed_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                       \
+    extern template hipError_t launch_cascade_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                      \
+    extern template hipError_t cascade_occupancy_s<S>(const KParams &, size_t, int *);                                    \
     extern template hipError_t launch_full_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     extern template hipError_t launch_fused_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
     extern template hipError_t launch_fused_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
@@ -197,6 +199,14 @@ hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st) 
 
 hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
     PK_DISPATCH_S(launch_closed_s, p.S, p, lc, st)
+}
+
+hipError_t launch_cascade(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    PK_DISPATCH_S(launch_cascade_s, p.S, p, lc, st)
+}
+
+hipError_t cascade_occupancy(const KParams &p, size_t lds, int *blocks) {
+    PK_DISPATCH_S(cascade_occupancy_s, p.S, p, lds, blocks)
 }
 
 hipError_t launch_fused(const KParams &p, const LaunchCfg &lc, hipStream_t st) {

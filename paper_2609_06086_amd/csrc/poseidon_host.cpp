@@ -17,6 +17,7 @@
 
 #include "../../include/poseidon.h"
 #include "poseidon_internal.h"
+#include "poseidon_share.h"
 
 #ifndef PK_CASCADE_K0
 #define PK_CASCADE_K0 S   // first checkpoint of the steady-state cascade (1F1B)
@@ -377,6 +378,7 @@ struct poseidon_ctx {
     uint32_t grid_max;
     uint32_t full_grid;    // blocks of the recurrence pass behind the closed form
     uint32_t fuse_grid;    // blocks of the fused decode and closed form (0: not used)
+    uint32_t casc_grid;    // blocks of the recurrence for every candidate (0: not used)
     void *ws;              // cut codes, lists and queues of the passes (see ensure_workspace)
     uint64_t ws_n;         // candidates per chunk the workspace is for
     uint64_t ws_cap;       // entries of its arrays (ws_n and slack for per-block segments)
@@ -457,6 +459,42 @@ int poseidon_validate(const poseidon_problem *p, uint64_t *n_candidates) {
     if (n_candidates) *n_candidates = (uint64_t)tot;
     return POSEIDON_OK;
 }
+
+}  // extern "C"
+
+namespace {
+
+// Whether long calls on an Eager 1F1B problem with a closed form evaluate
+// every candidate by the recurrence alone (cascade_kernel) instead of the
+// closed form and then the recurrence for the lanes it does not prove.  The
+// proof asks every stage's forward and backward to outweigh every boundary,
+// so transfers of a layer or more leave most lanes without one; such a lane
+// costs more in the second way (its closed form, the list, 2 waves a SIMD
+// instead of 4), a proven one a tenth.  2^22 candidates of 16 stages, us,
+// recurrence / closed form first: 3 % unproven 940 / 217, 73 % about 940 /
+// 840, 88 % 918 / 1,093, all 916 / 1,125; 8 stages: 53 % 336 / 223, 88 %
+// 335 / 330, all 341 / 358.  The cascade's launches and tails cost shorter
+// calls more than it saves: all unproven, 100 micro-batches, 16 stages 2^20
+// 313 / 298, 2^21 514 / 552; 8 stages 2^21 245 / 229, 2^22 364 / 392; 4
+// stages 2^22 242 / 222.  Under 1F1B the two differ by at most 6 % either way
+// at any share, so it always takes the closed form first.
+constexpr double kCascadeShare = 0.85;
+constexpr uint64_t kCascadeMin = 3ull << 23;   // candidates times stages of a call
+
+// Estimated share of an Eager 1F1B problem's candidates without a proof.
+double eager_share(const pk::KParams &kp, const poseidon_problem *p, const uint64_t *cost, const uint32_t *pd,
+                   const uint32_t *ctab) {
+    uint32_t light = UINT32_MAX;
+    for (size_t i = 0; i < (size_t)p->T * p->L; ++i) light = std::min(light, std::min(p->fwd_us[i], p->bwd_us[i]));
+    if (kp.edge_max <= light) return 0;   // (every lane has the proof)
+    pk::KParams h = kp;
+    h.ctab = ctab;
+    return pk::unproven_share(h, pk::ShareTables{cost, pd, p->assign});
+}
+
+}  // namespace
+
+extern "C" {
 
 int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx **out) {
     if (!out) return POSEIDON_E_INVAL;
@@ -607,19 +645,10 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     // closed form (poseidon_closed.h); with fewer micro-batches the steady
     // part is at most S + 1 (Eager 1F1B: 2S + 2) iterations of the recurrence
     kp.closed = !ilv && !table_path && M >= (eager ? 4 * S + 2 : 2 * S + 2);
-    std::vector<uint32_t> ctab(pk::kCRows * pk::kSMax, 0);
-    for (uint32_t s = 0; s < S; ++s) {
-        auto row = [&](int r) { return &ctab[(size_t)r * pk::kSMax]; };
-        const uint32_t lo = s > 0 ? row(pk::kCE)[s - 1] : 0u, hi = s + 1 < S ? kp.cf[s] + kp.cb[s] : 0u;
-        row(pk::kCE)[s] = hi;
-        row(pk::kCSum)[s] = s > 0 ? row(pk::kCSum)[s - 1] + lo : 0u;
-        row(pk::kCE2)[s] = lo + hi;
-        // (1F1B, M > S; at most M times the boundaries' sum, below 2^31)
-        if (kp.closed) row(pk::kCE2n)[s] = (M - S + 1 + s) * (lo + hi);
-        row(pk::kCCb)[s] = s + 1 < S ? kp.cb[s] : 0u;
-        row(pk::kCPsi)[s] = s > 0 ? row(pk::kCPsi)[s - 1] + kp.cb[s - 1] : 0u;
-        kp.edge_max = std::max(kp.edge_max, hi);
-    }
+    uint32_t ctab[pk::kCRows * pk::kSMax];
+    pk::closed_constants(kp, ctab);
+    const double share = kp.closed && eager ? eager_share(kp, p, cost.data(), has_ar ? pd.data() : nullptr, ctab) : 0;
+    const bool unproven = share > kCascadeShare;
     // cascade checkpoints of the steady loop: K0, 2 K0, 4 K0, ... below M - S
     // (steady iterations: 1F1B slot pairs after its prologue, Eager 1F1B
     // slot pairs between its prologue and epilogue)
@@ -691,7 +720,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     const size_t o_slots = off; off = al(off + (table_path ? masks.size() * 4 : 0));
     const size_t o_pd = off; off = al(off + pd.size() * 4);
     const size_t o_ent = off; off = al(off + ent.size() * 4);
-    const size_t o_ctab = off; off = al(off + ctab.size() * 4);
+    const size_t o_ctab = off; off = al(off + sizeof(ctab));
     const size_t o_assign = off; off = al(off + (has_table ? (size_t)A * ndev : 0));   // (last: not part of the image)
     const size_t total = off;
 
@@ -723,7 +752,7 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
         if (table_path) put(o_slots, masks.data(), masks.size() * 4);
         if (has_ar) put(o_pd, pd.data(), pd.size() * 4);
         put(o_ent, ent.data(), ent.size() * 4);
-        put(o_ctab, ctab.data(), ctab.size() * 4);
+        put(o_ctab, ctab, sizeof(ctab));
         if (hipMemcpy(d, img.data(), o_assign, hipMemcpyHostToDevice) != hipSuccess ||
             (has_table && hipMemcpy(b + o_assign, p->assign, (size_t)A * ndev, hipMemcpyHostToDevice) != hipSuccess)) {
             status = POSEIDON_E_DEVICE;
@@ -778,6 +807,12 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
             status = POSEIDON_E_DEVICE;
             break;
         }
+        int casc = 0;
+        if (unproven && pk::cascade_occupancy(kp, elds, &casc) != hipSuccess) {
+            status = POSEIDON_E_DEVICE;
+            break;
+        }
+        ctx->casc_grid = (uint32_t)std::max(0, casc) * (uint32_t)std::max(1, prop.multiProcessorCount);
         ctx->fuse_grid = (uint32_t)std::max(0, fuse) * (uint32_t)std::max(1, prop.multiProcessorCount);
         ctx->full_grid = (uint32_t)std::max(1, full) * (uint32_t)std::max(1, prop.multiProcessorCount);
         // (at most grid_max: the survivor segments are sized for that many blocks)
@@ -886,9 +921,9 @@ struct ChunkGrid {
     uint32_t grid;
     uint64_t seg_cap;
 };
-ChunkGrid chunk_grid(const poseidon_ctx *ctx, uint64_t n) {
+ChunkGrid chunk_grid(uint64_t n, uint32_t grid_max) {
     ChunkGrid g;
-    g.grid = (uint32_t)std::min<uint64_t>((n + 255) / 256, ctx->grid_max);
+    g.grid = (uint32_t)std::min<uint64_t>((n + 255) / 256, grid_max);
     const uint64_t stride = (uint64_t)g.grid * 256;
     g.seg_cap = (n + stride - 1) / stride * 256;
     return g;
@@ -906,7 +941,7 @@ ChunkGrid fuse_chunk_grid(const poseidon_ctx *ctx, uint64_t n, bool succ) {
 }
 // Entries that hold any pass's segments for n candidates.
 uint64_t segment_cap(const poseidon_ctx *ctx, uint64_t n) {
-    const ChunkGrid g = chunk_grid(ctx, n);
+    const ChunkGrid g = chunk_grid(n, ctx->grid_max);
     uint64_t cap = std::max<uint64_t>(n, g.grid * g.seg_cap);
     for (int succ = 0; ctx->fuse_grid && succ < 2; ++succ) {
         const ChunkGrid f = fuse_chunk_grid(ctx, n, succ != 0);
@@ -915,16 +950,28 @@ uint64_t segment_cap(const poseidon_ctx *ctx, uint64_t n) {
     return cap;
 }
 
-// Interleaved 1F1B: slots of a straggler queue for chunks of n candidates
+// Cascades over HBM queues (Interleaved 1F1B; the recurrence for every
+// candidate): slots of a straggler queue for chunks of n candidates
 // (one block of slack per segment) and the words of an entry: candidate
 // index, cut codes, the assignment index (room for it whenever the problem
 // has more than one assignment; used by calls with a list of assignment
-// indices) and the live registers at a period boundary.
-uint64_t queue_cap(const poseidon_ctx *ctx, uint64_t n) { return n + (uint64_t)ctx->grid_max * 256; }
+// indices) and the live registers at a period boundary (of the recurrence:
+// S, Eager 1F1B 2S).
+uint32_t queue_grid(const poseidon_ctx *ctx) { return std::max(ctx->grid_max, ctx->casc_grid); }
+uint64_t queue_cap(const poseidon_ctx *ctx, uint64_t n) { return n + (uint64_t)queue_grid(ctx) * 256; }
 uint64_t queue_entry_words(const poseidon_ctx *ctx) {
-    return 1 + (uint64_t)pk::code_words((int)ctx->S) + (ctx->A > 1 ? 1 : 0) +
-           (uint64_t)pk::ilv_state_words(ctx->S, ctx->base.ndev);
+    const uint32_t sched = ctx->base.sched;
+    const uint64_t state = sched == POSEIDON_SCHEDULE_INTERLEAVED_1F1B ? (uint64_t)pk::ilv_state_words(ctx->S, ctx->base.ndev)
+                                                                      : (sched ? 2ull : 1ull) * ctx->S;
+    return 1 + (uint64_t)pk::code_words((int)ctx->S) + (ctx->A > 1 ? 1 : 0) + state;
 }
+// the straggler queues' words for arrays of cap candidates: two queues, then
+// the counts [levels][grid]
+uint64_t queue_words(const poseidon_ctx *ctx, uint64_t cap) {
+    return 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) + (uint64_t)pk::kMaxLevels * queue_grid(ctx);
+}
+// whether a context has passes that use them
+bool has_queues(const poseidon_ctx *ctx) { return ctx->base.nlevels && (!ctx->base.closed || ctx->casc_grid); }
 
 // Closed form: words per entry of the list of candidates without a proof
 // (position, cut codes, assignment), and of the recurrence pass's two queues
@@ -947,17 +994,17 @@ uint32_t tile_for(const poseidon_ctx *ctx, uint64_t n) {
     return (uint32_t)std::min<uint64_t>(kTile, (waves + grid - 1) / grid * 64);
 }
 
+// per-block counts of any pass
+uint64_t count_words(const poseidon_ctx *ctx) { return std::max(ctx->grid_max, ctx->fuse_grid); }
+
 // Workspace for chunks of up to `n` candidates (cap = n and one decode batch
 // per block of slack, so that per-block segments fit): the cut codes
 // [words][cap], the early-stop survivor indices [cap] and the first-stage
 // list [kAListWords][cap] (the closed form's list of candidates without a
 // proof takes the same words) with their per-block counts [count_words] each;
-// then the recurrence pass's queues (closed form), or two straggler queues
-// and their counts [levels][grid_max] (Interleaved 1F1B).  Grown on demand;
+// then, in the same words, the recurrence pass's queues (closed form) and
+// two straggler queues with their counts (queue_words).  Grown on demand;
 // the old buffer is released only after the stream has drained.
-// per-block counts of any pass
-uint64_t count_words(const poseidon_ctx *ctx) { return std::max(ctx->grid_max, ctx->fuse_grid); }
-
 int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     if (ctx->ws_n >= n) return POSEIDON_OK;
     if (ctx->ws) {
@@ -973,17 +1020,16 @@ int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     while (r < n && r < (1ull << 20)) r *= 2;
     n = (n + r - 1) / r * r;
     // (a multiple of 4 words: the range-mode decode stores four code words at once)
-    const uint64_t cap = (std::max<uint64_t>(segment_cap(ctx, n), n + (uint64_t)chunk_grid(ctx, n).grid * pk::kDecodeIlp * 256) + 3) & ~3ull;
+    const uint64_t cap = (std::max<uint64_t>(segment_cap(ctx, n), n + (uint64_t)chunk_grid(n, ctx->grid_max).grid * pk::kDecodeIlp * 256) + 3) & ~3ull;
     const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
     // cut codes, the early stop's survivor and first-stage lists and their counts
     uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * count_words(ctx);
-    if (ctx->base.closed) elems += tile_queue_words(ctx, tile_for(ctx, n)) * full_grid_for(ctx, n);
-    else if (ctx->base.nlevels)
-        elems += 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) + (uint64_t)pk::kMaxLevels * ctx->grid_max;
+    elems += std::max(ctx->base.closed ? tile_queue_words(ctx, tile_for(ctx, n)) * full_grid_for(ctx, n) : 0ull,
+                      has_queues(ctx) ? queue_words(ctx, cap) : 0ull);
     // the kernels address the code words, each list and each queue with
     // 32-bit word offsets (n is at most kChunk, so this always holds)
     if ((words + pk::kAListWords) * cap >= (1ull << 32) ||
-        (!ctx->base.closed && ctx->base.nlevels && queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32)))
+        (has_queues(ctx) && queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32)))
         return POSEIDON_E_RANGE;
     void *q = nullptr;
     if (hipMalloc(&q, elems * 4) != hipSuccess) {
@@ -1006,10 +1052,12 @@ int rearm(poseidon_ctx *ctx, hipStream_t st) {
 // Memory of one evaluation call: cut codes [words][cap] at `codes`; closed
 // form: the list of candidates without a proof [full_list_words][cap] at
 // `list` with counts [grid] at `counts`, and the recurrence pass's queues
-// for `tile` entries on `full_grid` blocks at `queues`; Interleaved 1F1B:
+// for `tile` entries on `full_grid` blocks at `queues`; Interleaved 1F1B and
+// `cascade` (the recurrence for every candidate instead of the closed form):
 // two straggler queues of qcap entries at `queues`, then their counts
 // [levels][grid].
 struct EvalMem {
+    bool cascade;
     uint64_t cap, qcap;
     uint32_t *codes, *list, *queues;
     unsigned int *counts;
@@ -1023,7 +1071,7 @@ struct EvalMem {
 constexpr uint32_t kNoallocTile = 256, kNoallocFullGrid = 256;
 uint64_t noalloc_layout(const poseidon_ctx *ctx, uint64_t n, uint32_t *base, EvalMem *m) {
     const uint64_t words = (uint64_t)pk::code_words((int)ctx->S);
-    const ChunkGrid g = chunk_grid(ctx, n);
+    const ChunkGrid g = chunk_grid(n, ctx->grid_max);
     memset(m, 0, sizeof(*m));
     uint64_t o = 0;
     const uint64_t cap = segment_cap(ctx, n);
@@ -1087,7 +1135,7 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
     kp.host_words = best_out ? ctx->hostw : nullptr;
     kp.codes = m.codes;
     kp.ccap = m.cap;
-    if (kp.closed) {
+    if (kp.closed && !m.cascade) {
         kp.flist = m.list;
         kp.fcount = m.counts;
         kp.tile = m.tile;
@@ -1102,8 +1150,9 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         kp.first_i = c0;
         kp.n_i = std::min(chunk, cands->count - c0);
         kp.accumulate = c0 > 0;
-        const bool fuse = ctx->fuse_grid != 0;
-        const ChunkGrid g = fuse ? fuse_chunk_grid(ctx, kp.n_i, !kp.comp_rank && ctx->A == 1) : chunk_grid(ctx, kp.n_i);
+        const bool fuse = ctx->fuse_grid != 0 && !m.cascade;
+        const ChunkGrid g = fuse ? fuse_chunk_grid(ctx, kp.n_i, !kp.comp_rank && ctx->A == 1)
+                                 : chunk_grid(kp.n_i, m.cascade ? ctx->casc_grid : ctx->grid_max);
         pk::LaunchCfg lc;
         lc.lds_bytes = ctx->base.sched == POSEIDON_SCHEDULE_INTERLEAVED_1F1B ? ctx->lds_bytes : ctx->ent_lds_bytes;
         lc.grid = g.grid;
@@ -1119,6 +1168,10 @@ int eval_chunks(poseidon_ctx *ctx, const poseidon_cands *cands, uint32_t *makesp
         pk::LaunchCfg ld = lc;
         ld.grid = (uint32_t)std::min<uint64_t>((kp.n_i + 4 * 256 - 1) / (4 * 256), ctx->grid_max);
         if (pk::launch_decode(kp, ld, st) != hipSuccess) return rearm(ctx, st);
+        if (m.cascade) {
+            if (pk::launch_cascade(kp, lc, st) != hipSuccess) return rearm(ctx, st);
+            continue;
+        }
         if (kp.closed) {
             if (pk::launch_closed(kp, lc, st) != hipSuccess || pk::launch_full(kp, lc, st) != hipSuccess)
                 return rearm(ctx, st);
@@ -1156,6 +1209,7 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands, uin
     rc = ensure_workspace(ctx, chunk, st);
     if (rc != POSEIDON_OK) return rc;
     EvalMem m;
+    m.cascade = ctx->casc_grid && cands->count * ctx->S >= kCascadeMin;
     m.cap = ctx->ws_cap;
     m.codes = (uint32_t *)ctx->ws;
     // (laid out as ensure_workspace describes it)

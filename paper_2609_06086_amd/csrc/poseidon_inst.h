@@ -8,6 +8,8 @@
 #define PK_INST(S)                                                                                              \
     template hipError_t launch_eval_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     template hipError_t launch_closed_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                       \
+    template hipError_t launch_cascade_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                      \
+    template hipError_t cascade_occupancy_s<S>(const KParams &, size_t, int *);                                    \
     template hipError_t launch_full_s<S>(const KParams &, const LaunchCfg &, hipStream_t);                         \
     template hipError_t launch_fused_s<S, uint32_t>(const KParams &, const LaunchCfg &, hipStream_t);              \
     template hipError_t launch_fused_s<S, uint64_t>(const KParams &, const LaunchCfg &, hipStream_t);              \

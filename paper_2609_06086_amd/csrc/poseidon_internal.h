@@ -223,6 +223,8 @@ hipError_t launch_decode(const KParams &p, const LaunchCfg &lc, hipStream_t st);
 // Problems with a closed form (KParams::closed): the closed-form pass over a
 // chunk, then the recurrence for the candidates it could not prove.
 hipError_t launch_closed(const KParams &p, const LaunchCfg &lc, hipStream_t st);
+hipError_t launch_cascade(const KParams &p, const LaunchCfg &lc, hipStream_t st);   // the recurrence for all
+hipError_t cascade_occupancy(const KParams &p, size_t lds, int *blocks);
 hipError_t launch_fused(const KParams &p, const LaunchCfg &lc, hipStream_t st);   // decode and closed form
 hipError_t fused_occupancy(const KParams &p, int *blocks);
 constexpr uint32_t kFuseThreads = 512;   // threads of its blocks

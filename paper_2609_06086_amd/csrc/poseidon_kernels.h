@@ -1112,7 +1112,7 @@ __device__ __forceinline__ unsigned long long make_key(bool feasible, uint32_t T
 // kernels
 // ---------------------------------------------------------------------------
 
-// Layout of one straggler queue (Interleaved 1F1B): idx[cap] | codes[kWords][cap] | asg[cap]
+// Layout of one straggler queue (the cascades over HBM): idx[cap] | codes[kWords][cap] | asg[cap]
 // (calls with a list of assignment indices) | Y[NX][cap].  The entry holds
 // the assignment index rather than the next level re-reading it from the
 // caller's list: a 4-byte read at a scattered index costs a whole memory
@@ -1738,7 +1738,122 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(KParams p) {
     block_min_and_finish(best, p.acc, p.done, p.result, nullptr, true, p.accumulate, nullptr, 0, host_out(p));
 }
 
-// The list of candidates without a closed-form proof, arrays of lcap
+// (a2)-(a4), (a6) for a chunk of an Eager 1F1B problem whose candidates mostly
+// have no closed-form proof: the recurrence for every candidate, in a cascade.
+// A lane whose steady state has not settled by pair p.lvl_k[0] is queued for
+// resume_kernel.  Held to 128 VGPRs (4 waves a SIMD instead of 3 at S = 16),
+// where full_kernel has 2: with none of the candidates proven (transfers of
+// 1-5 layers) 2^24 of 16 stages and 128 micro-batches take 3.28 ms so, 4.15
+// with the closed form and full_kernel; 2^22 of 300 and 1,000 micro-batches
+// 1.14 and 1.49 against 1.59 and 2.84.
+template <int S, bool AR>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void cascade_kernel(KParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Ent tab = entry_tables(p, smem);
+    const Comm<S> comm = load_comm<S>(p);
+    constexpr int NW = Codes<S>::kWords, NX = 2 * S;
+    unsigned long long best = ~0ull;
+    // 32-bit positions and trip counts as in eval_kernel
+    const uint32_t stride = gridDim.x * kBlock, n_i = (uint32_t)p.n_i, ccap = (uint32_t)p.ccap;
+    const uint32_t first_i = (uint32_t)p.first_i;
+    const uint32_t span = (n_i + stride - 1) / stride;
+    const uint32_t nit = p.M - 2 * S + 1, k1 = p.nlevels ? p.lvl_k[0] : nit;
+    __shared__ unsigned int nq;
+    if (threadIdx.x == 0) nq = 0;
+    __syncthreads();
+    uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    for (uint32_t it = 0; it < span; ++it, i += stride) {
+        const bool active = i < n_i;
+        const uint32_t gi = first_i + i;
+        uint32_t w[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = active ? p.codes[k * ccap + i] : 0u;
+        uint32_t cut[S + 1], to[S], F[S], B[S], Y[S], Fn[S], Fp[S];
+        const bool ok = unpack_cuts<S>(w, p.L, cut);
+        const uint32_t a = ok ? assign_of(p, gi) : 0u;
+        decode_toff<S>(p, tab, a, to);
+        const bool feas = stage_weights<S>(p, tab, cut, to, F, B) && ok && active;
+        eager_prologue<S>(Y, Fn, Fp, F, B, comm);
+        const bool done_here = eager_advance<S>(Y, Fn, Fp, F, B, comm, 0, k1, nit);
+        if (p.nlevels) {
+            uint32_t X[NX];
+            eager_pack<S>(Y, Fn, Fp, X);
+            enqueue<S, NX>(p, 0, &nq, !done_here && active && ok, gi, w, -1, X);
+        }
+        eager_epilogue<S>(Y, Fn, Fp, F, B, comm);
+        uint32_t T = end_time<S, AR>(p, tab, Y, comm, w, a);
+        if (!ok) T = 0xFFFFFFFFu;
+        const bool write = active && (done_here || !ok);
+        write_outputs(p, gi, write, T, feas);
+        if (write) {
+            const unsigned long long key = make_key(feas, T, gi);
+            best = key < best ? key : best;
+        }
+    }
+    if (p.nlevels) {
+        __syncthreads();
+        if (threadIdx.x == 0) p.qcount[blockIdx.x] = nq;   // entries for level 1
+    }
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, p.nlevels == 0, p.accumulate, nullptr, 0, host_out(p));
+}
+
+// Level `lvl` of that cascade: the queued lanes from steady pair
+// p.lvl_k[lvl-1] to p.lvl_k[lvl] (the end at the last level).  Block b takes
+// the segment that block b of the level before wrote.
+template <int S, bool AR>
+__global__ __launch_bounds__(kBlock) void resume_kernel(KParams p, uint32_t lvl) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Ent tab = entry_tables(p, smem);
+    const Comm<S> comm = load_comm<S>(p);
+    constexpr int NW = Codes<S>::kWords, NX = 2 * S;
+    const uint32_t nit = p.M - 2 * S + 1;
+    const uint32_t k0 = p.lvl_k[lvl - 1];
+    const uint32_t k1 = lvl < p.nlevels ? p.lvl_k[lvl] : nit;
+    const uint32_t n = p.qcount[(uint64_t)(lvl - 1) * p.nseg + blockIdx.x];
+    const QueueView<S> qin(p, (lvl - 1) & 1);
+    __shared__ unsigned int nq;
+    if (threadIdx.x == 0) nq = 0;
+    __syncthreads();
+    unsigned long long best = ~0ull;
+    const uint32_t span = (n + kBlock - 1) / kBlock;
+    // 32-bit word offsets: a queue holds fewer than 2^32 words
+    const uint32_t seg = blockIdx.x * (uint32_t)p.seg_cap, qcap = (uint32_t)p.qcap;
+    for (uint32_t it = 0; it < span; ++it) {
+        const uint32_t q = seg + it * kBlock + threadIdx.x;
+        const bool active = it * kBlock + threadIdx.x < n;
+        const uint32_t i = active ? qin.idx[q] : 0u;
+        uint32_t w[NW], cut[S + 1], to[S], F[S], B[S], X[NX], Y[S], Fn[S], Fp[S];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = active ? qin.codes[k * qcap + q] : 0u;
+#pragma unroll
+        for (int s = 0; s < NX; ++s) X[s] = active ? qin.Y[s * qcap + q] : 0u;
+        unpack_cuts<S>(w, p.L, cut);   // (a queued entry's codes were valid when it was queued)
+        const uint32_t a = !active ? 0u : p.qasg ? qin.asg[q] : assign_of(p, i);
+        decode_toff<S>(p, tab, a, to);
+        const bool feas = stage_weights<S>(p, tab, cut, to, F, B);
+        eager_unpack<S>(X, Y, Fn, Fp);
+        const bool settled = eager_advance<S>(Y, Fn, Fp, F, B, comm, k0, k1, nit);
+        if (lvl < p.nlevels) {
+            eager_pack<S>(Y, Fn, Fp, X);
+            enqueue<S, NX>(p, lvl & 1, &nq, active && !settled, i, w, a, X);
+        }
+        eager_epilogue<S>(Y, Fn, Fp, F, B, comm);
+        const uint32_t T = end_time<S, AR>(p, tab, Y, comm, w, a);
+        if (active && settled) {
+            // scattered one-word writes: the nontemporal hint keeps them out of L2 write-allocate
+            if (p.makespan_out) __builtin_nontemporal_store(T, p.makespan_out + i);
+            const unsigned long long key = make_key(feas, T, i);
+            best = key < best ? key : best;
+        }
+    }
+    if (lvl < p.nlevels) {
+        __syncthreads();
+        if (threadIdx.x == 0) p.qcount[(uint64_t)lvl * p.nseg + blockIdx.x] = nq;
+    }
+    block_min_and_finish(best, p.acc, p.done, p.result, nullptr, lvl == p.nlevels, p.accumulate, nullptr, 0, host_out(p));
+}
+
+// The list of candidates without a closed-form proof, arrays of ccap
 // entries: call position, cut codes, assignment index.  Block b of
 // closed_kernel fills slots [b * seg_cap, (b + 1) * seg_cap) and writes its
 // count to fcount[b].
@@ -2662,6 +2777,31 @@ hipError_t launch_closed_s(const KParams &p, const LaunchCfg &lc, hipStream_t st
                            lc.lds_bytes, st, p);
         return hipGetLastError();
     });
+}
+
+// The recurrence over a chunk, then its cascade's levels (p.nlevels + 1
+// launches on lc.grid blocks).
+template <int S, bool AR>
+hipError_t launch_cascade_ar(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    const dim3 g(lc.grid), b(kBlock);
+    hipLaunchKernelGGL((cascade_kernel<S, AR>), g, b, lc.lds_bytes, st, p);
+    hipError_t e = hipGetLastError();
+    for (uint32_t l = 1; l <= p.nlevels && e == hipSuccess; ++l) {
+        hipLaunchKernelGGL((resume_kernel<S, AR>), g, b, lc.lds_bytes, st, p, l);
+        e = hipGetLastError();
+    }
+    return e;
+}
+template <int S>
+hipError_t launch_cascade_s(const KParams &p, const LaunchCfg &lc, hipStream_t st) {
+    return p.has_ar ? launch_cascade_ar<S, true>(p, lc, st) : launch_cascade_ar<S, false>(p, lc, st);
+}
+
+// Resident blocks per CU of its first kernel.
+template <int S>
+hipError_t cascade_occupancy_s(const KParams &p, size_t lds, int *blocks) {
+    if (p.has_ar) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, cascade_kernel<S, true>, kBlock, lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, cascade_kernel<S, false>, kBlock, lds);
 }
 
 template <int S, typename R>

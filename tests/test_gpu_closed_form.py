@@ -113,3 +113,50 @@ def test_search_ties_and_runs(S):
                 assert (st.visited, st.evaluated, st.pruned_memory, st.pruned_ridge, st.pruned_bound) == \
                     (o["visited"], o["evaluated"], o["pruned_memory"], o["pruned_ridge"], o["pruned_bound"])
         ctx.close()
+
+
+@pytest.mark.parametrize("S,M,rows,mode", [(16, 66, 1, "list"), (12, 300, 5, "list"), (9, 38, 3, "range"), (16, 67, 1, "range")])
+def test_recurrence_alone_on_long_unproven_eager_calls(S, M, rows, mode):
+    """Eager 1F1B with transfers above the layers: no candidate has a proof, and a call of 3 * 2^23 candidates times
+    stages or more runs the recurrence for all of them (one to four levels of queues, one or several assignments, a
+    ragged end, invalid list entries refused as ever); a shorter call and the allocation-free one take the closed
+    form first.  All agree with each other, and with the oracle on a prefix."""
+    rng = np.random.default_rng(7400 + S + M)
+    dev = torch.device("cuda:0")
+    prob = W.random_problem(rng, S + 44, S, M, 2, cost_lo=20, cost_hi=60, comm_hi=0, assign_rows=rows)
+    prob.comm_fwd[:] = rng.integers(200, 4000, S - 1)
+    prob.schedule = P.SCHEDULE_EAGER_1F1B
+    if rows == 5:
+        prob.allreduce = rng.integers(0, 3000, size=(2, prob.L)).astype(np.uint32)
+    n = (3 << 23) // S + 12345
+    ctx = P.poseidon_load_costs(prob, 0)
+    cands = W.random_candidates(rng, prob, n) if mode == "list" else W.Candidates(first=prob.n_candidates // 3, count=n)
+
+    def run(call, k):
+        T = torch.full((k,), -1, dtype=torch.int32, device=dev)
+        bits = torch.full(((k + 31) // 32,), -1, dtype=torch.int32, device=dev)
+        if mode == "list":
+            kw = dict(comp_rank=torch.from_numpy(cands.comp_rank[:k].view(np.int64)).to(dev))
+            if rows > 1:
+                kw["assign_idx"] = torch.from_numpy(cands.assign_idx[:k].view(np.int32)).to(dev)
+        else:
+            kw = dict(first=cands.first, count=k)
+        return call(ctx, makespan_out=T, feasible_bits_out=bits, **kw), T, bits
+    a, Ta, ba = run(P.poseidon_eval_candidates, n)
+    b, Tb, bb = run(P.poseidon_eval_candidates_noalloc, n)
+    assert a == b and torch.equal(Ta, Tb) and torch.equal(ba, bb)
+    k = 20000
+    c, Tc, _ = run(P.poseidon_eval_candidates, k)
+    assert torch.equal(Ta[:k], Tc)
+    sub = (W.Candidates(comp_rank=cands.comp_rank[:k].copy(), assign_idx=cands.assign_idx[:k].copy() if rows > 1 else None)
+           if mode == "list" else W.Candidates(first=cands.first, count=k))
+    To, fo = coracle.evaluate(prob, sub)
+    assert np.array_equal(Tc.cpu().numpy().view(np.uint32), To)
+    if mode == "list":
+        bad = torch.from_numpy(cands.comp_rank.view(np.int64)).to(dev)
+        bad[n - 1] = prob.n_compositions
+        with pytest.raises(P.PoseidonError):
+            P.poseidon_eval_candidates(ctx, comp_rank=bad)
+        a2, Ta2, _ = run(P.poseidon_eval_candidates, n)     # and the context goes on
+        assert a2 == a and torch.equal(Ta2, Ta)
+    ctx.close()
