@@ -481,12 +481,55 @@ namespace {
 constexpr double kCascadeShare = 0.85;
 constexpr uint64_t kCascadeMin = 3ull << 23;   // candidates times stages of a call
 
+// Whether some transfer is heavy against the lightest layer: a boundary above
+// its F or B (Eager 1F1B: else every lane has the proof), or above half its
+// F + B (1F1B: else under 1 % lack it).
+bool heavy_transfers(const pk::KParams &kp, const poseidon_problem *p) {
+    uint32_t light = UINT32_MAX;
+    for (size_t i = 0; i < (size_t)p->T * p->L; ++i)
+        light = std::min(light, kp.sched ? std::min(p->fwd_us[i], p->bwd_us[i]) : (p->fwd_us[i] + p->bwd_us[i]) / 2);
+    return kp.edge_max > light;
+}
+
+// From how many early-stop survivors on (kp.surv_least), and up to how many
+// quarters of a batch per wave (kp.surv_direct), all take the recurrence at
+// once (surv_kernel).  The closed form saves work where a
+// wave has several batches, and more of it the deeper the pipeline; in fewer
+// it comes on top of the recurrence of the lanes it does not prove.  Eager
+// 1F1B where most lanes have the proof keeps it throughout.  Where none has,
+// no known makespan ever rules a lane out, and up to 8 stages it only costs.
+// Calls of 2^22
+// candidates, us, closed form first / recurrence at once (survivors, transfer
+// as a multiple of a tenth of a layer): 1F1B 4 stages (1.6e5, 3) 122 / 110,
+// (6.3e5, 3) 191 / 148, (4.2e6, 3) 227 / 183 but (4.2e6, 0.3) 163 / 175; 5
+// stages (7.2e5, 1) 188 / 146; 8 stages (2.8e5, 1) 144 / 127, (6.3e5, 30) 206 /
+// 162 but (4.1e6, 30) 262 / 373; 12 stages (1.9e4, 1) 124 / 113, (1.5e5, 10)
+// 148 / 136 but (1.5e5, 0.3) 129 / 136; 16 stages (4.2e4, 1) 138 / 125, (2.4e5,
+// 1) 156 / 174.  Eager 1F1B 16 stages (3.6e4, 0.3) 108 / 127, (3.6e4, 3) 181 /
+// 127, (9.5e5, 10: no lane proven) 427 / 437; 8 stages (2.4e5, 10) 142 / 124,
+// (4.1e6, 10) 231 / 446, (4.1e6, 30: none proven) 464 / 445; 4 stages (4.2e6,
+// 10: 77 % unproven) 238 / 200.  The least: so few survivors mostly all have
+// the proof (1F1B, light transfers, 6 stages and 146 micro-batches, 199
+// survivors 87 / 103; 8 stages 920 survivors 103 / 99, heavy ones 1,011 108 /
+// 98).
+void survivors_direct(pk::KParams &kp, bool heavy, double share) {
+    constexpr uint32_t kAll = 0xFFFFFFFFu;
+    const uint32_t S = kp.S;
+    kp.surv_least = kp.sched ? 0 : heavy ? 64 : 512;
+    if (kp.sched) {
+        if (share <= 0.25) kp.surv_direct = 0;
+        else if ((S <= 8 && share >= 1.0) || (S <= 5 && share > 0.6)) kp.surv_direct = kAll;
+        else kp.surv_direct = S <= 5 ? 16 : 4;
+    } else if (S <= 5) {
+        kp.surv_direct = heavy ? kAll : 16;
+    } else {
+        kp.surv_direct = S <= 8 ? 8 : heavy ? 4 : 1;
+    }
+}
+
 // Estimated share of an Eager 1F1B problem's candidates without a proof.
 double eager_share(const pk::KParams &kp, const poseidon_problem *p, const uint64_t *cost, const uint32_t *pd,
                    const uint32_t *ctab) {
-    uint32_t light = UINT32_MAX;
-    for (size_t i = 0; i < (size_t)p->T * p->L; ++i) light = std::min(light, std::min(p->fwd_us[i], p->bwd_us[i]));
-    if (kp.edge_max <= light) return 0;   // (every lane has the proof)
     pk::KParams h = kp;
     h.ctab = ctab;
     return pk::unproven_share(h, pk::ShareTables{cost, pd, p->assign});
@@ -647,7 +690,9 @@ int poseidon_load_costs(const poseidon_problem *p, int hip_device, poseidon_ctx 
     kp.closed = !ilv && !table_path && M >= (eager ? 4 * S + 2 : 2 * S + 2);
     uint32_t ctab[pk::kCRows * pk::kSMax];
     pk::closed_constants(kp, ctab);
-    const double share = kp.closed && eager ? eager_share(kp, p, cost.data(), has_ar ? pd.data() : nullptr, ctab) : 0;
+    const bool heavy = kp.closed && heavy_transfers(kp, p);
+    const double share = heavy && eager ? eager_share(kp, p, cost.data(), has_ar ? pd.data() : nullptr, ctab) : 0;
+    if (kp.closed) survivors_direct(kp, heavy, share);
     const bool unproven = share > kCascadeShare;
     // cascade checkpoints of the steady loop: K0, 2 K0, 4 K0, ... below M - S
     // (steady iterations: 1F1B slot pairs after its prologue, Eager 1F1B

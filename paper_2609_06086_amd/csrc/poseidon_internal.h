@@ -95,6 +95,8 @@ struct KParams {
                                       // this many steady periods
     uint32_t closed;              // 1F1B / Eager 1F1B with M large enough for the closed form
     uint32_t edge_max;            // largest cf_s + cb_s
+    uint32_t surv_direct, surv_least; // early stop: from surv_least survivors up to surv_direct quarters of a
+                                      // batch per wave (of the whole grid) all take the recurrence at once
     const uint32_t *ctab;         // [kCRows][kSMax] constants of the closed form (ClosedRow)
     uint32_t psi[kSMax];          // cf_0 + ... + cf_{s-1}: undoes the per-stage shift at the end
     uint32_t fixed_word[kSMax / 4];   // kAssignFixed: the stages' (devices') types, one byte each

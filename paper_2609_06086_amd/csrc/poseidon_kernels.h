@@ -2680,8 +2680,14 @@ __device__ __forceinline__ bool closed_or_bound(const KParams &p, const Ent &tab
 // survivors spread over the whole grid, 64 to a wave.  Only the blocks the
 // list needs (one per kBlock survivors, at least one) go on: the others
 // leave before loading the entries and take no ticket on the done counter.
-// Bound by latency (14 % VALU issue: 0.1-0.8 % of the candidates come here):
-// 29 us at 8 stages, 42 us at 16 of calls of 491 and 287 us.
+// Bound by latency (0.1-0.8 % of the candidates come here).  With few batches
+// a wave the closed form does not shorten the chain: some lane of some wave
+// needs the recurrence all the same, after it, unless they are so few that
+// all have the proof.  So from p.surv_least survivors up to p.surv_direct
+// quarters of a batch per wave all take the recurrence at once (the limits
+// and what they were measured on are at their rule in the host code).
+// 8 stages, 7.0e4 survivors of 2^26: 25 us, 29 with the closed form first; 16
+// stages, 1.0e5 of 2^24: 51 us with it first, 62 at once.
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publish, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2712,6 +2718,7 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
         return make_key(true, dp_full_settle<S, SCH, AR>(p, tab, F, B, comm, w, a), i);
     };
     unsigned long long best = ~0ull;
+    const bool closed = p.closed && (n < p.surv_least || (uint64_t)n * 4 > (uint64_t)p.surv_direct * (gridDim.x * kBlock));
     const uint32_t lane = threadIdx.x & 63;
     for (uint32_t k0 = blockIdx.x * kBlock + (threadIdx.x - lane); k0 < n; k0 += gridDim.x * kBlock) {   // (wave-uniform)
         const uint32_t k = k0 + lane;
@@ -2726,13 +2733,13 @@ __global__ __launch_bounds__(kBlock) void surv_kernel(KParams p, uint32_t publis
                 else hi = mid;
             }
             at = lo * (uint32_t)p.seg_cap + (k - pre[lo]);
-            if (p.closed) {
+            if (closed) {
                 uint32_t a, w[NW], cut[S + 1], to[S], F[S], B[S];
                 load(at, i, a, w, cut, to, F, B);
                 proven = closed_or_bound<S, AR, SCH>(p, tab, cut, to, F, B, T);
             }
         }
-        pend_add(l, k < n, proven, at, T, i, best, full, p.closed ? 64u : 1u);
+        pend_add(l, k < n, proven, at, T, i, best, full, closed ? 64u : 1u);
     }
     best = pend_finish(l, best, p.acc, full);
     block_min_and_finish(best, p.acc, p.done, nullptr, p.run_best, true, false, publish ? p.snap : nullptr, need, host_out(p));

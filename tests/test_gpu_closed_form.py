@@ -160,3 +160,37 @@ def test_recurrence_alone_on_long_unproven_eager_calls(S, M, rows, mode):
         a2, Ta2, _ = run(P.poseidon_eval_candidates, n)     # and the context goes on
         assert a2 == a and torch.equal(Ta2, Ta)
     ctx.close()
+
+
+@pytest.mark.parametrize("S,schedule,comm_hi", [(4, 0, 60), (4, 0, 9000), (5, 1, 9000), (8, 0, 60), (8, 1, 9000),
+                                                (12, 0, 60), (12, 0, 9000), (16, 1, 9000), (16, 1, 300)])
+def test_survivors_in_few_and_in_many_batches(S, schedule, comm_hi):
+    """Early stop with the limits of survivors that take the recurrence at once on both sides: from a handful of
+    survivors to all of 600,000 candidates (several batches a wave), light and dominating transfers.  The best and
+    the counters are those of an exhaustive evaluation and of the bound applied to every candidate."""
+    rng = np.random.default_rng(7500 + 20 * S + schedule)
+    dev = torch.device("cuda:0")
+    prob = W.random_problem(rng, 3 * S + 6, S, (4 if schedule else 2) * S + 9, 2, cost_lo=80, cost_hi=220,
+                            comm_hi=comm_hi, mem_hi=9, cap=9 * (3 * S + 6), assign_rows=3)
+    prob.schedule = schedule
+    n = 600000
+    cands = W.random_candidates(rng, prob, n)
+    kw = dict(comp_rank=torch.from_numpy(cands.comp_rank.view(np.int64)).to(dev),
+              assign_idx=torch.from_numpy(cands.assign_idx.view(np.int32)).to(dev))
+    ctx = P.poseidon_load_costs(prob, 0)
+    best = P.poseidon_eval_candidates(ctx, **kw)
+    To, fo = coracle.evaluate(prob, W.Candidates(comp_rank=cands.comp_rank[:2000].copy(),
+                                                 assign_idx=cands.assign_idx[:2000].copy()))
+    kept = []
+    for bound in (best.makespan, int(1.02 * best.makespan), int(1.3 * best.makespan), 2 ** 31 - 1):
+        b, st = P.poseidon_eval_candidates_bounded(ctx, bound, **kw)
+        assert (b.index, b.makespan) == (best.index, best.makespan), bound
+        assert st.evaluated + st.pruned + st.infeasible == n
+        kept.append(st.evaluated)
+    assert kept == sorted(kept) and kept[-1] == n      # (every candidate fits the caps)
+    b, st = P.poseidon_eval_candidates_bounded(ctx, best.makespan - 1, **kw)
+    assert b.index is None
+    # a prefix against the oracle's own makespans
+    b, st = P.poseidon_eval_candidates_bounded(ctx, 2 ** 31 - 1, **{k: v[:2000] for k, v in kw.items()})
+    assert (b.index, b.makespan) == coracle.argmin(To, fo)
+    ctx.close()
