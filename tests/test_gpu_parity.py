@@ -828,3 +828,31 @@ def test_maximum_layer_and_type_counts(dev):
         digits.schedule = schedule
         assert digits.A == 8 ** 8
         check_against_oracle(digits, W.random_candidates(rng, digits, 5000), dev)
+
+
+def test_more_contexts_than_pinned_result_slots():
+    """70 contexts at once: 64 have a slot of pinned host words for their results, the others read theirs with a
+    copy.  Every context, evaluated and early-stopped alone and with the others alive, gives the oracle's result, and
+    slots that were given back serve again."""
+    rng = np.random.default_rng(640)
+    probs = [W.random_problem(rng, 12, 4, 13, 2, cap=10 ** 6, assign_rows=2) for _ in range(70)]
+    want = []
+    for prob in probs:
+        To, fo = coracle.evaluate(prob, W.Candidates(first=0, count=prob.n_candidates))
+        want.append(coracle.argmin(To, fo))
+    ctxs = [P.poseidon_load_costs(prob, 0) for prob in probs]
+    for turn in range(2):
+        for ctx, prob, w in zip(ctxs, probs, want):
+            b = P.poseidon_eval_candidates(ctx, first=0, count=prob.n_candidates)
+            assert (b.index, b.makespan) == w
+            b, st = P.poseidon_eval_candidates_bounded(ctx, 2 ** 31 - 1, first=0, count=prob.n_candidates)
+            assert (b.index, b.makespan) == w and st.evaluated == prob.n_candidates
+            b, st = P.poseidon_eval_candidates_bounded(ctx, w[1] - 1, first=0, count=prob.n_candidates)
+            assert b.index is None
+            with pytest.raises(P.PoseidonError):    # an invalid entry is refused, and the context goes on
+                P.poseidon_eval_candidates(ctx, comp_rank=torch.tensor([prob.n_compositions], dtype=torch.int64, device="cuda:0"))
+        for i in range(0, 70, 3):                   # slots go back and are taken again
+            ctxs[i].close()
+            ctxs[i] = P.poseidon_load_costs(probs[i], 0)
+    for ctx in ctxs:
+        ctx.close()
