@@ -285,7 +285,7 @@ def eval_record(wl, dev, args, schedule="1f1b", early_stop=True, cpu_s=0.0, py_s
            "candidates_per_s": n / (ms_wall * 1e-3), "dag_nodes_per_s": n * 2 * S * M / (ms_wall * 1e-3),
            "best": {"index": best.index, "makespan_us": best.makespan},
            "roofline": roofline(committed_counters(profile_tag("eval_pipeline", prob, schedule), n), call_ms, ops,
-                                algo_bytes, "one poseidon_eval_candidates call: decode, eval and resume kernels")}
+                                algo_bytes, "one poseidon_eval_candidates call: all its kernels")}
     if early_stop and wl.cands.is_list and schedule != "interleaved":
         bound = e.warm_bound()
         es_ms_wall, es_ms, (bb, st) = timed(torch, lambda: e.bounded(bound, args.es_chunk, args.es_ramp),
@@ -426,7 +426,7 @@ def profile_only(args):
 # ------------------------------------------------------------------ summaries
 
 PASS_KERNELS = {
-    "exhaustive": r"pk::(fused_kernel|closed_kernel|full_kernel|decode_kernel|eval_kernel|ilv_kernel|ilv_resume_kernel)",
+    "exhaustive": r"pk::(fused_kernel|closed_kernel|full_kernel|decode_kernel|eval_kernel|cascade_kernel|resume_kernel|ilv_kernel|ilv_resume_kernel)",
     "early_stop": r"pk::(filter_kernel|surv_kernel|fill_u64)",
     "search": r"pk::(search_|fill_u64)",
 }

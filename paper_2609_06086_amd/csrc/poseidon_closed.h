@@ -47,14 +47,14 @@
 // leave room for the walks between stages.
 //
 // Lanes without proof are evaluated by the recurrence.  How many those are
-// depends on the transfers.  1F1B, 16 and 8 stages of some 8-10 layers:
-// 0.2-0.5 % at cf + cb of a tenth to a third of a layer (also when every layer
-// costs the same), 5 and 2 % at 1-3 layers, 30 and 19 % at 3-10.  Eager 1F1B's
-// condition is the stricter one, over all stages and boundaries at once: none
-// while no boundary outweighs the lightest layer on the fastest type, 9 % of
-// the 16-stage synthetic workload, where some do, 88 and 53 % at a third of a
-// layer to one, and nearly all beyond.  (The value itself is exact for almost
-// all of them.)
+// depends on the transfers.  1F1B, 16 and 8 stages of some 8-10 layers each:
+// 0.4 % where cf + cb is a tenth to a third of a layer (also when every layer
+// costs the same), 7 and 6 % at one to three layers, 36 and 25 % at three to
+// ten.  Eager 1F1B's condition is the stricter one, over all stages and
+// boundaries at once: none while no boundary outweighs the lightest layer on
+// the fastest type, 9 % of the 16-stage synthetic workload, where some do, 94
+// and 45 % at a quarter of a layer to one, and nearly all beyond.  (The value
+// is exact for almost all of them.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -92,10 +92,9 @@ __global__ __launch_bounds__(kBlock) void argmin_kernel(const uint32_t *T, const
 // out coalesced.  The kernel sits between the count and write launches of
 // every level and its time is the latency of its loads, so it reads nothing
 // else (the counters go to slots the host sums).  A block has at most
-// 256 (L - 1)^2 < 2^22 children (fused levels, L <= 129) and a run at most
-// kSearchScanMax / 256 = 64 blocks, so an offset within its run fits 32 bits
-// in LDS; the run's own 64-bit start is kept beside it (a whole piece can
-// exceed 2^32 children).
+// 256 (L - 1) < 2^16 children and a run at most kSearchScanMax / 256 = 64
+// blocks, so an offset within its run fits 32 bits in LDS; the run's own start
+// is kept beside it.
 
 __device__ __forceinline__ uint32_t scan_pad(uint32_t b) { return b + (b >> 6); }
 
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(kBlock) void search_scan_kernel(SearchParams q, uin
     }
 }
 
-static_assert((uint64_t)(kSearchScanMax / kBlock) * kBlock * 128 * 128 < (1ull << 32),
+static_assert((uint64_t)(kSearchScanMax / kBlock) * kBlock * (POSEIDON_L_MAX - 1) < (1ull << 32),
               "a scan run's offsets must fit 32 bits");
 
 // Start of a chunk: its bound is min(caller's bound, best so far).

@@ -2004,7 +2004,9 @@ __device__ __forceinline__ void fused_all(const KParams &p, unsigned char *smem)
     block_min<NT>(best, p.acc, part);
 }
 
-// (128 VGPRs: two blocks of eight waves a CU at S = 16)
+// (128 VGPRs: two blocks of eight waves a CU at S = 16.  With all-reduce times
+// the drain keeps A, B and D of every stage, and at S = 16 70 registers, Eager
+// 1F1B 49, go to scratch; without, and up to S = 13 with them, none)
 template <int S, typename R, bool AR, bool SCH>
 __global__ __launch_bounds__(kFuseBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void fused_kernel(KParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2057,11 +2059,15 @@ __global__ __launch_bounds__(kBlock) void closed_kernel(KParams p) {
 // checkpoint of the steady part, the ones that have not settled are packed
 // into the block's queue and run to the next, and so on, so that the few
 // long transients share waves.  Queue entries carry position, cut codes,
-// assignment and the DP state; blocks share nothing.  Bound by latency: few
-// lanes (0.2-0.5 % of a chunk) on long serial chains, 18 % VALU issue.  It
-// takes 60 us of the 8-stage and 45 us of the 16-stage calls (2^26, 2^24);
-// the launches per checkpoint over the whole chunk's queue that it replaces
-// took 653 and 510 us for the 20 % of lanes the stencil left unsettled.
+// assignment and the DP state; blocks share nothing.  Under 1F1B bound by
+// latency: few lanes (0.2-0.5 % of a chunk with transfers of a tenth of a
+// layer) on long serial chains, 18 % VALU issue.  It takes 83 us of the
+// 8-stage and 58 us of the 16-stage calls (2^26, 2^24); the launches per
+// checkpoint over the whole chunk's queue that it replaces took 653 and 510 us
+// for the 20 % of lanes the stencil left unsettled.  Under Eager 1F1B the list
+// is longer (9 % of the 16-stage workload: 422 of 775 us) and the state larger
+// (192 VGPRs at S = 16, 2 waves a SIMD); calls that would list nearly
+// everything take cascade_kernel instead.
 template <int S, bool AR, bool SCH>
 __global__ __launch_bounds__(kBlock) void full_kernel(KParams p, uint32_t nseg) {
     extern __shared__ __align__(16) unsigned char smem[];

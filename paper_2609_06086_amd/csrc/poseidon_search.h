@@ -158,7 +158,7 @@ __device__ __forceinline__ int search_try(const KParams &p, const Lds &tab, cons
 }
 
 // Per-type tables of the stage tests, built in LDS behind the stage tables
-// by the count and write kernels: fb = prefix fwd + prefix bwd, mfb = M fb
+// by the count kernel and the last pass: fb = prefix fwd + prefix bwd, mfb = M fb
 // (below 2^31 like every path weight, checked at load), and hm[t][lo] = the
 // largest h with layers [lo, h) within type t's memory cap.  Without
 // all-reduce times a stage's Eq. 2 test is then one compare, mfb[h] against

@@ -86,9 +86,8 @@ def test_search_monotone_last_stage(dev):
 
 
 def test_search_long_models_unfused(dev):
-    """L > 129 layers: one block's grandchildren could exceed a frontier piece,
-    so the level before the last cut is expanded on its own (the fused
-    expansion covers L <= 129 everywhere else)."""
+    """140-160 layers and 3 to 5 stages: few nodes above the last pass, each
+    with up to 1.2 x 10^4 complete configurations, and 8 halvings a search."""
     rng = np.random.default_rng(125)
     for S, rows in ((3, 4), (4, 3), (5, 2)):
         L = 140 + int(rng.integers(0, 20))
@@ -116,9 +115,9 @@ def test_search_deep_pipelines(dev):
 
 def test_search_maximum_layer_and_type_counts(dev):
     """T = 8 with L = 256 (the largest tables: cut values up to 255, LDS stage
-    and search tables for 8 types; above the fused-level limit) and with
-    L = 120, S = 4 (fused), with and without all-reduce times, the ridge
-    filter and growing chunks."""
+    and search tables and stage entries for 8 types, over 64 KB together) and
+    with L = 120, S = 4, with and without all-reduce times, the ridge filter
+    and growing chunks."""
     rng = np.random.default_rng(124)
     for trial in range(6):
         L, S = (256, 3) if trial < 4 else (120, 4)
