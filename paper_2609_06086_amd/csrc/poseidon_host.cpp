@@ -381,8 +381,10 @@ struct poseidon_ctx {
     uint32_t casc_grid;    // blocks of the recurrence for every candidate (0: not used)
     void *ws;              // cut codes, lists and queues of the passes (see ensure_workspace)
     uint64_t ws_n;         // candidates per chunk the workspace is for
+    bool ws_queues;        // it has the recurrence cascade's queues
     uint64_t ws_cap;       // entries of its arrays (ws_n and slack for per-block segments)
     void *sws;             // search frontiers (allocated on the first poseidon_search)
+    bool search_list;      // they end with the last pass's list
     unsigned long long *shost;   // pinned host words for the search's read-backs (level totals
                                  // and block offsets), allocated with sws
     unsigned long long *hostw;   // pinned host words for results (HostPool), or null
@@ -1015,8 +1017,6 @@ uint64_t queue_entry_words(const poseidon_ctx *ctx) {
 uint64_t queue_words(const poseidon_ctx *ctx, uint64_t cap) {
     return 2 * queue_entry_words(ctx) * queue_cap(ctx, cap) + (uint64_t)pk::kMaxLevels * queue_grid(ctx);
 }
-// whether a context has passes that use them
-bool has_queues(const poseidon_ctx *ctx) { return ctx->base.nlevels && (!ctx->base.closed || ctx->casc_grid); }
 
 // Closed form: words per entry of the list of candidates without a proof
 // (position, cut codes, assignment), and of the recurrence pass's two queues
@@ -1048,16 +1048,20 @@ uint64_t count_words(const poseidon_ctx *ctx) { return std::max(ctx->grid_max, c
 // list [kAListWords][cap] (the closed form's list of candidates without a
 // proof takes the same words) with their per-block counts [count_words] each;
 // then, in the same words, the recurrence pass's queues (closed form) and
-// two straggler queues with their counts (queue_words).  Grown on demand;
-// the old buffer is released only after the stream has drained.
-int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
-    if (ctx->ws_n >= n) return POSEIDON_OK;
+// two straggler queues with their counts (queue_words; with `cascade`, or
+// without a closed form).  Grown on demand; the old buffer is released only
+// after the stream has drained.
+int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st, bool cascade = false) {
+    if (ctx->ws_n >= n && (ctx->ws_queues || !cascade)) return POSEIDON_OK;
+    n = std::max(n, ctx->ws_n);
+    const bool queues = ctx->base.nlevels && (!ctx->base.closed || cascade);
     if (ctx->ws) {
         if (hipStreamSynchronize(st) != hipSuccess) return POSEIDON_E_DEVICE;
         (void)hipFree(ctx->ws);
         ctx->ws = nullptr;
         ctx->ws_cap = 0;
         ctx->ws_n = 0;
+        ctx->ws_queues = false;
     }
     // a power of two up to 2^20, then a multiple of it, so that calls of
     // slowly growing size do not reallocate each time
@@ -1070,11 +1074,11 @@ int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     // cut codes, the early stop's survivor and first-stage lists and their counts
     uint64_t elems = (words + 1 + pk::kAListWords) * cap + 2ull * count_words(ctx);
     elems += std::max(ctx->base.closed ? tile_queue_words(ctx, tile_for(ctx, n)) * full_grid_for(ctx, n) : 0ull,
-                      has_queues(ctx) ? queue_words(ctx, cap) : 0ull);
+                      queues ? queue_words(ctx, cap) : 0ull);
     // the kernels address the code words, each list and each queue with
     // 32-bit word offsets (n is at most kChunk, so this always holds)
     if ((words + pk::kAListWords) * cap >= (1ull << 32) ||
-        (has_queues(ctx) && queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32)))
+        (queues && queue_entry_words(ctx) * queue_cap(ctx, cap) >= (1ull << 32)))
         return POSEIDON_E_RANGE;
     void *q = nullptr;
     if (hipMalloc(&q, elems * 4) != hipSuccess) {
@@ -1084,6 +1088,7 @@ int ensure_workspace(poseidon_ctx *ctx, uint64_t n, hipStream_t st) {
     ctx->ws = q;
     ctx->ws_cap = cap;
     ctx->ws_n = n;
+    ctx->ws_queues = cascade;
     return POSEIDON_OK;
 }
 
@@ -1251,10 +1256,15 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands, uin
         return POSEIDON_OK;
     }
     const uint64_t chunk = std::min<uint64_t>(cands->count, kChunk);
-    rc = ensure_workspace(ctx, chunk, st);
-    if (rc != POSEIDON_OK) return rc;
     EvalMem m;
     m.cascade = ctx->casc_grid && cands->count * ctx->S >= kCascadeMin;
+    rc = ensure_workspace(ctx, chunk, st, m.cascade);
+    if (rc == POSEIDON_E_NOMEM && m.cascade) {   // (its queues are several times the rest: never tried again)
+        m.cascade = false;
+        ctx->casc_grid = 0;
+        rc = ensure_workspace(ctx, chunk, st);
+    }
+    if (rc != POSEIDON_OK) return rc;
     m.cap = ctx->ws_cap;
     m.codes = (uint32_t *)ctx->ws;
     // (laid out as ensure_workspace describes it)
@@ -1464,7 +1474,7 @@ SearchWs search_layout(poseidon_ctx *ctx, size_t *bytes) {
     w.slot_row = (uint32_t *)(b + o); o += pk::kSlotMax * 4;
     w.slot_w = (uint32_t *)(b + o); o += words * pk::kSlotMax * 4;
     w.words = (unsigned long long *)(b + o); o += SW_COUNT * 8;
-    if (!ctx->base.closed) {
+    if (ctx->search_list) {
         w.list_n = (unsigned int *)(b + o); o += pk::kListParts * 4;
         w.list = (uint32_t *)(b + o); o += (2 + words) * pk::kListParts * pk::kListCap * 4;
     }
@@ -1587,13 +1597,17 @@ extern "C" int poseidon_search(poseidon_ctx *ctx, uint64_t first_row, uint64_t n
     DeviceGuard g(ctx->device);
     if (!g.ok) return POSEIDON_E_DEVICE;
     if (!ctx->sws) {
+        // (without a closed form with the list, where the memory is there for it)
         size_t bytes = 0;
-        search_layout(ctx, &bytes);
-        if (hipMalloc(&ctx->sws, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            ctx->sws = nullptr;
-            return POSEIDON_E_NOMEM;
+        for (int list = !ctx->base.closed && ctx->S > 1; list >= 0 && !ctx->sws; --list) {
+            ctx->search_list = list != 0;
+            search_layout(ctx, &bytes);
+            if (hipMalloc(&ctx->sws, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                ctx->sws = nullptr;
+            }
         }
+        if (!ctx->sws) return POSEIDON_E_NOMEM;
     }
     if (!ctx->shost) {
         if (hipHostMalloc((void **)&ctx->shost, ((size_t)kSearchBlk + 2) * 8, hipHostMallocDefault) != hipSuccess) {

@@ -188,7 +188,7 @@ struct SearchParams {
     unsigned long long *slot_key;     // [kSlotMax] its blocks' bests, with the configuration that has each
     uint32_t *slot_row, *slot_w;      // [kSlotMax], [words][kSlotMax]
     unsigned int *list_n;             // [kListParts] entries offered to each part of the list (may exceed its room)
-    uint32_t *list;                   // [2 + words][kListParts kListCap]: node and choice, row, cut codes
+    uint32_t *list;                   // [2 + words][kListParts kListCap]: node and choice, row, cut codes; or null
     unsigned long long *best;         // makespan, row, composition rank of the best so far
     unsigned long long *total;        // children of the scanned level piece (one word per level)
     uint32_t root_first;              // first row of a root piece

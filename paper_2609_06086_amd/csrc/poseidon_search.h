@@ -724,11 +724,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(S <= 8 ?
                 if (lane >= (uint32_t)o) incl += u;
             }
             const uint32_t total = __shfl(incl, 63, 64);
-            uint32_t slot = 0, lpart = 0;
+            uint32_t slot = kListCap, lpart = 0;
             if constexpr (!CLOSED) {   // room for all of them in one part of the list (the parts in turn)
-                lpart = npend++ % kListParts;
-                if (lane == 0) slot = atomicAdd(&q.list_n[lpart], total);
-                slot = __builtin_amdgcn_readfirstlane(slot);
+                if (q.list) {
+                    lpart = npend++ % kListParts;
+                    if (lane == 0) slot = atomicAdd(&q.list_n[lpart], total);
+                    slot = __builtin_amdgcn_readfirstlane(slot);
+                }
             }
             for (uint32_t o0 = 0; o0 < total; o0 += 64) {
                 const uint32_t o = o0 + lane;

@@ -194,3 +194,26 @@ def test_survivors_in_few_and_in_many_batches(S, schedule, comm_hi):
     b, st = P.poseidon_eval_candidates_bounded(ctx, 2 ** 31 - 1, **{k: v[:2000] for k, v in kw.items()})
     assert (b.index, b.makespan) == coracle.argmin(To, fo)
     ctx.close()
+
+
+def test_recurrence_alone_between_other_calls():
+    """The queues of the recurrence alone come and go with a context's calls: early stop and short evaluations before,
+    between and after long ones that take it, on a workspace that grows."""
+    rng = np.random.default_rng(7600)
+    dev = torch.device("cuda:0")
+    prob = W.random_problem(rng, 30, 8, 40, 2, cost_lo=20, cost_hi=60, comm_hi=0, assign_rows=1)
+    prob.comm_fwd[:] = 900
+    prob.schedule = P.SCHEDULE_EAGER_1F1B
+    ranks = torch.from_numpy(W.random_candidates(rng, prob, 3 << 21).comp_rank.view(np.int64)).to(dev)
+    ctx = P.poseidon_load_costs(prob, 0)
+    seen = {}
+    for n, bounded in ((1000, False), (1000, True), (3 << 20, False), (5000, True), (3 << 20, True), (7 << 19, True),
+                       (3 << 20, False), (3 << 21, False), (3 << 21, True), (3 << 20, False), (1000, False)):
+        if bounded:
+            b, st = P.poseidon_eval_candidates_bounded(ctx, 2 ** 31 - 1, comp_rank=ranks[:n])
+        else:
+            b = P.poseidon_eval_candidates(ctx, comp_rank=ranks[:n])
+        assert seen.setdefault(n, (b.index, b.makespan)) == (b.index, b.makespan), (n, bounded)
+        c = P.poseidon_eval_candidates_noalloc(ctx, comp_rank=ranks[:n])
+        assert (c.index, c.makespan) == seen[n]
+    ctx.close()
