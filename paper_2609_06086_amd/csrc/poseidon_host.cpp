@@ -478,10 +478,18 @@ namespace {
 // 335 / 330, all 341 / 358.  The cascade's launches and tails cost shorter
 // calls more than it saves: all unproven, 100 micro-batches, 16 stages 2^20
 // 313 / 298, 2^21 514 / 552; 8 stages 2^21 245 / 229, 2^22 364 / 392; 4
-// stages 2^22 242 / 222.  Under 1F1B the two differ by at most 6 % either way
+// stages 2^22 242 / 222.  With up to 5 stages and so few micro-batches that
+// the cascade has one or two levels it is ahead from shorter calls on: 3 and 4
+// stages, 4S + 2 micro-batches, 2^18 71 / 95 and 72 / 93, 2^22 147 / 193 and
+// 172 / 204; two levels, 3 stages 2^20 138 / 134, 2^21 151 / 160, 2^22 175 /
+// 200.  Under 1F1B the two differ by at most 6 % either way
 // at any share, so it always takes the closed form first.
 constexpr double kCascadeShare = 0.85;
-constexpr uint64_t kCascadeMin = 3ull << 23;   // candidates times stages of a call
+// candidates of a call from which on it is taken (nlevels: its levels)
+uint64_t cascade_min(uint32_t S, uint32_t nlevels) {
+    if (S <= 5 && nlevels <= 2) return nlevels <= 1 ? 1ull << 18 : 1ull << 21;
+    return (3ull << 23) / S;
+}
 
 // Whether some transfer is heavy against the lightest layer: a boundary above
 // its F or B (Eager 1F1B: else every lane has the proof), or above half its
@@ -1257,7 +1265,7 @@ int poseidon_eval_candidates(poseidon_ctx *ctx, const poseidon_cands *cands, uin
     }
     const uint64_t chunk = std::min<uint64_t>(cands->count, kChunk);
     EvalMem m;
-    m.cascade = ctx->casc_grid && cands->count * ctx->S >= kCascadeMin;
+    m.cascade = ctx->casc_grid && cands->count >= cascade_min(ctx->S, ctx->base.nlevels);
     rc = ensure_workspace(ctx, chunk, st, m.cascade);
     if (rc == POSEIDON_E_NOMEM && m.cascade) {   // (its queues are several times the rest: never tried again)
         m.cascade = false;

@@ -115,10 +115,11 @@ def test_search_ties_and_runs(S):
         ctx.close()
 
 
-@pytest.mark.parametrize("S,M,rows,mode", [(16, 66, 1, "list"), (12, 300, 5, "list"), (9, 38, 3, "range"), (16, 67, 1, "range")])
+@pytest.mark.parametrize("S,M,rows,mode", [(16, 66, 1, "list"), (12, 300, 5, "list"), (9, 38, 3, "range"), (16, 67, 1, "range"),
+                                            (3, 14, 5, "list"), (4, 18, 1, "list"), (5, 32, 3, "list")])
 def test_recurrence_alone_on_long_unproven_eager_calls(S, M, rows, mode):
     """Eager 1F1B with transfers above the layers: no candidate has a proof, and a call of 3 * 2^23 candidates times
-    stages or more runs the recurrence for all of them (one to four levels of queues, one or several assignments, a
+    stages or more (fewer at 3 to 5 stages and few micro-batches) runs the recurrence for all of them (one to four levels of queues, one or several assignments, a
     ragged end, invalid list entries refused as ever); a shorter call and the allocation-free one take the closed
     form first.  All agree with each other, and with the oracle on a prefix."""
     rng = np.random.default_rng(7400 + S + M)
@@ -216,4 +217,36 @@ def test_recurrence_alone_between_other_calls():
         assert seen.setdefault(n, (b.index, b.makespan)) == (b.index, b.makespan), (n, bounded)
         c = P.poseidon_eval_candidates_noalloc(ctx, comp_rank=ranks[:n])
         assert (c.index, c.makespan) == seen[n]
+    ctx.close()
+
+
+@pytest.mark.parametrize("comm", [0, 900])
+def test_captured_evaluation_replays(comm):
+    """A long Eager 1F1B call, with the closed form and with the recurrence alone, and the allocation-free call,
+    captured into a graph (no result read back: no copy, no fill) and replayed with other work between."""
+    rng = np.random.default_rng(7700 + comm)
+    dev = torch.device("cuda:0")
+    prob = W.random_problem(rng, 30, 8, 40, 2, cost_lo=20, cost_hi=60, comm_hi=0, assign_rows=1)
+    prob.comm_fwd[:] = comm
+    prob.schedule = P.SCHEDULE_EAGER_1F1B
+    n = 3 << 20
+    ranks = torch.from_numpy(W.random_candidates(rng, prob, n).comp_rank.view(np.int64)).to(dev)
+    ctx = P.poseidon_load_costs(prob, 0)
+    for call in (P.poseidon_eval_candidates, P.poseidon_eval_candidates_noalloc):
+        T0 = torch.zeros(n, dtype=torch.int32, device=dev)
+        want = call(ctx, comp_rank=ranks, makespan_out=T0)          # (grows the workspace)
+        T = torch.zeros(n, dtype=torch.int32, device=dev)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            call(ctx, comp_rank=ranks, makespan_out=T, want_best=False, stream=torch.cuda.current_stream())
+        for turn in range(4):
+            T.fill_(-1)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(T, T0), turn
+            b = P.poseidon_last_best(ctx)
+            assert (b.index, b.makespan) == (want.index, want.makespan), turn
+            P.poseidon_eval_candidates(ctx, comp_rank=ranks[:1000 + turn])   # the context's own eager work
+        del g
     ctx.close()
